@@ -11,19 +11,23 @@
 //             handed to pirrt_insert_batch / pirrt_batch_add_problem on the device.
 //   heuristic: binary32 rounding of the binary64 distance to the goal.
 //
-// The radius search is brute force over all earlier vertices: a workgroup owns 256
-// consecutive new vertices (one per thread) and streams the earlier points through
-// LDS in tiles every thread reads by broadcast.  It runs twice (count, then write
-// candidates in ascending u); the segment tests then run once per candidate and a
-// scan compacts the survivors into rows.
+// The radius search runs on the matrix cores (search.hip) while every point lies in the
+// unit cube and no row has more than kSearchRowMax candidates.  Otherwise it is done in
+// binary64 over all earlier vertices (k_radius): a workgroup owns 256 consecutive new
+// vertices (one per thread) and streams the earlier points through LDS in tiles every
+// thread reads by broadcast, twice (count, then write candidates in ascending u); the
+// segment tests then run once per candidate and a scan compacts the survivors into rows.
 #include <string.h>
 
+#include <algorithm>
 #include <cmath>
 #include <string>
 #include <vector>
 
+#include "geom.h"
 #include "internal.h"
 #include "pirrt.h"
+#include "search.h"
 
 using namespace pirrt;
 
@@ -32,13 +36,6 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kTile = 256;
 constexpr int kMaxDim = 8;
-
-struct ObsView {
-  int32_t n;
-  const int32_t* kind;
-  const double* centre;
-  const double* size;
-};
 
 __device__ __forceinline__ void philox(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, uint32_t k0, uint32_t k1,
                                        uint32_t out[4]) {
@@ -58,97 +55,6 @@ __device__ __forceinline__ void philox(uint32_t c0, uint32_t c1, uint32_t c2, ui
   out[1] = c1;
   out[2] = c2;
   out[3] = c3;
-}
-
-template <int D>
-__device__ __forceinline__ bool point_blocked(const double* x, const ObsView& ob) {
-  for (int o = 0; o < ob.n; ++o) {
-    const double* c = ob.centre + (int64_t)o * D;
-    const double* s = ob.size + (int64_t)o * D;
-    if (ob.kind[o] == 0) {
-      double d2 = 0.0;
-#pragma unroll
-      for (int k = 0; k < D; ++k) {
-        const double e = x[k] - c[k];
-        d2 = __dadd_rn(d2, __dmul_rn(e, e));
-      }
-      if (d2 <= __dmul_rn(s[0], s[0])) return true;
-    } else {
-      bool inside = true;
-#pragma unroll
-      for (int k = 0; k < D; ++k)
-        if (fabs(x[k] - c[k]) > s[k]) inside = false;
-      if (inside) return true;
-    }
-  }
-  return false;
-}
-
-template <int D>
-__device__ __forceinline__ bool hits_sphere(const double* a, const double* b, const double* c, double rad) {
-  double ee = 0.0, ce = 0.0;
-#pragma unroll
-  for (int k = 0; k < D; ++k) {
-    const double e = b[k] - a[k];
-    ee = __dadd_rn(ee, __dmul_rn(e, e));
-    ce = __dadd_rn(ce, __dmul_rn(c[k] - a[k], e));
-  }
-  double t = ee > 0.0 ? __ddiv_rn(ce, ee) : 0.0;
-  if (t < 0.0) t = 0.0;
-  if (t > 1.0) t = 1.0;
-  double q2 = 0.0;
-#pragma unroll
-  for (int k = 0; k < D; ++k) {
-    const double q = __dadd_rn(a[k], __dmul_rn(t, b[k] - a[k])) - c[k];
-    q2 = __dadd_rn(q2, __dmul_rn(q, q));
-  }
-  return q2 <= __dmul_rn(rad, rad);
-}
-
-template <int D>
-__device__ __forceinline__ bool hits_box(const double* a, const double* b, const double* c, const double* half) {
-  double lo_t = 0.0, hi_t = 1.0;
-#pragma unroll
-  for (int k = 0; k < D; ++k) {
-    const double lo = c[k] - half[k], hi = c[k] + half[k];
-    const double e = b[k] - a[k];
-    if (e == 0.0) {
-      if (a[k] < lo || a[k] > hi) return false;
-      continue;
-    }
-    double t_lo = __ddiv_rn(lo - a[k], e), t_hi = __ddiv_rn(hi - a[k], e);
-    if (t_lo > t_hi) {
-      const double s = t_lo;
-      t_lo = t_hi;
-      t_hi = s;
-    }
-    if (t_lo > lo_t) lo_t = t_lo;
-    if (t_hi < hi_t) hi_t = t_hi;
-    if (lo_t > hi_t) return false;
-  }
-  return true;
-}
-
-template <int D>
-__device__ __forceinline__ bool segment_blocked(const double* a, const double* b, const ObsView& ob) {
-  for (int o = 0; o < ob.n; ++o) {
-    const double* c = ob.centre + (int64_t)o * D;
-    const double* s = ob.size + (int64_t)o * D;
-    const bool hit = ob.kind[o] == 0 ? hits_sphere<D>(a, b, c, s[0]) : hits_box<D>(a, b, c, s);
-    if (hit) return true;
-  }
-  return false;
-}
-
-template <int D>
-__device__ __forceinline__ double dist2(const double* a, const double* b) {
-  double d2 = 0.0;
-#pragma unroll
-  for (int k = 0; k < D; ++k) {
-    const double e = a[k] - b[k];
-    d2 = __dadd_rn(d2, __dmul_rn(e, e));
-  }
-  return d2;
 }
 
 // Candidates k0 .. k0 + T - 1: coordinates into cbuf, free flag into flag.
@@ -403,6 +309,21 @@ struct pirrt_rrg {
   int64_t* rp = nullptr;
   int32_t* col = nullptr;
   float* cost = nullptr;
+  int64_t col_cap = 0;
+  // matrix-core search: packed points, candidate lists and finished rows of a slab
+  uint4* rec = nullptr;
+  int64_t rec_cap = 0, packed = 0;  // records of room; points packed so far
+  int32_t* scand = nullptr;
+  float* sccost = nullptr;
+  int64_t scand_cap = 0;
+  int32_t* scnt = nullptr;
+  int64_t scnt_cap = 0;
+  int32_t* sdeg = nullptr;
+  int64_t* soff = nullptr;
+  int64_t sdeg_cap = 0;
+  SearchState* sstate = nullptr;
+  int32_t room = 128;      // candidates a row is expected to have at most
+  bool outside = false;    // a point outside the unit cube: no matrix-core search
   float* hbuf = nullptr;
   int64_t hcap = 0;
   // learned sampler scratch (at most kSelMax candidates)
@@ -547,12 +468,156 @@ void launch_heuristic(pirrt_rrg* R, const double* goal, float* h) {
     default: call(8); break;       \
   }
 
+// Where the rows go: the handle's own arrays, or device buffers of the caller that hold
+// `capacity` entries (written only when the rows fit; col / cost may be NULL).
+struct RowsOut {
+  int64_t* rp;
+  int32_t* col;
+  float* cost;
+  int64_t capacity;
+};
+
+constexpr int64_t kSlabEntries = (int64_t)1 << 27;  // candidate room of one slab of rows
+
+// Room for `need` entries of rows, the first `keep` kept.
+int ensure_rows(pirrt_rrg* R, int64_t need, int64_t keep) {
+  if (need <= R->col_cap) return PIRRT_OK;
+  int64_t c = need + need / 4 + 1024, cc = R->col_cap;
+  int rc;
+  if ((rc = grow(R, &R->col, &cc, c, keep))) return rc;
+  cc = R->col_cap;
+  if ((rc = grow(R, &R->cost, &cc, c, keep))) return rc;
+  R->col_cap = cc;
+  return PIRRT_OK;
+}
+
+// The rows by the matrix-core search.  *done stays false where that search does not
+// apply (points outside the unit cube, rows of more than kSearchRowMax candidates).
+// Lists that turn out too short are made longer and the slab searched again; the room
+// is remembered, so a handle learns the density of its scene once.
+int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direct, int64_t* nnz, bool* done,
+                bool* wrote) {
+  const int64_t rows = R->n - n_old;
+  hipStream_t s = R->stream;
+  int rc;
+  *done = *wrote = false;
+  if (R->outside) return PIRRT_OK;
+  if (!R->sstate) {
+    if (!ralloc(&R->sstate, 1)) return rfail(R, PIRRT_ENOMEM, "device allocation of the search state failed");
+    RHIP(R, hipMemsetAsync(R->sstate, 0, sizeof(SearchState), s));
+  }
+  if (R->n + kSearchPad > R->rec_cap) {
+    int64_t c = 2 * R->rec_cap;
+    if ((rc = grow(R, &R->rec, &c, 2 * (R->n + kSearchPad), 2 * R->packed))) return rc;
+    R->rec_cap = c / 2;
+  }
+  SearchArgs a;
+  a.d = R->d;
+  a.n_old = n_old;
+  a.n = R->n;
+  a.radius = radius;
+  a.pts = R->pts;
+  a.obs = obs_view(R);
+  a.rec = R->rec;
+  a.state = R->sstate;
+  // enough workgroups to fill the chip: a row's earlier points are cut into chunks, each
+  // with its own candidate list
+  const int64_t groups = (rows + (rows >= kSearchWideRows ? 511 : 127)) / (rows >= kSearchWideRows ? 512 : 128);
+  int64_t nch = (kSearchGroups + groups - 1) / groups;
+  nch = std::max<int64_t>(1, std::min<int64_t>({nch, kSearchMaxChunks, (R->n + kSearchPad - 1) / kSearchPad}));
+  a.chunk = ((R->n + nch - 1) / nch + kSearchPad - 1) / kSearchPad * kSearchPad;
+  a.nch = (int32_t)((R->n + a.chunk - 1) / a.chunk);
+  a.cap = a.nch == 1 ? R->room : std::max(16, (2 * R->room / a.nch + 3) / 4 * 4);
+  int64_t base = 0;
+  for (int64_t row0 = 0; row0 < rows;) {
+    const int64_t stride = (int64_t)a.nch * a.cap;
+    const int64_t slab = std::min(rows - row0, std::max<int64_t>(kSearchPad, kSlabEntries / stride));
+    a.row0 = row0;
+    a.rows = (int32_t)slab;
+    if (slab * stride > R->scand_cap) {
+      rfree(R->scand); rfree(R->sccost);
+      R->scand_cap = 0;
+      if (!ralloc(&R->scand, slab * stride) || !ralloc(&R->sccost, slab * stride))
+        return rfail(R, PIRRT_ENOMEM, "device allocation of candidate lists failed");
+      R->scand_cap = slab * stride;
+    }
+    if (slab * a.nch > R->scnt_cap) {
+      rfree(R->scnt);
+      R->scnt_cap = 0;
+      if (!ralloc(&R->scnt, slab * a.nch)) return rfail(R, PIRRT_ENOMEM, "device allocation of list lengths failed");
+      R->scnt_cap = slab * a.nch;
+    }
+    if (slab + 1 > R->sdeg_cap) {
+      rfree(R->sdeg); rfree(R->soff);
+      R->sdeg_cap = 0;
+      if (!ralloc(&R->sdeg, slab + 1) || !ralloc(&R->soff, slab + 1))
+        return rfail(R, PIRRT_ENOMEM, "device allocation of row lengths failed");
+      R->sdeg_cap = slab + 1;
+    }
+    if ((rc = ensure_scan(R, slab + 1))) return rc;
+    if ((rc = ensure_rows(R, base + slab * 64, base))) return rc;
+    a.cand = R->scand;
+    a.ccost = R->sccost;
+    a.cnt = R->scnt;
+    a.deg = R->sdeg;
+    const bool own = !direct || slab < rows;  // several slabs are gathered in the handle's arrays
+    int64_t* rp = own ? R->rp : direct->rp;
+    launch_search_pack(R->d, R->packed, R->n, R->pts, R->rec, R->sstate, s);
+    R->packed = R->n;
+    launch_search(a, s);
+    launch_search_rows(a, base, own ? R->col_cap : direct->capacity, rp, own ? R->col : direct->col,
+                       own ? R->cost : direct->cost, R->soff, R->scan, s);
+    RHIP(R, hipGetLastError());
+    SearchState* st = reinterpret_cast<SearchState*>(R->host);
+    RHIP(R, hipMemcpyAsync(st, R->sstate, sizeof(SearchState), hipMemcpyDeviceToHost, s));
+    RHIP(R, hipStreamSynchronize(s));
+    if (st->outside) {
+      R->outside = true;
+      return PIRRT_OK;
+    }
+    if (st->listed || st->most > kSearchRowMax) return PIRRT_OK;
+    if (st->most) {  // longer lists, the same slab again
+      a.cap = (st->most + st->most / 4 + 3) / 4 * 4;
+      R->room = std::max(R->room, a.nch == 1 ? a.cap : std::min(a.cap * a.nch / 2, kSearchRowMax));
+      continue;
+    }
+    if (own && st->nnz > R->col_cap) {
+      if ((rc = ensure_rows(R, st->nnz, base))) return rc;
+      continue;
+    }
+    base = st->nnz;
+    row0 += slab;
+    *wrote = !own;
+  }
+  *nnz = base;
+  *done = true;
+  return PIRRT_OK;
+}
+
 // Forward rows of points [n_old, n) in R->rp / col / cost; *nnz their entries.
-int build_rows(pirrt_rrg* R, int64_t n_old, double radius, int64_t* nnz) {
+// direct (nullable): device buffers of the caller; *wrote tells whether the rows went
+// there (if they fit) instead.
+int build_rows(pirrt_rrg* R, int64_t n_old, double radius, int64_t* nnz, const RowsOut* direct = nullptr,
+               bool* wrote = nullptr) {
   const int64_t rows = R->n - n_old;
   hipStream_t s = R->stream;
   int rc;
   *nnz = 0;
+  if (rows + 1 > R->rp_cap) {
+    rfree(R->rp);
+    R->rp_cap = 0;
+    if (!ralloc(&R->rp, rows + 1 + (rows + 1) / 2)) return rfail(R, PIRRT_ENOMEM, "device allocation of rows failed");
+    R->rp_cap = rows + 1 + (rows + 1) / 2;
+  }
+  if (rows == 0) {
+    RHIP(R, hipMemsetAsync(R->rp, 0, sizeof(int64_t), s));
+    RHIP(R, hipStreamSynchronize(s));
+    return PIRRT_OK;
+  }
+  bool done = false, to_caller = false;
+  if ((rc = search_rows(R, n_old, radius, direct, nnz, &done, &to_caller))) return rc;
+  if (wrote) *wrote = to_caller;
+  if (done) return PIRRT_OK;
   // per-(row, chunk) counts and their scan: cnt / cptr hold rows * nch (+1) entries
   const int32_t nch = (int32_t)((R->n + kChunk - 1) / kChunk);
   const int64_t cells = rows * nch;
@@ -564,17 +629,6 @@ int build_rows(pirrt_rrg* R, int64_t n_old, double radius, int64_t* nnz) {
     if (!ralloc(&R->cnt, c) || !ralloc(&R->cptr, c))
       return rfail(R, PIRRT_ENOMEM, "device allocation of row offsets failed");
     R->rows_cap = c;
-  }
-  if (rows + 1 > R->rp_cap) {
-    rfree(R->rp);
-    R->rp_cap = 0;
-    if (!ralloc(&R->rp, rows + 1 + (rows + 1) / 2)) return rfail(R, PIRRT_ENOMEM, "device allocation of rows failed");
-    R->rp_cap = rows + 1 + (rows + 1) / 2;
-  }
-  if (rows == 0) {
-    RHIP(R, hipMemsetAsync(R->rp, 0, sizeof(int64_t), s));
-    RHIP(R, hipStreamSynchronize(s));
-    return PIRRT_OK;
   }
   if ((rc = ensure_scan(R, cells + 1))) return rc;
   const double r2 = radius * radius;
@@ -589,14 +643,15 @@ int build_rows(pirrt_rrg* R, int64_t n_old, double radius, int64_t* nnz) {
   const int64_t m = R->host[0];
   if (m > ((int64_t)1 << 40)) return rdev(R, hipErrorUnknown, "candidate count out of range");
   if (m + 1 > R->cand_cap) {
-    rfree(R->cand_u); rfree(R->cand_v); rfree(R->keep); rfree(R->kpos); rfree(R->ccost); rfree(R->col); rfree(R->cost);
+    rfree(R->cand_u); rfree(R->cand_v); rfree(R->keep); rfree(R->kpos); rfree(R->ccost);
     R->cand_cap = 0;
     const int64_t c = (m + 1) + (m + 1) / 4 + 1024;
     if (!ralloc(&R->cand_u, c) || !ralloc(&R->cand_v, c) || !ralloc(&R->keep, c) || !ralloc(&R->kpos, c + 1) ||
-        !ralloc(&R->ccost, c) || !ralloc(&R->col, c) || !ralloc(&R->cost, c))
+        !ralloc(&R->ccost, c))
       return rfail(R, PIRRT_ENOMEM, "device allocation of candidate edges failed");
     R->cand_cap = c;
   }
+  if ((rc = ensure_rows(R, m + 1, 0))) return rc;
   if ((rc = ensure_scan(R, m + 1))) return rc;
   if (m > 0) {
 #define RAD_WRITE(D) launch_radius<D>(R, n_old, r2, nch, true)
@@ -677,6 +732,7 @@ void release(pirrt_rrg* R) {
   rfree(R->okind); rfree(R->ocentre); rfree(R->osize); rfree(R->pts); rfree(R->cbuf); rfree(R->flag); rfree(R->pos);
   rfree(R->cnt); rfree(R->cptr); rfree(R->cand_u); rfree(R->cand_v); rfree(R->keep); rfree(R->kpos); rfree(R->ccost);
   rfree(R->rp); rfree(R->col); rfree(R->cost); rfree(R->hbuf); rfree(R->dword); rfree(R->dflag);
+  rfree(R->rec); rfree(R->scand); rfree(R->sccost); rfree(R->scnt); rfree(R->sdeg); rfree(R->soff); rfree(R->sstate);
   rfree(R->lpts); rfree(R->lfeat); rfree(R->llogit); rfree(R->lenc); rfree(R->lflag); rfree(R->lsel);
   if (R->scan) (void)hipFree(R->scan);
   R->scan = nullptr;
@@ -882,9 +938,12 @@ int pirrt_rrg_rows(pirrt_rrg* R, int64_t n_old, double radius, int64_t* row_ptr,
   if (!(radius > 0.0) || !std::isfinite(radius)) return rfail(R, PIRRT_EINVAL, "radius must be finite and > 0");
   if (!nnz || !row_ptr) return rfail(R, PIRRT_EINVAL, "nnz or row_ptr is NULL");
   int64_t m = 0;
-  if ((rc = build_rows(R, n_old, radius, &m))) return rc;
+  const RowsOut direct{row_ptr, col, cost, capacity};
+  bool wrote = false;
+  if ((rc = build_rows(R, n_old, radius, &m, mem_kind == PIRRT_MEM_DEVICE ? &direct : nullptr, &wrote))) return rc;
   *nnz = m;
   if (m > capacity) return rfail(R, PIRRT_EINVAL, "capacity below the entry count (returned in *nnz)");
+  if (wrote) return PIRRT_OK;
   const hipMemcpyKind kind = mem_kind == PIRRT_MEM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice;
   RHIP(R, hipMemcpyAsync(row_ptr, R->rp, sizeof(int64_t) * (size_t)(R->n - n_old + 1), kind, R->stream));
   if (m > 0 && col) RHIP(R, hipMemcpyAsync(col, R->col, sizeof(int32_t) * (size_t)m, kind, R->stream));
