@@ -62,6 +62,9 @@ template <int D>
 __global__ void __launch_bounds__(kThreads) k_candidates(int64_t T, uint64_t k0, uint64_t seed, uint32_t stream,
                                                          ObsView ob, double* __restrict__ cbuf,
                                                          int32_t* __restrict__ flag) {
+  __shared__ NearObstacles<D> spheres;
+  spheres.load(ob);
+  __syncthreads();
   const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (t >= T) return;
   const uint64_t k = k0 + (uint64_t)t;
@@ -73,7 +76,7 @@ __global__ void __launch_bounds__(kThreads) k_candidates(int64_t T, uint64_t k0,
   for (int i = 0; i < D; ++i) x[i] = (double)(w[i] >> 8) * (1.0 / 16777216.0);
 #pragma unroll
   for (int i = 0; i < D; ++i) cbuf[t * D + i] = x[i];
-  flag[t] = point_blocked<D>(x, ob) ? 0 : 1;
+  flag[t] = spheres.point_blocked(x, ob) ? 0 : 1;
 }
 
 // Appends the free candidates whose rank (pos) is below `need`; records one past

@@ -83,7 +83,8 @@ __global__ void __launch_bounds__(kThreads) k_search_pack(int64_t first, int64_t
   if (!in) atomicOr(&state->outside, 1);
 }
 
-// A wave owns NB blocks of 32 rows, a workgroup 4 NB of them; the earlier points of the
+// A wave owns NB blocks of 32 rows, a workgroup 4 NB of them, and takes NU tiles of 32
+// earlier points together (NB x NU = 4 independent matrix instructions); the earlier points of the
 // workgroup's chunk go through LDS in stages of 256 (8 tiles), the next stage's loads in
 // flight.  Lane l holds column l % 32 of a block's result: the two lanes of a row share
 // its candidate count in registers, and candidates are written as they are found, in no
@@ -91,7 +92,7 @@ __global__ void __launch_bounds__(kThreads) k_search_pack(int64_t first, int64_t
 // instruction, a three-way maximum over the 16 results' bits and a branch.
 // (Two waves per SIMD at least: the compiler then keeps the results in VGPRs, where the
 // maximum reads them, instead of accumulation registers.)
-template <int NB>
+template <int NB, int NU>
 __global__ void __launch_bounds__(kThreads, 2) k_search(int64_t n_old, int64_t n, int64_t row0, int32_t rows,
                                                      const uint4* __restrict__ rec, float half_t, int32_t nch,
                                                      int64_t chunk, int32_t cap, int32_t* __restrict__ cand,
@@ -139,28 +140,33 @@ __global__ void __launch_bounds__(kThreads, 2) k_search(int64_t n_old, int64_t n
       next1 = rec[2 * (u0 + kStage) + kThreads + threadIdx.x];
     }
     const int tiles = u_end - u0 < kStage ? (int)((u_end - u0 + 31) / 32) : kStage / 32;
-    for (int t = 0; t < tiles; ++t) {
-      const f16x8 a = __builtin_bit_cast(f16x8, tile[buf][2 * (32 * t + col) + half]);
-      f32x16 acc[NB];
+    for (int t0 = 0; t0 < tiles; t0 += NU) {
+      f32x16 acc[NU][NB];
 #pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        f32x16 zero;
+      for (int j = 0; j < NU; ++j) {
+        const f16x8 a = __builtin_bit_cast(f16x8, tile[buf][2 * (32 * (t0 + j) + col) + half]);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) zero[r] = 0.0f;
-        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, vb[b], zero, 0, 0, 0);
+        for (int b = 0; b < NB; ++b) {
+          f32x16 zero;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) zero[r] = 0.0f;
+          acc[j][b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, vb[b], zero, 0, 0, 0);
+        }
       }
 #pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        int top = __float_as_int(acc[b][0]);
+      for (int jb = 0; jb < NU * NB; ++jb) {
+        const int j = jb / NB, b = jb % NB, t = t0 + j;
+        if (t >= tiles) break;
+        int top = __float_as_int(acc[j][b][0]);
 #pragma unroll
         for (int r = 1; r < 16; ++r) {
-          const int x = __float_as_int(acc[b][r]);
+          const int x = __float_as_int(acc[j][b][r]);
           top = x > top ? x : top;
         }
         if (__ballot(top >= 0) == 0ull) continue;  // no sign bit is clear: no candidate
         uint32_t neg = 0;
 #pragma unroll
-        for (int r = 15; r >= 0; --r) neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(acc[b][r]), 31);
+        for (int r = 15; r >= 0; --r) neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(acc[j][b][r]), 31);
         uint32_t m = ~neg & 0xffffu;  // bit r: result r, point 8 (r / 4) + 4 half + r % 4 of the tile
         const int64_t row = r_wave + b * 32 + col, v = n_old + row0 + row;
         const int64_t ut = u0 + 32 * t;
@@ -203,6 +209,7 @@ __global__ void __launch_bounds__(kThreads, 2) k_search(int64_t n_old, int64_t n
 // costs over the row's candidates.
 constexpr int kFinLanes = 32;
 constexpr int kFinRows = kThreads / kFinLanes;
+constexpr int kRankStep = 8;  // ids compared per step of the ranking
 
 template <int D>
 __global__ void __launch_bounds__(kThreads) k_search_finish(int64_t n_old, int64_t row0, int32_t rows, double r2,
@@ -211,9 +218,11 @@ __global__ void __launch_bounds__(kThreads) k_search_finish(int64_t n_old, int64
                                                             const int32_t* __restrict__ cnt,
                                                             float* __restrict__ ccost, int32_t* __restrict__ deg,
                                                             SearchState* __restrict__ state) {
-  __shared__ int32_t ids[kFinRows][kSearchRowMax];
+  __shared__ int32_t ids[kFinRows][kSearchRowMax + kRankStep];
   __shared__ float cst[kFinRows][kSearchRowMax];
+  __shared__ NearObstacles<D> spheres;
   if (state->outside || state->most) return;
+  spheres.load(ob);
   const int g = threadIdx.x / kFinLanes, l = threadIdx.x % kFinLanes;
   const int64_t row = (int64_t)blockIdx.x * kFinRows + g;
   const bool live = row < rows;
@@ -230,10 +239,15 @@ __global__ void __launch_bounds__(kThreads) k_search_finish(int64_t n_old, int64
     }
     const int at = total + incl - k;
     total += __shfl(incl, kFinLanes - 1, kFinLanes);
-    if (nch > 1) {
-      const int32_t* list = cand + (row * nch + c) * cap;
-      for (int i = 0; i < k; ++i)
-        if (at + i < kSearchRowMax) ids[g][at + i] = list[i];
+    if (nch > 1 && k > 0) {  // (lists are 16 bytes aligned: their room is a multiple of 4)
+      const int4* list = reinterpret_cast<const int4*>(cand + (row * nch + c) * cap);
+      for (int i = 0; i < k; i += 4) {
+        const int4 w = list[i / 4];
+        const int32_t u[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (i + e < k && at + i + e < kSearchRowMax) ids[g][at + i + e] = u[e];
+      }
     }
   }
   if (total > kSearchRowMax) {
@@ -244,9 +258,7 @@ __global__ void __launch_bounds__(kThreads) k_search_finish(int64_t n_old, int64
   float* outc = ccost + row * nch * cap;
   if (nch == 1)
     for (int i = l; i < total; i += kFinLanes) ids[g][i] = out[i];
-  // (a row's group lies inside one wave: its LDS traffic needs no barrier, but the
-  // compiler has to keep the order)
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __syncthreads();  // the obstacles' spheres; from here on a row's LDS traffic stays inside its wave
   const int64_t v = n_old + row0 + row;
   double xv[D];
 #pragma unroll
@@ -265,7 +277,7 @@ __global__ void __launch_bounds__(kThreads) k_search_finish(int64_t n_old, int64
       ok = d2 <= r2 && d2 > 0.0;
       if (ok) {
         w = __double2float_rn(__dsqrt_rn(d2));
-        ok = !segment_blocked<D>(xu, xv, ob);
+        ok = !spheres.segment_blocked(xu, xv, d2, ob);
       }
     }
     const uint32_t bits = (uint32_t)(__ballot(ok) >> (threadIdx.x & 32));
@@ -277,10 +289,14 @@ __global__ void __launch_bounds__(kThreads) k_search_finish(int64_t n_old, int64
     kept += __popc(bits);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   }
+  if (l < kRankStep) ids[g][kept + l] = INT32_MAX;
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   for (int i = l; i < kept; i += kFinLanes) {
     const int32_t u = ids[g][i];
     int rank = 0;
-    for (int j = 0; j < kept; ++j) rank += ids[g][j] < u;
+    for (int j = 0; j < kept; j += kRankStep)
+#pragma unroll
+      for (int e = 0; e < kRankStep; ++e) rank += ids[g][j + e] < u;
     out[rank] = u;
     outc[rank] = cst[g][i];
   }
@@ -346,14 +362,16 @@ __global__ void __launch_bounds__(kThreads) k_search_rows(int32_t rows, int32_t 
   if (base + total > capacity) return;
   if (threadIdx.x < last - first) rp[first + threadIdx.x] = base + start[threadIdx.x];
   if (last == rows && threadIdx.x == 0) rp[rows] = base + total;
-  const int lane = threadIdx.x & (kWave - 1);
-  for (int i = threadIdx.x / kWave; i < last - first; i += kThreads / kWave) {
-    const int64_t from = (int64_t)(first + i) * stride, to = base + start[i];
-    const int k = (int)(start[i + 1] - start[i]);
-    for (int j = lane; j < k; j += kWave) {
-      if (col) col[to + j] = cand[from + j];
-      if (cost) cost[to + j] = ccost[from + j];
-    }
+  // a group of lanes per row: every row of the workgroup at once
+  constexpr int kLanes = kThreads / kCsrRows;
+  const int i = threadIdx.x / kLanes;
+  if (i >= last - first) return;
+  const int64_t from = (int64_t)(first + i) * stride, to = base + start[i];
+  const int k = (int)(start[i + 1] - start[i]);
+#pragma unroll 4
+  for (int j = threadIdx.x % kLanes; j < k; j += kLanes) {
+    if (col) col[to + j] = cand[from + j];
+    if (cost) cost[to + j] = ccost[from + j];
   }
 }
 
@@ -395,10 +413,10 @@ void launch_search(const SearchArgs& a, hipStream_t s) {
   // four blocks of rows per wave share each point's load; with few rows one block per
   // wave gives the chip more waves
   if (a.rows >= kSearchWideRows)
-    hipLaunchKernelGGL(k_search<4>, dim3(blocks_for(a.rows, 512), (unsigned)a.nch), dim3(kThreads), 0, s, a.n_old, a.n,
+    hipLaunchKernelGGL((k_search<4, 1>), dim3(blocks_for(a.rows, 512), (unsigned)a.nch), dim3(kThreads), 0, s, a.n_old, a.n,
                        a.row0, a.rows, a.rec, ht, a.nch, a.chunk, a.cap, a.cand, a.cnt, a.state);
   else
-    hipLaunchKernelGGL(k_search<1>, dim3(blocks_for(a.rows, 128), (unsigned)a.nch), dim3(kThreads), 0, s, a.n_old, a.n,
+    hipLaunchKernelGGL((k_search<1, 4>), dim3(blocks_for(a.rows, 128), (unsigned)a.nch), dim3(kThreads), 0, s, a.n_old, a.n,
                        a.row0, a.rows, a.rec, ht, a.nch, a.chunk, a.cap, a.cand, a.cnt, a.state);
 #define FINISH(D)                                                                                                   \
   hipLaunchKernelGGL(k_search_finish<D>, dim3(blocks_for(a.rows, kFinRows)), dim3(kThreads), 0, s, a.n_old, a.row0, \

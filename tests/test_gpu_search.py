@@ -151,3 +151,22 @@ def test_device_rows_capacity(P):
     assert args(m, col.data_ptr(), None) == 0
     assert np.array_equal(rp.cpu().numpy(), orp) and np.array_equal(col.cpu().numpy()[:m], ocol)
     assert (col[m:] == -7).all()
+
+
+@pytest.mark.parametrize("d,count", [(2, 64), (3, 65), (2, 129), (5, 200)])
+def test_many_obstacles(P, d, count):
+    """More obstacles than one mask, and than the bounding spheres kept in LDS, holds;
+    some far outside the cube, some huge: sampling and rows as the oracle has them."""
+    obs = W.make_obstacles(d, count, "mixed", count)
+    obs.size[:] *= 0.3
+    obs.centre[-3:] += 7.0
+    obs.size[-1] += 6.5
+    obs.centre[1] = 60.0
+    n = 500
+    G = P.Rrg(d, obs, stream=stream())
+    G.add_points(np.stack([np.full(d, 0.05), np.full(d, 0.95)]))
+    c = G.sample(seed=4, stream=1, counter=0, count=n)
+    want, wc = R.sample(d, 4, 1, 0, n, obs)
+    pts = G.points()
+    assert c == wc and np.array_equal(pts[2:], want)
+    check(P, pts, 100, W.radius(n, d), obs, G)
