@@ -203,13 +203,23 @@ struct pirrt_graph {
   bool truncated = false;  // truncated Evaluate for the current call (PIRRT_TRUNCATED)
   LoopKey prev_key;          // loop arguments of the previous Replan (graphs when they repeat)
   bool have_prev_key = false;
-  bool small_graphs = true;  // single-workgroup Replan up to kSmallMax vertices (PIRRT_SMALL=0: off)
+  ResidentSync* rsync = nullptr;  // the one-launch Replan's gate and barrier words, then its lists
+  // One-launch Replan up to kResidentMax vertices (PIRRT_SMALL=0: off; off too where the
+  // environment fixes a configuration of the multi-kernel loop)
+  bool resident = true;
+  // The stored policy is known to be a forest: insertions and Replans keep it one, a
+  // policy given by the caller may hold cycles, and the truncated mode's stale g could
+  // close one.
+  bool tree = true;
+  bool snap_tree = true;
   // Host-side fault hook (PIRRT_FAULT_INJECT at create): "launch" makes the next
   // Replan fail as if a kernel launch had returned a HIP error (no device work is
   // involved; the handle is poisoned like after a real one), "alloc" makes the next
-  // growth of the vertex storage fail as if the device allocation had.
+  // growth of the vertex storage fail as if the device allocation had, "gate" makes the
+  // next one-launch Replan find its gate closed (the multi-kernel loop takes over).
   bool fault_launch = false;
   bool fault_alloc = false;
+  bool fault_gate = false;
   bool poisoned = false;
   std::string err;
 };
@@ -509,7 +519,7 @@ void release_all(pirrt_graph* G) {
   dfree(G->A, G->brp); dfree(G->A, G->bcol); dfree(G->A, G->bslot); dfree(G->A, G->bcost);
   dfree(G->A, G->info); dfree(G->A, G->dflag); dfree(G->A, G->dcount); dfree(G->A, G->dhops);
   dfree(G->A, G->ps); dfree(G->A, G->ctr); dfree(G->A, G->ctl); dfree(G->A, G->pscratch); dfree(G->A, G->droots); dfree(G->A, G->dbase);
-  dfree(G->A, G->pstart); dfree(G->A, G->dgrow);
+  dfree(G->A, G->pstart); dfree(G->A, G->dgrow); dfree(G->A, G->rsync);
   if (G->hps) (void)hipHostFree(G->hps);
   G->hps = nullptr;
   raw_free(G->A, G->scan_scratch);
@@ -1093,6 +1103,26 @@ struct PolicyOut {
   int mem_kind;
 };
 
+// Statistics and return code of a Replan done in one launch, from its final state.
+int finish_single(pirrt_graph* G, const ProblemState& q, std::chrono::steady_clock::time_point t_start,
+                  pirrt_stats* stats) {
+  if (stats) {
+    pirrt_stats& st = stats[0];
+    memset(&st, 0, sizeof(st));
+    st.iterations = q.iterations;
+    st.edges_examined = (int64_t)q.edges;
+    st.sum_P = (int64_t)q.sum_P;
+    st.sum_D = (int64_t)q.sum_D;
+    st.changed_total = (int64_t)q.changed_total;
+    st.mark_edges = (int64_t)q.mark_edges;
+    st.evaluate_calls = q.iterations;
+    st.ms_total = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_start).count();
+  }
+  G->last_iterations = q.iterations;
+  if (q.status != 0) return fail(G, PIRRT_ENOTCONVERGED, "iteration cap reached");
+  return PIRRT_OK;
+}
+
 // Runs Replan for P problems with the given root ids and root / goal slots.  h is
 // a device array in slot order (or NULL).  Fills per-problem stats (P entries,
 // nullable).  out (nullable): the policy copy-out is enqueued before the final wait,
@@ -1118,7 +1148,8 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
   if (P == 1 && !G->batched) {
     // one launch from scalar arguments: no host-to-device copies on the latency path
     launch_replan_init_single(G->ps, root_slots[0], goal_slots[0], G->hps[0].cap, root_ids[0], G->nroots, G->droots,
-                              G->slot_of, G->parent, G->pcost, G->ctr, G->ctl, G->g, prune ? 1 : 0, s);
+                              G->slot_of, G->parent, G->pcost, G->ctr, G->ctl, G->g, prune ? 1 : 0, G->rsync, G->fault_gate ? 2u : 0u, s);
+    G->fault_gate = false;
   } else {
     HIP_OR_FAIL(G, hipMemcpyAsync(G->ps, G->hps, sizeof(ProblemState) * (size_t)P, hipMemcpyHostToDevice, s));
     // the previous roots lose their mark; the new roots get it
@@ -1199,32 +1230,33 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
   int64_t lb = (int64_t)n / 2048;
   ea.level_blocks = (int32_t)(lb < 16 ? 16 : (lb > 1024 ? 1024 : lb));
   if (G->eval_levels && P != 1) return fail(G, PIRRT_EINVAL, "the level-synchronous Evaluate takes one problem");
-  if (P == 1 && !G->batched && n <= kSmallMax && G->small_graphs && !timing && !G->trace && !G->eval_levels &&
-      !G->truncated) {
-    // one workgroup runs the whole loop
-    launch_replan_small(n, G->rp, G->col, G->cst, h, G->ext_of, prune, G->lookahead, G->ps, G->parent, G->pcost,
-                        G->g, s);
-    HIP_OR_FAIL(G, hipGetLastError());
+  if (P == 1 && !G->batched && G->resident && n <= kResidentMax && G->nnz <= kResidentEdges && !timing && !G->trace &&
+      !G->eval_levels && !G->truncated) {
+    ResidentArgs ra;
+    ra.n = n;
+    ra.rp = G->rp;
+    ra.col = G->col;
+    ra.cst = G->cst;
+    ra.h = h;
+    ra.ext_of = G->ext_of;
+    ra.ps = G->ps;
+    ra.parent = G->parent;
+    ra.pcost = G->pcost;
+    ra.g = G->g;
+    ra.sync = G->rsync;
+    ra.lists = reinterpret_cast<unsigned long long*>(G->rsync + 1);
+    ra.prune = prune ? 1 : 0;
+    ra.lookahead = G->lookahead;
+    ra.tree = G->tree;
+    HIP_OR_FAIL(G, launch_replan_resident(ra, s));
     if (out && (out->g || out->parent) && (rc = policy_out(G, out->g, out->parent, nullptr, out->mem_kind)))
       return rc;
     HIP_OR_FAIL(G, hipMemcpyAsync(G->hps, G->ps, sizeof(ProblemState), hipMemcpyDeviceToHost, s));
     HIP_OR_FAIL(G, hipStreamSynchronize(s));
     const ProblemState& q = G->hps[0];
-    if (stats) {
-      pirrt_stats& st = stats[0];
-      memset(&st, 0, sizeof(st));
-      st.iterations = q.iterations;
-      st.edges_examined = (int64_t)q.edges;
-      st.sum_P = (int64_t)q.sum_P;
-      st.sum_D = (int64_t)q.sum_D;
-      st.changed_total = (int64_t)q.changed_total;
-      st.mark_edges = (int64_t)q.mark_edges;
-      st.evaluate_calls = q.iterations;
-      st.ms_total = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_start).count();
-    }
-    G->last_iterations = q.iterations;
-    if (q.status != 0) return fail(G, PIRRT_ENOTCONVERGED, "iteration cap reached");
-    return PIRRT_OK;
+    if (q.status == 2) return fail_device(G, hipErrorUnknown, "the resident Replan's barrier did not complete");
+    if (!q.active) return finish_single(G, q, t_start, stats);
+    // its workgroups did not all become resident and left: the loop does the Replan
   }
 
   // the multi-kernel loop's marks: no stamp older than this Replan
@@ -1246,6 +1278,7 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
     agg.evaluate_calls += 1;
   }
 
+  if (G->truncated) G->tree = false;  // stale g could close a cycle
   const bool direct = timing || G->trace || !G->use_graph;
   int64_t done_iters = 0;
   if (direct) {
@@ -1524,6 +1557,13 @@ int tune(pirrt_graph* G, int32_t P, const int32_t* rid, const int32_t* rs, const
     HIP_OR_FAIL(G, hipStreamSynchronize(s));
     return PIRRT_OK;
   };
+  // the configurations are those of the multi-kernel loop
+  struct LoopOnly {
+    pirrt_graph* G;
+    bool was;
+    ~LoopOnly() { G->resident = was; }
+  } loop_only{G, G->resident};
+  G->resident = false;
   double best = 1e300;
   int bestc = 0;
   auto apply = [&](int c) {
@@ -1617,7 +1657,7 @@ pirrt_graph* new_graph(const pirrt_config* cfg, int* rc_out) {
     G->cus = 256;
   }
   bool ok = dalloc(G->A, &G->info, 1) && dalloc(G->A, &G->dflag, 1) && dalloc(G->A, &G->dcount, 3) && dalloc(G->A, &G->dhops, 1) &&
-            dalloc(G->A, &G->ctl, 1);
+            dalloc(G->A, &G->ctl, 1) && dalloc(G->A, &G->rsync, 1 + (kResidentLists * 8 + sizeof(ResidentSync) - 1) / sizeof(ResidentSync));
   if (ok && hipHostMalloc((void**)&G->host, sizeof(HostBlock), hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     G->host = nullptr;
@@ -1677,11 +1717,13 @@ pirrt_graph* new_graph(const pirrt_config* cfg, int* rc_out) {
   const char* gr = getenv("PIRRT_GRAPH");
   if (gr) G->use_graph = atoi(gr) != 0;
   const char* sm = getenv("PIRRT_SMALL");
-  if (sm) G->small_graphs = atoi(sm) != 0;
+  if (sm) G->resident = atoi(sm) != 0;
+  if (getenv("PIRRT_ROW_VARIANT") || wc || wp || gr) G->resident = false;
   const char* fi = getenv("PIRRT_FAULT_INJECT");
   if (fi) {
     G->fault_launch = strcmp(fi, "launch") == 0;
     G->fault_alloc = strcmp(fi, "alloc") == 0;
+    G->fault_gate = strcmp(fi, "gate") == 0;
   }
   const char* wr = getenv("PIRRT_WALK_ORDER");
   if (wr) G->walk_rank = strcmp(wr, "tiles") != 0;
@@ -1859,6 +1901,7 @@ int pirrt_set_policy(pirrt_graph* G, const float* g_in, const int32_t* parent_in
   HIP_OR_FAIL(G, hipStreamSynchronize(s));
   G->nroots = 0;  // the new policy carries no root marks
   G->hroots.clear();
+  G->tree = false;  // and may hold cycles
   return PIRRT_OK;
 }
 
@@ -1894,6 +1937,7 @@ int pirrt_snapshot_save(pirrt_graph* G) {
   HIP_OR_FAIL(G, hipStreamSynchronize(s));
   G->snap_n = n;
   G->snap_roots = G->hroots;
+  G->snap_tree = G->tree;
   return PIRRT_OK;
 }
 
@@ -1917,6 +1961,7 @@ int pirrt_snapshot_restore(pirrt_graph* G) {
   HIP_OR_FAIL(G, hipStreamSynchronize(s));
   G->nroots = m;
   G->hroots = G->snap_roots;
+  G->tree = G->snap_tree;
   return PIRRT_OK;
 }
 

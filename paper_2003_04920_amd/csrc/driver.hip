@@ -54,8 +54,13 @@ __global__ void __launch_bounds__(kCounterSlots) k_replan_init_single(
     ProblemState* __restrict__ ps, int32_t root, int32_t goal, int32_t cap, int32_t root_id, int32_t nold,
     int32_t* __restrict__ droots, const int32_t* __restrict__ slot_of, int32_t* __restrict__ parent,
     float* __restrict__ pcost, IterCounters* __restrict__ ctr, LoopCtl* __restrict__ ctl, const float* __restrict__ g,
-    int prune) {
+    int prune, ResidentSync* __restrict__ sync, uint32_t gate) {
   const int t = threadIdx.x;
+  if (t < 4) sync->word[t][0] = 0ull;
+  if (t == 0) {
+    sync->arrived = 0u;
+    sync->gate = gate;
+  }
   IterCounters& c = ctr[t];
   c.changed = 0;
   c.nP = 0;
@@ -313,9 +318,10 @@ void launch_replan_init(int32_t P, ProblemState* ps, int32_t* parent, float* pco
 
 void launch_replan_init_single(ProblemState* ps, int32_t root, int32_t goal, int32_t cap, int32_t root_id,
                                int32_t nold, int32_t* droots, const int32_t* slot_of, int32_t* parent, float* pcost,
-                               IterCounters* ctr, LoopCtl* ctl, const float* g, int prune, hipStream_t s) {
+                               IterCounters* ctr, LoopCtl* ctl, const float* g, int prune, ResidentSync* sync,
+                               uint32_t gate, hipStream_t s) {
   hipLaunchKernelGGL(k_replan_init_single, dim3(1), dim3(kCounterSlots), 0, s, ps, root, goal, cap, root_id, nold,
-                     droots, slot_of, parent, pcost, ctr, ctl, g, prune);
+                     droots, slot_of, parent, pcost, ctr, ctl, g, prune, sync, gate);
 }
 
 void launch_finish(int32_t P, ProblemState* ps, IterCounters* ctr, LoopCtl* ctl, bool single, hipStream_t s) {

@@ -199,6 +199,8 @@ struct HostReplanStats {
 // 0 at the fixed point, 1 at the iteration cap (the state is consistent either way).
 int host_replan(const HostReplan& p, HostReplanStats* st);
 
+struct ResidentSync;
+
 // ---- driver.hip ----
 // Also sets each problem's threshold to g(goal) as stored (+inf without pruning): the
 // threshold the truncated Evaluate reads in the first walk.
@@ -206,10 +208,12 @@ void launch_replan_init(int32_t P, ProblemState* ps, int32_t* parent, float* pco
                         LoopCtl* ctl, const float* g, int prune, hipStream_t s);
 // A single graph's set-up from scalar arguments (no host copies): unmarks the nold
 // previous roots listed in droots (caller ids), marks root (a slot), writes root_id to
-// droots[0] and initialises ps[0] with goal (a slot) and cap.
+// droots[0] and initialises ps[0] with goal (a slot) and cap, and the one-launch Replan's
+// barrier words and gate (2: closed from the start).
 void launch_replan_init_single(ProblemState* ps, int32_t root, int32_t goal, int32_t cap, int32_t root_id,
                                int32_t nold, int32_t* droots, const int32_t* slot_of, int32_t* parent, float* pcost,
-                               IterCounters* ctr, LoopCtl* ctl, const float* g, int prune, hipStream_t s);
+                               IterCounters* ctr, LoopCtl* ctl, const float* g, int prune, ResidentSync* sync,
+                               uint32_t gate, hipStream_t s);
 // single: one graph (P == 1, no problem map); see launch_after_eval.
 void launch_finish(int32_t P, ProblemState* ps, IterCounters* ctr, LoopCtl* ctl, bool single, hipStream_t s);
 // prob / base / tiles: a batch's problem map, its problems' slot ranges (P + 1
@@ -253,15 +257,46 @@ struct StepArgs {
   int blocks;                // batches: workgroups of each grid-stride launch
 };
 constexpr int kRowVariants = 4;
-// One small graph (n <= kSmallMax vertices; the single workgroup is faster than the
-// multi-kernel loop up to about 1,700 vertices of a 2D graph) replanned by a single workgroup with its
-// vertex state in LDS: the whole loop in one launch (small.hip).  Reads the root,
-// goal and cap from ps[0] and leaves the counters and status there; parent / pcost
-// are read and written in place (the root's entries untouched), g written.
-constexpr int32_t kSmallMax = 1536;
-void launch_replan_small(int32_t n, const int64_t* rp, const int32_t* col, const float* cst, const float* h,
-                         const int32_t* ext_of, bool prune, bool lookahead, ProblemState* ps, int32_t* parent,
-                         float* pcost, float* g, hipStream_t s);
+// ---- resident.hip ----
+// One graph of at most kResidentMax vertices and kResidentEdges entries replanned in one
+// launch by workgroups that stay resident for the whole loop.  Reads the root, goal and
+// cap from ps[0] and leaves the counters and status there (active stays 1 when the
+// workgroups could not all become resident: nothing was changed); parent, pcost and g are
+// read and written in place (the root's parent and cost untouched).
+//
+// kResidentMax: what fits 16-bit slots and the LDS (10 bytes a vertex).  It is faster than
+// the multi-kernel loop at every size below (one synchronous call, 2D unless noted: 600
+// vertices 119 against 389 us, 2,002: 189 / 726, 8,000: 436 / 1,452, 15,000: 921 / 2,159;
+// 6D 15,000: 316 / 401).  kResidentEdges: entries past a row's first 64 come from memory
+// every iteration, by one workgroup per 128 rows; 4,000 vertices of 3D with 251 neighbours
+// take 184 against 376 us, with 532 (2.1M entries) 482 / 486.
+constexpr int32_t kResidentMax = 15360;
+constexpr int64_t kResidentEdges = 1 << 21;
+constexpr int kResidentGroups = 128;  // workgroups at most
+constexpr int64_t kResidentLists = 2 * (kResidentMax + 2 * kResidentGroups);
+struct ResidentSync {  // cleared by the single graph's set-up kernel
+  uint32_t arrived, gate;
+  uint32_t pad[30];
+  unsigned long long word[4][16];  // a 128-byte line each
+};
+struct ResidentArgs {
+  int32_t n, rows;  // vertices; rows owned by a workgroup (set by the launch)
+  const int64_t* rp;
+  const int32_t* col;
+  const float* cst;
+  const float* h;  // nullable
+  const int32_t* ext_of;
+  ProblemState* ps;
+  int32_t* parent;
+  float* pcost;
+  float* g;
+  ResidentSync* sync;
+  unsigned long long* lists;  // kResidentLists words of scratch
+  int prune;
+  bool lookahead;
+  bool tree;  // the stored policy has no cycle: Evaluate may start from the stored g
+};
+hipError_t launch_replan_resident(ResidentArgs a, hipStream_t s);
 void launch_mark(const StepArgs& a, int variant, hipStream_t s);
 // Compacts the stamped slots into dlist / ctl->ndomain (and clears every stamp when
 // the next mark epoch wraps its low byte).
