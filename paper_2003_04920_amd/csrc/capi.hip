@@ -63,7 +63,7 @@ struct LoopKey {
   const void* ptrs[17];
   int64_t n, nnz;
   int32_t P, prune, variant, walk_parts, walk_coherent, eval_levels, has_h, iters, mid, lookahead, truncated, blocks;
-  int32_t bitmap_tiles, walk_rank;
+  int32_t bitmap_tiles, walk_rank, pull;
   bool operator==(const LoopKey& o) const { return memcmp(this, &o, sizeof(LoopKey)) == 0; }
 };
 
@@ -199,6 +199,7 @@ struct pirrt_graph {
   int cus = 256;                     // compute units of the device
   int32_t bitmap_tiles = INT32_MAX;  // batches: tile lists from the bitmap up to this many tiles
   bool walk_rank = true;  // batches: the walk takes the active tiles by their rank inside their problem
+  int pull = -1;  // Improve's pull form: 0 never, 1 always, -1 by the rule (PIRRT_PULL)
   bool lookahead = false;  // narrowed Improve domain for the current call (PIRRT_LOOKAHEAD)
   bool truncated = false;  // truncated Evaluate for the current call (PIRRT_TRUNCATED)
   LoopKey prev_key;          // loop arguments of the previous Replan (graphs when they repeat)
@@ -1026,8 +1027,12 @@ void enqueue_evaluate(pirrt_graph* G, LoopArgs& L, hipStream_t s, bool after_imp
 // (The thresholds of an iteration come from the after-eval step before it.)
 void enqueue_iteration(pirrt_graph* G, LoopArgs& L, hipStream_t s, bool timing) {
   if (timing) (void)hipEventRecord(G->ev[2], s);
-  launch_mark(L.sa, G->row_variant, s);
-  launch_domain_list(L.sa, s);
+  if (L.sa.pull) {
+    launch_promising_signs(L.sa, s);
+  } else {
+    launch_mark(L.sa, G->row_variant, s);
+    launch_domain_list(L.sa, s);
+  }
   if (timing) (void)hipEventRecord(G->ev[3], s);
   launch_improve(L.sa, G->row_variant, s);
   if (timing) (void)hipEventRecord(G->ev[4], s);
@@ -1065,6 +1070,7 @@ LoopKey loop_key(pirrt_graph* G, const LoopArgs& L, int iters) {
   k.blocks = L.sa.blocks;
   k.bitmap_tiles = G->bitmap_tiles;
   k.walk_rank = G->walk_rank;
+  k.pull = L.sa.pull;
   return k;
 }
 
@@ -1102,6 +1108,23 @@ struct PolicyOut {
   int32_t* parent;
   int mem_kind;
 };
+
+// Whether a single graph's Improve takes every row and finds the domain by itself (pull:
+// two streams of n and one of the whole adjacency an iteration) or the domain is marked
+// and listed first (three launches more, but only the domain's rows, and the promising
+// ones twice).  Without pruning the domain is every reachable row.  With pruning about
+// half the rows are in it, and up to some hundred thousand vertices the launches cost more
+// than the other half.  Measured, marks against pull: 6D with pruning 60,000 vertices 510
+// against 386 us, 100,002: 623 / 527, 200,000: 799 / 745, 400,000: 1,196 / 1,278, 1M:
+// 2,695 / 3,245; 2D 200,000: 15,959 / 14,923; without pruning 6D 200,000: 1,142 / 823, 1M:
+// 5,073 / 3,266.
+constexpr int32_t kPullMax = 1 << 18;
+constexpr int64_t kPullEdges = (int64_t)12 << 20;
+
+bool pulls(const pirrt_graph* G, bool prune) {
+  if (G->batched || G->truncated || G->pull == 0) return false;
+  return G->pull == 1 || !prune || (G->n <= kPullMax && G->nnz <= kPullEdges);
+}
 
 // Statistics and return code of a Replan done in one launch, from its final state.
 int finish_single(pirrt_graph* G, const ProblemState& q, std::chrono::steady_clock::time_point t_start,
@@ -1192,6 +1215,8 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
   sa.truncated = G->truncated;
   sa.word = G->word;
   sa.blocks = G->batch_blocks;
+  sa.gs = reinterpret_cast<float*>(G->fr1);  // (in the place of the promising list)
+  sa.pull = pulls(G, prune);
   WalkArgs& wa = L.wa;
   wa.n = n;
   wa.prob = problem_map(G);
@@ -1719,6 +1744,8 @@ pirrt_graph* new_graph(const pirrt_config* cfg, int* rc_out) {
   const char* sm = getenv("PIRRT_SMALL");
   if (sm) G->resident = atoi(sm) != 0;
   if (getenv("PIRRT_ROW_VARIANT") || wc || wp || gr) G->resident = false;
+  const char* pl = getenv("PIRRT_PULL");
+  if (pl) G->pull = atoi(pl) != 0;
   const char* fi = getenv("PIRRT_FAULT_INJECT");
   if (fi) {
     G->fault_launch = strcmp(fi, "launch") == 0;

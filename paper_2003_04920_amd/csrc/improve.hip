@@ -15,6 +15,13 @@
 // kBatched: several problems share the arrays; prob[slot] names the problem of a
 // slot.  Without it every slot belongs to problem 0.
 //
+// kPull (single graphs): Improve takes every slot instead of the compacted domain, and
+// each row finds out by itself whether its vertex is in the domain: `g` holds the signs of
+// the promising set (k_promising_signs), so the gather that brings a neighbour's g also
+// tells whether it is promising.  No marks and no domain list: three launches an iteration
+// instead of five.  kLook: the narrowed domain (a promising neighbour counts only if its
+// offer passes).
+//
 // kTrunc (truncated Evaluate, single graphs): g(v) may be stale, and the minimum may
 // be v's own parent and cost below it; that leaves the policy as it is and is not
 // counted as a switch.
@@ -40,7 +47,7 @@ using rows::batch_grid;
 //
 // Improve runs over the compacted domain: group i takes entry i of dlist; workgroups
 // past the domain's end leave at once.
-template <int GW, int Q, typename Idx, bool kBatched, bool kTrunc>
+template <int GW, int Q, typename Idx, bool kBatched, bool kTrunc, bool kPull = false, bool kLook = false>
 __global__ void __launch_bounds__(kThreads) k_improve(int32_t n, const int32_t* __restrict__ prob,
                                                      const ProblemState* __restrict__ ps,
                                                      const LoopCtl* __restrict__ ctl, const float* __restrict__ g,
@@ -48,9 +55,11 @@ __global__ void __launch_bounds__(kThreads) k_improve(int32_t n, const int32_t* 
                                                      const float* __restrict__ cst, const int32_t* __restrict__ dlist,
                                                      const int32_t* __restrict__ ext_of,
                                                      int32_t* __restrict__ parent, float* __restrict__ pcost,
-                                                     IterCounters* __restrict__ ctr) {
+                                                     IterCounters* __restrict__ ctr,
+                                                     const float* __restrict__ h = nullptr) {
+  static_assert(!(kPull && (kBatched || kTrunc)) && (kPull || !kLook), "pull: single graphs");
   if (ctl->any_active == 0) return;  // every problem has converged
-  const int64_t cnt = ctl->ndomain;
+  const int64_t cnt = kPull ? n : ctl->ndomain;
   // a batch strides over the domain with a fixed grid; a single graph's grid covers it
   const int64_t step = kBatched ? (int64_t)gridDim.x * (kThreads / GW) : cnt;
   for (int64_t first = (int64_t)blockIdx.x * (kThreads / GW); first < cnt; first += step) {
@@ -58,12 +67,15 @@ __global__ void __launch_bounds__(kThreads) k_improve(int32_t n, const int32_t* 
   const int grp = lane / GW, gl = threadIdx.x % GW;
   const int64_t gi = first + threadIdx.x / GW;
   const bool valid = gi < cnt;
-  const int32_t x = dlist[valid ? gi : cnt - 1];
+  const int32_t x = kPull ? (int32_t)(valid ? gi : cnt - 1) : dlist[valid ? gi : cnt - 1];
   const int p = kBatched ? prob[x] : 0;
-  const float gx = g[x];
+  const float gs = g[x], gx = kPull ? fabsf(gs) : gs;
   const Idx ra = (Idx)rp[x], rb = (Idx)rp[x + 1];
-  const bool in = valid && x != ps[p].root;
+  bool in = valid && x != ps[p].root;
   const Idx a = in ? ra : 0, b = in ? rb : 0;
+  const float hx = kLook && h ? h[x] : 0.0f, G = kLook ? ps[p].thr : 0.0f;
+  const bool px = kPull && valid && (__float_as_uint(gs) >> 31) != 0u;
+  bool near = false;  // a neighbour puts x into the domain
   const int4* col4 = reinterpret_cast<const int4*>(col);
   const float4* cst4 = reinterpret_cast<const float4*>(cst);
   // lane-local minimum of (g(u) + c, caller id of u, c); bu = slot of u
@@ -101,7 +113,9 @@ __global__ void __launch_bounds__(kThreads) k_improve(int32_t n, const int32_t* 
 #pragma unroll
     for (int i = 0; i < 4 * Q; ++i) {
       if (!ok[i]) continue;
-      const uint32_t vb = __float_as_uint(add_rn(gu[i], c[i])), cb = __float_as_uint(c[i]);
+      const float offer = add_rn(kPull ? fabsf(gu[i]) : gu[i], c[i]);
+      if (kPull) near = near || ((__float_as_uint(gu[i]) >> 31) != 0u && (!kLook || add_rn(offer, hx) < G));
+      const uint32_t vb = __float_as_uint(offer), cb = __float_as_uint(c[i]);
       if (vb >= 0x7f800000u) continue;  // +inf never improves anything
       if (vb < bv) {
         bv = vb;
@@ -116,6 +130,7 @@ __global__ void __launch_bounds__(kThreads) k_improve(int32_t n, const int32_t* 
       }
     }
   }
+  if (kPull) in = in && (px || group_bits<GW>(__ballot(near), grp) != 0ull);
   // group minimum: value first; the caller id is fetched only for real ties
   const uint32_t mv = dpp_group_min_u32<GW>(bv);
   const bool tied = bu >= 0 && bv == mv;
@@ -139,7 +154,40 @@ __global__ void __launch_bounds__(kThreads) k_improve(int32_t n, const int32_t* 
     rows::flush_counters_wave<false, true, true, true, false>(ctr, p, valid && gl == 0, 0, in ? 1 : 0,
                                                               in ? (unsigned long long)(b - a) : 0ull, changed);
   else
-    flush_counters(ctr, p, valid && gl == 0, 0, in ? 1 : 0, in ? (unsigned long long)(b - a) : 0ull, changed);
+    flush_counters(ctr, p, valid && gl == 0, px ? 1 : 0, in ? 1 : 0, in ? (unsigned long long)(b - a) : 0ull, changed,
+                   px ? (int)(rb - ra) : 0);
+  }
+}
+
+// The promising set as signs, for Improve's pull form: gs(v) = -g(v) where fl(g + h) < G,
+// else g(v).  Also the thresholds step of a single graph (see k_promising_list).
+__global__ void __launch_bounds__(kThreads) k_promising_signs(int32_t n, ProblemState* __restrict__ ps,
+                                                             LoopCtl* __restrict__ ctl, const float* __restrict__ g,
+                                                             const float* __restrict__ h, float* __restrict__ gs,
+                                                             int prune) {
+  const bool active = ps[0].active != 0;
+  const float G = active ? (prune ? g[ps[0].goal] : pos_inf()) : -pos_inf();
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    ps[0].thr = G;
+    ctl->any_active = active ? 1 : 0;
+    ctl->any_eval = 0;
+    ctl->ndomain = 0;
+    ctl->ntiles = -1;
+    ctl->eval_epoch = next_epoch(ctl->eval_epoch);
+    ps[0].changed_seen = ps[0].changed_total;  // the walk after this Improve compares against it
+  }
+  if (!active) return;  // the problem has converged
+  const int64_t v0 = ((int64_t)blockIdx.x * kThreads + threadIdx.x) * 4;
+  if (v0 + 4 <= n) {
+    float4 x = *reinterpret_cast<const float4*>(g + v0);
+    const float4 y = h ? *reinterpret_cast<const float4*>(h + v0) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (add_rn(x.x, y.x) < G) x.x = -x.x;
+    if (add_rn(x.y, y.y) < G) x.y = -x.y;
+    if (add_rn(x.z, y.z) < G) x.z = -x.z;
+    if (add_rn(x.w, y.w) < G) x.w = -x.w;
+    *reinterpret_cast<float4*>(gs + v0) = x;
+  } else {
+    for (int64_t v = v0; v < n; ++v) gs[v] = add_rn(g[v], h ? h[v] : 0.0f) < G ? -g[v] : g[v];
   }
 }
 
@@ -154,8 +202,24 @@ void launch_improve_t(const StepArgs& a, hipStream_t s) {
                        a.rp, a.col, a.cst, a.dlist, a.ext_of, a.parent, a.pcost, a.ctr);
 }
 
+template <int GW, int U, bool L>
+void launch_improve_pull(const StepArgs& a, hipStream_t s) {
+  if (a.nnz < ((int64_t)1 << 32) - 64 * GW)
+    hipLaunchKernelGGL((k_improve<GW, U, uint32_t, false, false, true, L>), grid_for(a.n, GW), dim3(kThreads), 0, s,
+                       a.n, a.prob, a.ps, a.ctl, a.gs, a.rp, a.col, a.cst, a.dlist, a.ext_of, a.parent, a.pcost, a.ctr,
+                       a.h);
+  else
+    hipLaunchKernelGGL((k_improve<GW, U, int64_t, false, false, true, L>), grid_for(a.n, GW), dim3(kThreads), 0, s,
+                       a.n, a.prob, a.ps, a.ctl, a.gs, a.rp, a.col, a.cst, a.dlist, a.ext_of, a.parent, a.pcost, a.ctr,
+                       a.h);
+}
+
 template <int GW, int U>
 void launch_improve_b(const StepArgs& a, hipStream_t s) {
+  if (a.pull) {
+    if (a.lookahead) launch_improve_pull<GW, U, true>(a, s); else launch_improve_pull<GW, U, false>(a, s);
+    return;
+  }
   if (a.prob)
     launch_improve_t<GW, U, true, false>(a, s);
   else if (a.truncated)
@@ -165,6 +229,12 @@ void launch_improve_b(const StepArgs& a, hipStream_t s) {
 }
 
 }  // namespace
+
+void launch_promising_signs(const StepArgs& a, hipStream_t s) {
+  const int64_t per_block = (int64_t)kThreads * 4;
+  hipLaunchKernelGGL(k_promising_signs, dim3((unsigned)((a.n + per_block - 1) / per_block)), dim3(kThreads), 0, s, a.n,
+                     a.ps, a.ctl, a.g, a.h, a.gs, a.prune);
+}
 
 void launch_improve(const StepArgs& a, int variant, hipStream_t s) {
   switch (variant) {

@@ -255,7 +255,10 @@ struct StepArgs {
   bool truncated;
   const unsigned long long* word;  // the walk stamps
   int blocks;                // batches: workgroups of each grid-stride launch
+  bool pull;                 // single graphs: Improve over every slot, from the signed g
+  float* gs;                 // pull: g with the promising set as signs (n entries of room)
 };
+void launch_promising_signs(const StepArgs& a, hipStream_t s);
 constexpr int kRowVariants = 4;
 // ---- resident.hip ----
 // One graph of at most kResidentMax vertices and kResidentEdges entries replanned in one
