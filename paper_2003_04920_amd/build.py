@@ -12,7 +12,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libpirrt.so")
 BUILD_DIR = os.path.join(PKG, "_build")
-SOURCES = ["scan.hip", "store.hip", "reorder.hip", "evaluate.hip", "mark.hip", "improve.hip", "resident.hip", "driver.hip", "capi.hip", "rrg.hip", "search.hip", "mlp.hip",
+SOURCES = ["scan.hip", "store.hip", "insert.hip", "reorder.hip", "evaluate.hip", "mark.hip", "improve.hip", "resident.hip", "driver.hip", "capi.hip", "rrg.hip", "search.hip", "mlp.hip",
            "host_replan.hip"]
 ARCH = os.environ.get("PIRRT_OFFLOAD_ARCH", "gfx950")
 

@@ -141,6 +141,11 @@ struct pirrt_graph {
   int64_t reorder_min = 131072;
   bool clustered_order = true;    // seed clusters on top of the breadth-first order
   bool renumber_pending = false;  // batch problems added since the last renumbering
+  // A single graph the one-launch Replan takes is not renumbered when inserts make it due
+  // (that Replan gathers from LDS, where the order does not matter: 2D 2,002 vertices 192 us
+  // renumbered, 185 in insertion order; the renumbering takes 1 to 7 ms): later, when a
+  // snapshot is taken, the multi-kernel loop runs on it or it outgrows that size.
+  bool renumber_due = false;
   // problems: problem i holds caller ids [pbase[i], pbase[i+1]) and the same slots
   bool batched = false;
   std::vector<int64_t> pbase{0, 0};
@@ -583,6 +588,12 @@ int policy_out(pirrt_graph* G, float* g_out, int32_t* parent_out, float* pcost_o
   return PIRRT_OK;
 }
 
+// Whether a graph of this size and handle replans in one launch (resident.hip).
+bool resident_size(const pirrt_graph* G) {
+  return !G->batched && G->resident && !G->eval_levels && !G->trace && G->n <= kResidentMax &&
+         G->nnz <= kResidentEdges;
+}
+
 // Renumbers the storage slots in breadth-first order of the graph, each problem
 // inside its own slot range from its x_init (its first vertex); vertices the BFS
 // cannot reach follow in their current order.
@@ -694,7 +705,7 @@ int renumber(pirrt_graph* G) {
   HIP_OR_FAIL(G, hipMemcpyAsync(G->hslot.data(), G->slot_of, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToHost, s));
   HIP_OR_FAIL(G, hipStreamSynchronize(s));
   G->reorder_n = n;
-  G->renumber_pending = false;
+  G->renumber_pending = G->renumber_due = false;
   G->adj_version++;
   G->snap_n = -1;  // a snapshot in the old order is no longer valid
   drop_loops(G);
@@ -746,8 +757,9 @@ int insert_levels(pirrt_graph* G, int32_t n_new, int64_t n_old, int32_t insert_r
 // Appends n_new vertices with forward rows.  With new_problem the block starts a
 // new problem of a batch and its rows use ids local to the block; otherwise the
 // rows use global ids and extend the last (only) problem.
+// built: the entry count of device rows that need no validation, or -1.
 int insert_rows(pirrt_graph* G, int32_t n_new, const int64_t* row_ptr, const int32_t* col, const float* cost,
-                int mem_kind, bool new_problem) {
+                int mem_kind, bool new_problem, int64_t built = -1) {
   if (mem_kind != PIRRT_MEM_HOST && mem_kind != PIRRT_MEM_DEVICE) return fail(G, PIRRT_EINVAL, "bad mem_kind");
   if (n_new < 0) return fail(G, PIRRT_EINVAL, "n_new < 0");
   if (n_new == 0 && !new_problem) return PIRRT_OK;
@@ -765,7 +777,13 @@ int insert_rows(pirrt_graph* G, int32_t n_new, const int64_t* row_ptr, const int
   const int32_t* bcol = G->bcol;
   const float* bcost = G->bcost;
   int32_t bad = 0;
-  if (direct) {
+  if (direct && built >= 0) {
+    nnz_b = built;
+    if ((rc = ensure_staging(G, n_new, nnz_b))) return rc;  // the slot translation's room
+    brp = row_ptr;
+    bcol = col;
+    bcost = cost;
+  } else if (direct) {
     HIP_OR_FAIL(G, hipMemsetAsync(G->dflag, 0, sizeof(int32_t), s));
     launch_validate_rows(n_new, n_old, 0, row_ptr, col, cost, 0, G->dflag, s, row_ptr + n_new);
     HIP_OR_FAIL(G, hipGetLastError());
@@ -816,6 +834,39 @@ int insert_rows(pirrt_graph* G, int32_t n_new, const int64_t* row_ptr, const int
   } else if ((rc = ensure_spare(G, G->nnz + 2 * nnz_b))) {
     return rc;
   }
+  const int32_t insert_root = new_problem ? (int32_t)n_old : (n_old == 0 ? 0 : -1);
+  const bool small = !G->batched && n_new <= kInsertBlockMax && n1 <= kInsertSmallMax;
+  if (small) {
+    InsertArgs ia;
+    ia.n_new = n_new;
+    ia.n_old = n_old;
+    ia.insert_root = insert_root;
+    ia.brp = brp;
+    ia.bcol = bcol;
+    ia.bcost = bcost;
+    ia.bslot = G->bslot;
+    ia.slot_of = G->slot_of;
+    ia.ext_of = G->ext_of;
+    ia.rp_old = G->rp;
+    ia.col_old = G->col;
+    ia.cst_old = G->cst;
+    ia.rp_new = G->rp2;
+    ia.col_new = G->col2;
+    ia.cst_new = G->cst2;
+    ia.add = G->add;
+    ia.add0 = G->add0;
+    ia.dcount = G->dcount;
+    ia.g = G->g;
+    ia.parent = G->parent;
+    ia.pcost = G->pcost;
+    ia.scratch = G->rsync + 1;
+    HIP_OR_FAIL(G, launch_insert_small(ia, s));
+    HIP_OR_FAIL(G, hipMemcpyAsync(G->host->count, G->dcount, 3 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    std::swap(G->rp, G->rp2);
+    std::swap(G->col, G->col2);
+    std::swap(G->cst, G->cst2);
+    std::swap(G->ecap, G->ecap2);
+  } else {
   // new vertices take the slots after the existing ones; neighbours to slots
   launch_identity_ids(n_old, n1, G->ext_of, G->slot_of, s, G->prob, new_problem ? (int32_t)G->pbase.size() - 1 : 0);
   launch_translate(nnz_b, bcol, G->slot_of, G->bslot, s);
@@ -834,6 +885,7 @@ int insert_rows(pirrt_graph* G, int32_t n_new, const int64_t* row_ptr, const int
     std::swap(G->cst, G->cst2);
     std::swap(G->ecap, G->ecap2);
   }
+  }
   G->n = n1;
   G->nnz += 2 * nnz_b;
   G->adj_version++;
@@ -844,13 +896,20 @@ int insert_rows(pirrt_graph* G, int32_t n_new, const int64_t* row_ptr, const int
   else
     G->pbase.back() = n1;
   drop_loops(G);
-  const int32_t insert_root = new_problem ? (int32_t)n_old : (n_old == 0 ? 0 : -1);
-  if ((rc = insert_levels(G, n_new, n_old, insert_root, brp, bcol, bcost))) return rc;
+  if (small) HIP_OR_FAIL(G, hipStreamSynchronize(s));
+  if (!(small && G->host->count[2] == n_new) &&
+      (rc = insert_levels(G, n_new, n_old, insert_root, brp, bcol, bcost)))
+    return rc;
   if (new_problem) {
     G->renumber_pending = true;
+  } else if (G->renumber_due && !resident_size(G)) {
+    if ((rc = renumber(G))) return rc;
   } else if (G->reorder_growth > 0.0 && (double)n1 >= G->reorder_growth * (double)G->reorder_n &&
              (n1 >= G->reorder_min || (double)n_new >= (1.0 - 1.0 / G->reorder_growth) * (double)n1)) {
-    if ((rc = renumber(G))) return rc;
+    if (resident_size(G) && G->reorder_min > 0)
+      G->renumber_due = true;
+    else if ((rc = renumber(G)))
+      return rc;
   }
   return PIRRT_OK;
 }
@@ -1255,8 +1314,7 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
   int64_t lb = (int64_t)n / 2048;
   ea.level_blocks = (int32_t)(lb < 16 ? 16 : (lb > 1024 ? 1024 : lb));
   if (G->eval_levels && P != 1) return fail(G, PIRRT_EINVAL, "the level-synchronous Evaluate takes one problem");
-  if (P == 1 && !G->batched && G->resident && n <= kResidentMax && G->nnz <= kResidentEdges && !timing && !G->trace &&
-      !G->eval_levels && !G->truncated) {
+  if (resident_size(G) && !timing && !G->truncated) {
     ResidentArgs ra;
     ra.n = n;
     ra.rp = G->rp;
@@ -1768,6 +1826,19 @@ pirrt_graph* new_graph(const pirrt_config* cfg, int* rc_out) {
 
 }  // namespace
 
+namespace pirrt {
+
+int insert_built_rows(void* graph, int32_t n_new, const int64_t* row_ptr, const int32_t* col, const float* cost,
+                      int64_t nnz) {
+  pirrt_graph* G = static_cast<pirrt_graph*>(graph);
+  int rc = guard(G);
+  if (rc) return rc;
+  if (G->batched) return fail(G, PIRRT_EINVAL, "this handle holds a batch of problems");
+  return insert_rows(G, n_new, row_ptr, col, cost, PIRRT_MEM_DEVICE, false, nnz);
+}
+
+}  // namespace pirrt
+
 extern "C" {
 
 int pirrt_config_init(pirrt_config* cfg) {
@@ -1841,6 +1912,7 @@ int pirrt_replan(pirrt_graph* G, int32_t root, int32_t goal, const float* h, uin
     if (stats) *stats = hst;
     return rc;
   }
+  if (G->renumber_due && (flags & (PIRRT_TIMING | PIRRT_TRUNCATED)) && (rc = renumber(G))) return rc;  // the loop
   const float* hdev = nullptr;
   if ((rc = stage_h(G, h, mem_kind, &hdev))) return rc;
   const int32_t rslot = G->hslot[(size_t)root], gslot = G->hslot[(size_t)goal];
@@ -1865,6 +1937,7 @@ int pirrt_tune(pirrt_graph* G, int32_t root, int32_t goal, const float* h, uint3
     return fail(G, PIRRT_EINVAL, "PIRRT_TRUNCATED and PIRRT_LOOKAHEAD cannot be combined");
   if (G->n <= 0) return fail(G, PIRRT_EINVAL, "empty graph");
   if (root < 0 || root >= G->n || goal < 0 || goal >= G->n) return fail(G, PIRRT_EINVAL, "root or goal out of range");
+  if (G->renumber_due && (rc = renumber(G))) return rc;  // the loop's configurations
   const float* hdev = nullptr;
   if ((rc = stage_h(G, h, mem_kind, &hdev))) return rc;
   const int32_t rslot = G->hslot[(size_t)root], gslot = G->hslot[(size_t)goal];
@@ -1935,7 +2008,7 @@ int pirrt_set_policy(pirrt_graph* G, const float* g_in, const int32_t* parent_in
 int pirrt_snapshot_save(pirrt_graph* G) {
   int rc = guard(G);
   if (rc) return rc;
-  if (G->batched && G->renumber_pending && (rc = renumber(G))) return rc;
+  if (((G->batched && G->renumber_pending) || G->renumber_due) && (rc = renumber(G))) return rc;
   const int64_t n = G->n;
   if (n > G->snap_cap) {
     float* a = nullptr;

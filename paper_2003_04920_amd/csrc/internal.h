@@ -5,6 +5,11 @@
 
 namespace pirrt {
 
+// Inserts rows the library built itself on the device (valid by construction, complete in
+// memory) into a single graph: pirrt_insert_batch without the validation (capi.hip).
+int insert_built_rows(void* graph, int32_t n_new, const int64_t* row_ptr, const int32_t* col, const float* cost,
+                      int64_t nnz);
+
 // ---- scan.hip ----
 size_t scan_scratch_bytes(int64_t n);
 void scan_i32_to_i64(const int32_t* in, int64_t n, int64_t* out, void* scratch, hipStream_t s);
@@ -56,6 +61,44 @@ void launch_insert_block(const int32_t* fsize0, int32_t* done, int32_t* f0, int3
                          int32_t insert_root, const int64_t* brp, const int32_t* bcol, const int32_t* bslot,
                          const float* bcost, const int64_t* rp, const int32_t* col, float* g, int32_t* parent,
                          float* pcost, int32_t* pending, hipStream_t s);
+// The whole insert of a small batch (n_new <= kInsertBlockMax) into a single graph of up
+// to kInsertSmallMax vertices afterwards (insert.hip): adjacency into the spare arrays, ids
+// and insertion-time policy.  Validated rows; add0 all zero on entry and on return; scratch
+// of kInsertScratch bytes.  dcount[2] receives n_new, or 0 when the batch has more inner
+// edges than kInsertInner: everything but the policy is then done.  (kInsertSmallMax: the
+// offsets' workgroups each sum the counts before their own, 0.5 MB at most here.)
+constexpr int32_t kInsertInner = 16384;
+constexpr int64_t kInsertSmallMax = 131072;
+struct InsertEdge {  // an edge inside the batch, from the lower to the higher vertex
+  int32_t to, from;
+  float cost;
+};
+constexpr size_t kInsertScratch = 16 * (size_t)kInsertBlockMax + sizeof(InsertEdge) * (size_t)kInsertInner;
+struct InsertArgs {
+  int32_t n_new;
+  int64_t n_old;
+  int32_t insert_root;
+  const int64_t* brp;
+  const int32_t* bcol;
+  const float* bcost;
+  int32_t* bslot;
+  int32_t* slot_of;
+  int32_t* ext_of;
+  const int64_t* rp_old;
+  const int32_t* col_old;
+  const float* cst_old;
+  int64_t* rp_new;
+  int32_t* col_new;
+  float* cst_new;
+  int32_t* add;
+  int32_t* add0;
+  int32_t* dcount;
+  float* g;
+  int32_t* parent;
+  float* pcost;
+  void* scratch;
+};
+hipError_t launch_insert_small(const InsertArgs& a, hipStream_t s);
 void launch_insert_level(int32_t max_size, const int32_t* fsize, int32_t* done, const int32_t* frontier,
                          int64_t n_old, int32_t insert_root, const int64_t* brp, const int32_t* bcol,
                          const int32_t* bslot, const float* bcost, const int64_t* rp, const int32_t* col, float* g,
@@ -277,6 +320,7 @@ constexpr int32_t kResidentMax = 15360;
 constexpr int64_t kResidentEdges = 1 << 21;
 constexpr int kResidentGroups = 128;  // workgroups at most
 constexpr int64_t kResidentLists = 2 * (kResidentMax + 2 * kResidentGroups);
+static_assert(kResidentLists * 8 >= (int64_t)kInsertScratch, "inserts use the lists' room");
 struct ResidentSync {  // cleared by the single graph's set-up kernel
   uint32_t arrived, gate;
   uint32_t pad[30];

@@ -600,8 +600,10 @@ int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direc
 // Forward rows of points [n_old, n) in R->rp / col / cost; *nnz their entries.
 // direct (nullable): device buffers of the caller; *wrote tells whether the rows went
 // there (if they fit) instead.
+// searched (nullable): whether the matrix-core search built them (points of the unit cube:
+// the rows are valid as pirrt_insert_batch asks, costs finite).
 int build_rows(pirrt_rrg* R, int64_t n_old, double radius, int64_t* nnz, const RowsOut* direct = nullptr,
-               bool* wrote = nullptr) {
+               bool* wrote = nullptr, bool* searched = nullptr) {
   const int64_t rows = R->n - n_old;
   hipStream_t s = R->stream;
   int rc;
@@ -620,6 +622,7 @@ int build_rows(pirrt_rrg* R, int64_t n_old, double radius, int64_t* nnz, const R
   bool done = false, to_caller = false;
   if ((rc = search_rows(R, n_old, radius, direct, nnz, &done, &to_caller))) return rc;
   if (wrote) *wrote = to_caller;
+  if (searched) *searched = done;
   if (done) return PIRRT_OK;
   // per-(row, chunk) counts and their scan: cnt / cptr hold rows * nch (+1) entries
   const int32_t nch = (int32_t)((R->n + kChunk - 1) / kChunk);
@@ -963,8 +966,11 @@ int pirrt_rrg_connect(pirrt_rrg* R, int64_t n_old, double radius, pirrt_graph* g
   if (!(radius > 0.0) || !std::isfinite(radius)) return rfail(R, PIRRT_EINVAL, "radius must be finite and > 0");
   if (n_old == R->n) return PIRRT_OK;
   int64_t m = 0;
-  if ((rc = build_rows(R, n_old, radius, &m))) return rc;
-  rc = pirrt_insert_batch(g, (int32_t)(R->n - n_old), R->rp, R->col, R->cost, PIRRT_MEM_DEVICE);
+  bool searched = false;
+  if ((rc = build_rows(R, n_old, radius, &m, nullptr, nullptr, &searched))) return rc;
+  const int32_t rows = (int32_t)(R->n - n_old);
+  rc = searched ? insert_built_rows(g, rows, R->rp, R->col, R->cost, m)
+                : pirrt_insert_batch(g, rows, R->rp, R->col, R->cost, PIRRT_MEM_DEVICE);
   if (rc) return rfail(R, rc, std::string("pirrt_insert_batch: ") + pirrt_last_error(g));
   return PIRRT_OK;
 }
