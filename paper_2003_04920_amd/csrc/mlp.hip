@@ -7,23 +7,30 @@
 // A2 = bf16(relu(Z2)); weights used by products are bf16 copies of the binary32
 // masters; dZ2 = bf16(dz w3^T * [Z2 > 0]); dZ1 = bf16(dZ2 W2^T * [Z1 > 0]).
 //
-// Every matrix product is one MFMA kernel: a workgroup of four waves owns a 64 x 64
-// output tile, each wave a 32 x 32 block accumulated by v_mfma_f32_32x32x16_bf16 over
-// K in steps of 16.  Operands are read through strides, so the transposed products of
-// the backward pass (A1^T dZ2, X^T dZ1, dZ2 W2^T) need no transposed copies; a
-// contiguous K run is fetched with one 16-byte load per lane.
+// A sample's whole pass is local to its row, so one kernel (k_net) takes 32 rows from the
+// features to the logit and, in training, back to dZ1: eight waves hold the 32 x 256
+// activations of a layer, one 32 x 32 block each accumulated by v_mfma_f32_32x32x16_bf16,
+// and hand them on in LDS.  Only the weight gradients contract over the batch: k_net leaves
+// their operands in fragment order along the batch, k_wgrad multiplies them over splits of
+// the batch and k_update adds the splits and the column sums in a fixed order, then takes
+// the Adam step.
+//
+// Bound by: a launch, the chain of a layer's 16 to 18 matrix instructions at one wave each and
+// three barriers, not by the matrix cores or memory.  Weights and gradient operands lie in
+// the order in which the lanes load them (fragment); by rows, each load touched a line a lane:
+// k_net 13.5 and 22.3 us, k_wgrad 16.1, now 10.6, 17.9 and 10.3.  Measured as a call: the
+// forward pass of 8,192 rows 48.5 us as five kernels through memory, now 23.5; loss and
+// gradients of 4,096 rows 136 us as sixteen, now 40.
 #include <string.h>
 
+#include <algorithm>
 #include <cmath>
-#include <mutex>
 #include <string>
 
 #include "internal.h"
 #include "pirrt.h"
 
 using namespace pirrt;
-
-static __device__ __align__(256) uint16_t scratch[(PIRRT_MLP_NOALLOC_MAX_BATCH) * (288 + 2 * 256)];
 
 namespace {
 
@@ -38,20 +45,6 @@ constexpr int64_t kOffB3 = kOffW3 + kHidden;
 constexpr int64_t kNumParams = kOffB3 + 1;
 constexpr int kThreads = 256;
 
-// Scratch of pirrt_mlp_forward_noalloc: the staged bf16 features X [kNoAllocRows x kIn]
-// followed by the bf16 activations A1 and A2 [kNoAllocRows x kHidden each], 12.5 MiB.
-// Each GPU the library runs on holds its own copy until the process ends.  Host code
-// never passes this name to a kernel: it uses the device address that
-// hipGetSymbolAddress returns for the current GPU (noalloc_scratch below).
-constexpr int32_t kNoAllocRows = PIRRT_MLP_NOALLOC_MAX_BATCH;  // a multiple of 64
-constexpr int64_t kScratchX = 0;
-constexpr int64_t kScratchA1 = kScratchX + (int64_t)kNoAllocRows * kIn;
-constexpr int64_t kScratchA2 = kScratchA1 + (int64_t)kNoAllocRows * kHidden;
-constexpr int64_t kScratchElems = kScratchA2 + (int64_t)kNoAllocRows * kHidden;
-static_assert(kNoAllocRows % 64 == 0, "rows are padded to 64");
-static_assert(sizeof(scratch) == sizeof(uint16_t) * (size_t)kScratchElems, "scratch layout");
-static_assert((kScratchA1 * 2) % 256 == 0 && (kScratchA2 * 2) % 256 == 0, "each part stays 256-byte aligned");
-
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -63,231 +56,374 @@ __device__ __forceinline__ uint16_t to_bf16(float f) {
 
 __device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-enum Epi { kEpiFwd = 0, kEpiMaskBf16 = 1, kEpiF32 = 2 };
+__device__ __forceinline__ bf16x8 load8(const uint16_t* p) {
+  return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p));
+}
 
-struct GemmArgs {
-  int32_t M, N, K;
-  const uint16_t* A;  // element (m, k) at A[m * sam + k * sak]
-  int64_t sam, sak;
-  const uint16_t* B;  // element (k, n) at B[k * sbk + n * sbn]
-  int64_t sbk, sbn;
-  const float* bias;  // kEpiFwd: per column
-  const float* zref;  // kEpiMaskBf16: fp32 [M x N] whose sign gates the output
-  float* zout;        // kEpiFwd: fp32 pre-activation [M x N] (nullable); kEpiF32: output
-  uint16_t* bout;     // kEpiFwd / kEpiMaskBf16: bf16 output [M x N]
-  int64_t kchunk;     // split K: workgroup z sums k in [z * kchunk, (z + 1) * kchunk) and
-                      // kEpiF32 writes its partial product to zout + z * M * N
+constexpr int kRows = 32;               // batch rows of a workgroup's tile
+constexpr int kNetThreads = 512;        // eight waves, 32 hidden units each
+constexpr int kXStride = kIn + 8;       // LDS row strides: 16-byte reads of 16 rows at one
+constexpr int kAStride = kHidden + 8;   // column fall into distinct banks
+constexpr int kNetGroups = 256;         // workgroups of a training pass at most
+constexpr int kSplits = 16;             // batch splits of the weight gradients at most
+constexpr int kGradRows = kIn + kHidden;  // rows of gW1 and gW2 together
+constexpr int kColSums = 3 * kHidden + 2;  // gb1, gb2, gw3, gb3, loss: per workgroup
+static_assert(kHidden == 32 * (kNetThreads / 64), "a wave per 32 hidden units");
+
+// Where element k of feature f lies in an operand that products read along k, in steps of 16:
+// the 64 lanes' fragments of one (32 features, step) block follow each other, so that a
+// fragment load of a wave is 1 KB in a row (rows 512 bytes apart cost four times the lines).
+__device__ __forceinline__ int64_t fragment(int64_t f, int64_t k, int64_t steps) {
+  return ((f >> 5) * steps + (k >> 4)) * 512 + ((k >> 3 & 1) * 32 + (f & 31)) * 8 + (k & 7);
+}
+
+// What a training pass leaves for the weight gradients: operands in fragment order, the
+// batch along k.
+struct TrainOut {
+  uint16_t* XT;
+  uint16_t* A1T;
+  uint16_t* dZ1T;
+  uint16_t* dZ2T;
+  float* colsum;  // [workgroup][kColSums]
+  int64_t steps;  // of 16 batch rows
 };
 
-template <bool kAContig>
-__device__ __forceinline__ bf16x8 load_a(const GemmArgs& g, int64_t m, int64_t k) {
-  if (kAContig) {
-    const uint4 w = *reinterpret_cast<const uint4*>(g.A + m * g.sam + k);
-    return __builtin_bit_cast(bf16x8, w);
-  }
-  uint16_t t[8];
+// One layer's 32 x 32 block of the wave: K products with 16 at a time, k ascending.  Lane l
+// supplies A row l % 32 (LDS) and B column l % 32 (the weights, in fragment order) with the 8
+// consecutive k from 8 (l / 32); accumulator register r of lane l holds row
+// 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32.
+// The weights' fragments are loaded ahead of the barrier before the layer (Weights), all in
+// flight together.
+template <int K>
+struct Weights {
+  bf16x8 b[K / 16];
+  __device__ __forceinline__ void load(const uint16_t* w) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i) t[i] = g.A[m * g.sam + (k + i) * g.sak];
-  return __builtin_bit_cast(bf16x8, t);
+    for (int k = 0; k < K / 16; ++k) b[k] = load8(w + 512 * k);
+    __builtin_amdgcn_sched_barrier(0);  // issued here, not where they are used
+  }
+  __device__ __forceinline__ f32x16 product(const uint16_t* a) const {
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll
+    for (int k = 0; k < K / 16; ++k)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(load8(a + 16 * k), b[k], acc, 0, 0, 0);
+    return acc;
+  }
+};
+
+// bf16(relu(z)); in training a unit that is off (z <= 0) is -0, so that its sign carries
+// [z > 0] for the backward pass (a zero of either sign adds nothing to a product).
+template <bool kTrain>
+__device__ __forceinline__ uint16_t activate(float z) {
+  return z > 0.0f ? to_bf16(z) : (uint16_t)(kTrain ? 0x8000u : 0u);
 }
 
-template <bool kBContig>
-__device__ __forceinline__ bf16x8 load_b(const GemmArgs& g, int64_t k, int64_t n) {
-  if (kBContig) {
-    const uint4 w = *reinterpret_cast<const uint4*>(g.B + n * g.sbn + k);
-    return __builtin_bit_cast(bf16x8, w);
-  }
-  uint16_t t[8];
+// Forward pass of rows [32 tile, 32 tile + 32); kTrain: loss, dZ2, dZ1 and the transposed
+// operands too.  Without kTrain one tile a workgroup; with it the workgroups loop over the
+// tiles and keep their column sums in registers.  Rows past B have zero features and, in
+// training, zero dz.
+template <bool kTrain>
+__global__ void __launch_bounds__(kNetThreads, 2) k_net(int32_t B, int32_t tiles, int32_t in_dim,
+                                                        const float* __restrict__ x, const uint16_t* __restrict__ W1t,
+                                                        const uint16_t* __restrict__ W2t,
+                                                        const uint16_t* __restrict__ W2b,
+                                                        const uint16_t* __restrict__ w3b, const float* __restrict__ P,
+                                                        const float* __restrict__ y, float* __restrict__ logits,
+                                                        TrainOut out) {
+  __shared__ __align__(16) uint16_t sx[kRows * kXStride];  // X, then dZ2
+  __shared__ __align__(16) uint16_t sa[kRows * kAStride];  // A1
+  __shared__ __align__(16) uint16_t sb[kRows * kAStride];  // A2
+  __shared__ float w3[kHidden], sdz[kRows], sloss[kRows];
+  const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
+  const int c = lane & 31, half = lane >> 5;
+  const int n = 32 * wave + c;  // the lane's hidden unit
+  if (t < kHidden) w3[t] = from_bf16(w3b[t]);
+  const float b1 = P[kOffB1 + n], b2 = P[kOffB2 + n];
+  float g1 = 0.0f, g2 = 0.0f, g3 = 0.0f, gb3 = 0.0f, gl = 0.0f;  // column sums
+  Weights<kIn> w1;
+  Weights<kHidden> w2;
+  for (int32_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const int64_t row0 = (int64_t)tile * kRows;
+    // (the weights are read again for every tile: kept over the loop they would spill)
+    asm volatile("" : "+s"(W1t), "+s"(W2t), "+s"(W2b));
+    {  // 16 threads a row, all of a thread's features in flight
+      const int r = t / 16, k0 = t % 16;
+      const float* xr = x + (row0 + r) * in_dim;
+      float f[kIn / 16];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) t[i] = g.B[(k + i) * g.sbk + n * g.sbn];
-  return __builtin_bit_cast(bf16x8, t);
-}
-
-// One 32 x 32 output block per wave.  Lane l supplies A row l % 32 and B column
-// l % 32 with the 8 consecutive K entries starting at 8 * (l / 32); accumulator
-// register r of lane l holds row 8 * (r / 4) + 4 * (l / 32) + r % 4, column l % 32.
-template <bool kAContig, bool kBContig, int kEpi>
-__global__ void __launch_bounds__(kThreads) k_gemm(GemmArgs g) {
-  const int wave = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
-  const int64_t m0 = (int64_t)blockIdx.y * 64 + (wave >> 1) * 32;
-  const int64_t n0 = (int64_t)blockIdx.x * 64 + (wave & 1) * 32;
-  if (m0 >= g.M || n0 >= g.N) return;  // whole wave outside (M, N are multiples of 32)
-  const int64_t am = m0 + (lane & 31), bn = n0 + (lane & 31);
-  const int kq = (lane >> 5) * 8;
-  f32x16 acc;
+      for (int j = 0; j < kIn / 16; ++j) f[j] = row0 + r < B && k0 + 16 * j < in_dim ? xr[k0 + 16 * j] : 0.0f;
+      w1.load(W1t + wave * 32 * kIn + 8 * lane);
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-  const int64_t k0 = (int64_t)blockIdx.z * g.kchunk;
-  const int64_t k1 = k0 + g.kchunk < g.K ? k0 + g.kchunk : g.K;
-  for (int64_t k = k0; k < k1; k += 16) {
-    const bf16x8 a = load_a<kAContig>(g, am, k + kq);
-    const bf16x8 b = load_b<kBContig>(g, k + kq, bn);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
-  }
-  const int64_t col = n0 + (lane & 31);
-#pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    const int64_t row = m0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-    const int64_t o = row * g.N + col;
-    if (kEpi == kEpiFwd) {
-      const float v = acc[r] + g.bias[col];
-      if (g.zout) g.zout[o] = v;
-      g.bout[o] = to_bf16(v > 0.0f ? v : 0.0f);
-    } else if (kEpi == kEpiMaskBf16) {
-      g.bout[o] = to_bf16(g.zref[o] > 0.0f ? acc[r] : 0.0f);
-    } else {
-      g.zout[(int64_t)blockIdx.z * g.M * g.N + o] = acc[r];
+      for (int j = 0; j < kIn / 16; ++j) sx[r * kXStride + k0 + 16 * j] = to_bf16(f[j]);
     }
-  }
-}
-
-// X = bf16(features), zero-padded to kIn columns and Bp rows.
-__global__ void k_features(int32_t B, int32_t Bp, int32_t in_dim, const float* __restrict__ x,
-                           uint16_t* __restrict__ X) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)Bp * kIn) return;
-  const int64_t b = i / kIn, k = i % kIn;
-  X[i] = (b < B && k < in_dim) ? to_bf16(x[b * in_dim + k]) : (uint16_t)0;
-}
-
-// z = A2 w3 + b3 per row (one thread per row, k ascending); with labels also
-// dz = (sigmoid(z) - y) / B and the workgroup's loss sum (rows in order) in lpart.
-// Without labels only rows b < B of z are written (z may be the caller's logits).
-__global__ void __launch_bounds__(kThreads) k_layer3(int32_t B, int32_t Bp, const uint16_t* __restrict__ A2,
-                                                     const uint16_t* __restrict__ w3b, const float* __restrict__ P,
-                                                     const float* __restrict__ y, float* __restrict__ z,
-                                                     float* __restrict__ dz, float* __restrict__ lpart) {
-  __shared__ float wl[kHidden];
-  __shared__ float red[kThreads];
-  for (int k = threadIdx.x; k < kHidden; k += kThreads) wl[k] = from_bf16(w3b[k]);
-  __syncthreads();
-  const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  float l = 0.0f;
-  if (b < Bp) {
-    const uint4* row = reinterpret_cast<const uint4*>(A2 + b * kHidden);
-    float s = 0.0f;
-    for (int q = 0; q < kHidden / 8; ++q) {
-      const uint4 w = row[q];
-      const uint32_t h[4] = {w.x, w.y, w.z, w.w};
+    __syncthreads();
+    if (kTrain) {
+      for (int i = t; i < kIn * 4; i += kNetThreads) {  // X^T, eight rows of a feature each
+        const int k = i % kIn, r = 8 * (i / kIn);
+        uint16_t v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = sx[(r + e) * kXStride + k];
+        *reinterpret_cast<uint4*>(out.XT + fragment(k, row0 + r, out.steps)) =
+            make_uint4(v[0] | (uint32_t)v[1] << 16, v[2] | (uint32_t)v[3] << 16, v[4] | (uint32_t)v[5] << 16,
+                       v[6] | (uint32_t)v[7] << 16);
+      }
+    }
+    // layer 1
+    f32x16 acc = w1.product(sx + c * kXStride + 8 * half);
+    w2.load(W2t + wave * 32 * kHidden + 8 * lane);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      uint16_t v[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        s += __uint_as_float(h[e] << 16) * wl[8 * q + 2 * e];
-        s += __uint_as_float(h[e] & 0xffff0000u) * wl[8 * q + 2 * e + 1];
+        v[e] = activate<kTrain>(acc[4 * q + e] + b1);
+        sa[(8 * q + 4 * half + e) * kAStride + n] = v[e];
       }
+      if (kTrain)
+        *reinterpret_cast<uint2*>(out.A1T + fragment(n, row0 + 8 * q + 4 * half, out.steps)) =
+            make_uint2(v[0] | (uint32_t)v[1] << 16, v[2] | (uint32_t)v[3] << 16);
     }
-    const float zb = s + P[kOffB3];
-    if (y || b < B) z[b] = zb;  // a forward pass writes the B logits only
-    if (y) {
-      if (b < B) {
-        const float yb = y[b];
-        dz[b] = (1.0f / (1.0f + expf(-zb)) - yb) / (float)B;
-        l = (fmaxf(zb, 0.0f) - zb * yb + log1pf(expf(-fabsf(zb)))) / (float)B;
+    __syncthreads();
+    // layer 2
+    acc = w2.product(sa + c * kAStride + 8 * half);
+    if (kTrain) w2.load(W2b + wave * 32 * kHidden + 8 * lane);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        sb[(8 * q + 4 * half + e) * kAStride + n] = activate<kTrain>(acc[4 * q + e] + b2);
+    __syncthreads();
+    // layer 3: one thread a row, k ascending
+    if (t < kRows) {
+      float z = 0.0f;
+#pragma unroll 4
+      for (int q = 0; q < kHidden / 8; ++q) {
+        const uint4 w = *reinterpret_cast<const uint4*>(sb + t * kAStride + 8 * q);
+        const uint32_t h[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          z += __uint_as_float(h[e] << 16) * w3[8 * q + 2 * e];
+          z += __uint_as_float(h[e] & 0xffff0000u) * w3[8 * q + 2 * e + 1];
+        }
+      }
+      z += P[kOffB3];
+      const int64_t row = row0 + t;
+      if (!kTrain) {
+        if (row < B) logits[row] = z;
       } else {
-        dz[b] = 0.0f;
+        float dz = 0.0f, l = 0.0f;
+        if (row < B) {
+          const float yb = y[row];
+          dz = (1.0f / (1.0f + expf(-z)) - yb) / (float)B;
+          l = (fmaxf(z, 0.0f) - z * yb + log1pf(expf(-fabsf(z)))) / (float)B;
+        }
+        sdz[t] = dz;
+        sloss[t] = l;
       }
     }
+    if (!kTrain) return;  // one tile a workgroup
+    __syncthreads();
+    // dZ2 = bf16(dz w3^T [Z2 > 0]) over X; gw3, gb2 (16 rows a thread), gb3 and the loss
+    {
+      const int col = t % kHidden, r0 = 16 * (t / kHidden);
+      const float w = w3[col];
+      uint16_t v[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const uint16_t a2 = sb[(r0 + r) * kAStride + col];
+        const float dz = sdz[r0 + r];
+        g3 += from_bf16(a2) * dz;
+        v[r] = to_bf16(a2 & 0x8000u ? 0.0f : dz * w);
+        g2 += from_bf16(v[r]);
+        sx[(r0 + r) * kAStride + col] = v[r];
+      }
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        *reinterpret_cast<uint4*>(out.dZ2T + fragment(col, row0 + r0 + 8 * q, out.steps)) =
+            make_uint4(v[8 * q] | (uint32_t)v[8 * q + 1] << 16, v[8 * q + 2] | (uint32_t)v[8 * q + 3] << 16,
+                       v[8 * q + 4] | (uint32_t)v[8 * q + 5] << 16, v[8 * q + 6] | (uint32_t)v[8 * q + 7] << 16);
+      if (t == 0)
+        for (int r = 0; r < kRows; ++r) {
+          gb3 += sdz[r];
+          gl += sloss[r];
+        }
+    }
+    __syncthreads();
+    // dZ1 = bf16(dZ2 W2^T [Z1 > 0]): element (k, n) of W2^T is W2b[n][k]
+    acc = w2.product(sx + c * kAStride + 8 * half);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      uint16_t v[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[e] = to_bf16(sa[(8 * q + 4 * half + e) * kAStride + n] & 0x8000u ? 0.0f : acc[4 * q + e]);
+        g1 += from_bf16(v[e]);
+      }
+      *reinterpret_cast<uint2*>(out.dZ1T + fragment(n, row0 + 8 * q + 4 * half, out.steps)) =
+          make_uint2(v[0] | (uint32_t)v[1] << 16, v[2] | (uint32_t)v[3] << 16);
+    }
+    __syncthreads();  // sx, sa and sb are read: the next tile may write them
   }
-  if (!y) return;
-  red[threadIdx.x] = l;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float t = 0.0f;
-    for (int i = 0; i < kThreads; ++i) t += red[i];
-    lpart[blockIdx.x] = t;
-  }
-}
-
-// dZ2 = bf16(dz w3^T * [Z2 > 0])
-__global__ void k_dz2(int32_t Bp, const float* __restrict__ dz, const uint16_t* __restrict__ w3b,
-                      const float* __restrict__ Z2, uint16_t* __restrict__ dZ2) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)Bp * kHidden) return;
-  const int64_t b = i / kHidden, k = i % kHidden;
-  dZ2[i] = to_bf16(Z2[i] > 0.0f ? dz[b] * from_bf16(w3b[k]) : 0.0f);
-}
-
-// out[n] = sum over rows of a bf16 [rows x N] matrix (one thread per column).
-// Column sums over the batch in two fixed-order stages (the same bits on every run):
-// workgroup (c, j) sums rows [j * rows_per, (j + 1) * rows_per) of 64 columns, four
-// row phases per column then the phases in order, into part[j][col]; k_sum_parts then
-// adds the kColParts partials of each column in order.  Column N (when `ones`) is the
-// all-ones column, and `w` (nullable) weights the rows: sum_b w[b] M[b][col].
-constexpr int kColParts = 64;
-constexpr int kSplitK = 32;  // K splits of the weight-gradient products
-
-__global__ void __launch_bounds__(kThreads) k_colsum_part(int32_t rows, int32_t rows_per, int32_t N, bool ones,
-                                                         const uint16_t* __restrict__ M,
-                                                         const float* __restrict__ w, float* __restrict__ part) {
-  __shared__ float red[4][64];
-  const int c = threadIdx.x & 63, ph = threadIdx.x >> 6;
-  const int col = blockIdx.x * 64 + c;
-  const int ncol = N + (ones ? 1 : 0);
-  const int64_t r0 = (int64_t)blockIdx.y * rows_per;
-  const int64_t r1 = r0 + rows_per < rows ? r0 + rows_per : rows;
-  float s = 0.0f;
-  if (col < ncol) {
-    for (int64_t r = r0 + ph; r < r1; r += 4) {
-      const float x = col < N ? from_bf16(M[r * N + col]) : 1.0f;
-      s += w ? x * w[r] : x;
+  if (kTrain) {
+    float* cs = out.colsum + (int64_t)blockIdx.x * kColSums;
+    g1 += __shfl_xor(g1, 32, kWave);
+    if (half == 0) cs[n] = g1;
+    // the two row halves of gb2 and gw3 meet in LDS
+    float* meet = reinterpret_cast<float*>(sx);
+    if (t >= kHidden) {
+      meet[t - kHidden] = g2;
+      meet[t] = g3;
+    }
+    __syncthreads();
+    if (t < kHidden) {
+      cs[kHidden + t] = g2 + meet[t];
+      cs[2 * kHidden + t] = g3 + meet[kHidden + t];
+    }
+    if (t == 0) {
+      cs[3 * kHidden] = gb3;
+      cs[3 * kHidden + 1] = gl;
     }
   }
-  red[ph][c] = s;
-  __syncthreads();
-  if (ph == 0 && col < ncol) part[(int64_t)blockIdx.y * ncol + col] = ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c];
 }
 
-// out[i] = sum over z < parts of part[z * count + i], in order of z (four outputs per
-// thread, eight partials in flight).
-__global__ void k_sum_parts(int64_t count, int32_t parts, const float* __restrict__ part, float* __restrict__ out) {
-  const int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
-  if (i0 >= count) return;
-  const int nv = count - i0 < 4 ? (int)(count - i0) : 4;
-  float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  int32_t z = 0;
-  for (; z + 8 <= parts; z += 8) {
-    float v[8][4];
+// Weight gradients, one split of the batch: rows 0 .. 287 are gW1 = X^T dZ1, rows 288 ..
+// 543 gW2 = A1^T dZ2, each element the sum over the split's batch rows.  A workgroup takes 32
+// rows x 256 columns, a wave two 32 x 32 blocks; the next eight steps' operands are in flight at once.
+__global__ void __launch_bounds__(kThreads, 2) k_wgrad(int64_t steps, int64_t per, TrainOut in,
+                                                       float* __restrict__ part) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int c = lane & 31, half = lane >> 5;
+  const int m0 = 32 * blockIdx.x;
+  const bool first = m0 < kIn;
+  const int64_t block = 512 * in.steps;
+  const uint16_t* a = (first ? in.XT + m0 / 32 * block : in.A1T + (m0 - kIn) / 32 * block) + 8 * lane;
+  const uint16_t* b0 = (first ? in.dZ1T : in.dZ2T) + 2 * wave * block + 8 * lane;
+  const uint16_t* b1 = b0 + block;
+  const int64_t k0 = (int64_t)blockIdx.y * per, k1 = k0 + per < steps ? k0 + per : steps;
+  f32x16 x, y;
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
+  for (int r = 0; r < 16; ++r) x[r] = y[r] = 0.0f;
+  int64_t k = k0;
+  for (; k + 8 <= k1; k += 8) {
+    bf16x8 av[8], bv[8], cv[8];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) v[u][j] = j < nv ? part[(int64_t)(z + u) * count + i0 + j] : 0.0f;
+    for (int j = 0; j < 8; ++j) {
+      av[j] = load8(a + 512 * (k + j));
+      bv[j] = load8(b0 + 512 * (k + j));
+      cv[j] = load8(b1 + 512 * (k + j));
+    }
+    __builtin_amdgcn_sched_barrier(0);  // all 24 loads in flight
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) s[j] += v[u][j];
+    for (int j = 0; j < 8; ++j) {
+      x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[j], bv[j], x, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[j], cv[j], y, 0, 0, 0);
+    }
   }
-  for (; z < parts; ++z)
+  for (; k < k1; ++k) {
+    const bf16x8 av = load8(a + 512 * k);
+    x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, load8(b0 + 512 * k), x, 0, 0, 0);
+    y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, load8(b1 + 512 * k), y, 0, 0, 0);
+  }
+  float* p = part + (int64_t)blockIdx.y * kGradRows * kHidden;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) s[j] += j < nv ? part[(int64_t)z * count + i0 + j] : 0.0f;
-  for (int j = 0; j < nv; ++j) out[i0 + j] = s[j];
+  for (int r = 0; r < 16; ++r) {
+    const int64_t row = m0 + 8 * (r >> 2) + 4 * half + (r & 3);
+    p[row * kHidden + 64 * wave + c] = x[r];
+    p[row * kHidden + 64 * wave + 32 + c] = y[r];
+  }
 }
 
-__global__ void k_adam(int64_t np, float* __restrict__ P, const float* __restrict__ G, float* __restrict__ m,
-                       float* __restrict__ v, float lr, float b1, float b2, float eps, float c1, float c2) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= np) return;
-  const float g = G[i];
-  const float mi = b1 * m[i] + (1.0f - b1) * g;
-  const float vi = b2 * v[i] + (1.0f - b2) * g * g;
-  m[i] = mi;
-  v[i] = vi;
-  P[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+// Adam (kTrain of the step) on one parameter.
+struct AdamArgs {
+  float* m;
+  float* v;
+  float lr, b1, b2, eps, c1, c2;
+};
+
+__device__ __forceinline__ float adam(const AdamArgs& a, int64_t i, float p, float g) {
+  const float mi = a.b1 * a.m[i] + (1.0f - a.b1) * g;
+  const float vi = a.b2 * a.v[i] + (1.0f - a.b2) * g * g;
+  a.m[i] = mi;
+  a.v[i] = vi;
+  return p - a.lr * (mi / a.c1) / (sqrtf(vi / a.c2) + a.eps);
 }
 
-// bf16 copies of the weights: W2b row-major (the backward product dZ2 W2^T reads its
-// rows contiguously), W1t / W2t transposed (the forward products read their columns
-// contiguously).
+// The gradient of every parameter, from the splits (in their order) and the workgroups'
+// column sums (lane l of a column's eight adds workgroups l, l + 8, ... in order, then the
+// lanes pairwise).  kStep: the Adam step and the bf16 copies of the new weights; else the
+// gradients go to G.  Workgroups [0, kGradRows * 256 / kThreads) take the weights, the others
+// the column sums.
+template <bool kStep>
+__global__ void __launch_bounds__(kThreads) k_update(int splits, int groups, const float* __restrict__ part,
+                                                    const float* __restrict__ colsum, float* __restrict__ G,
+                                                    float* __restrict__ P, AdamArgs ad, uint16_t* __restrict__ W1t,
+                                                    uint16_t* __restrict__ W2b, uint16_t* __restrict__ W2t,
+                                                    uint16_t* __restrict__ w3b, float* __restrict__ loss) {
+  constexpr int kWeightBlocks = kGradRows * kHidden / kThreads;
+  if (blockIdx.x < kWeightBlocks) {
+    const int64_t e = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    float s = 0.0f;
+#pragma unroll 8
+    for (int z = 0; z < splits; ++z) s += part[(int64_t)z * kGradRows * kHidden + e];
+    const int row = (int)(e / kHidden), n = (int)(e % kHidden);
+    const bool first = row < kIn;
+    const int k = first ? row : row - kIn;
+    const int64_t i = (first ? kOffW1 : kOffW2) + (int64_t)k * kHidden + n;
+    if (!kStep) {
+      G[i] = s;
+      return;
+    }
+    const float p = adam(ad, i, P[i], s);
+    P[i] = p;
+    const uint16_t b = to_bf16(p);
+    if (first) {
+      W1t[fragment(n, k, kIn / 16)] = b;
+    } else {
+      W2b[fragment(k, n, kHidden / 16)] = b;
+      W2t[fragment(n, k, kHidden / 16)] = b;
+    }
+    return;
+  }
+  const int t = (blockIdx.x - kWeightBlocks) * kThreads + threadIdx.x;
+  const int col = t / 8, l = t % 8;
+  float s = 0.0f;
+  if (col < kColSums)
+#pragma unroll 4
+    for (int w = l; w < groups; w += 8) s += colsum[(int64_t)w * kColSums + col];
+#pragma unroll
+  for (int o = 4; o > 0; o >>= 1) s += __shfl_xor(s, o, kWave);
+  if (col >= kColSums || l != 0) return;
+  if (col == kColSums - 1) {
+    *loss = s;
+    return;
+  }
+  const int64_t i = col < kHidden ? kOffB1 + col
+                                  : (col < 2 * kHidden ? kOffB2 + (col - kHidden) : kOffW3 + (col - 2 * kHidden));
+  if (!kStep) {
+    G[i] = s;
+    return;
+  }
+  const float p = adam(ad, i, P[i], s);
+  P[i] = p;
+  if (col >= 2 * kHidden && col < 3 * kHidden) w3b[col - 2 * kHidden] = to_bf16(p);
+}
+
+// bf16 copies of the weights in fragment order: W2b by rows (the backward product dZ2 W2^T),
+// W1t / W2t by columns (the forward products).
 __global__ void k_refresh(const float* __restrict__ P, uint16_t* __restrict__ W1t, uint16_t* __restrict__ W2b,
                           uint16_t* __restrict__ W2t, uint16_t* __restrict__ w3b) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < (int64_t)kIn * kHidden) {
     const int64_t k = i / kHidden, n = i % kHidden;
-    W1t[n * kIn + k] = to_bf16(P[kOffW1 + i]);
+    W1t[fragment(n, k, kIn / 16)] = to_bf16(P[kOffW1 + i]);
   }
   if (i < (int64_t)kHidden * kHidden) {
     const int64_t k = i / kHidden, n = i % kHidden;
     const uint16_t b = to_bf16(P[kOffW2 + i]);
-    W2b[i] = b;
-    W2t[n * kHidden + k] = b;
+    W2b[fragment(k, n, kHidden / 16)] = b;
+    W2t[fragment(n, k, kHidden / 16)] = b;
   }
   if (i < kHidden) w3b[i] = to_bf16(P[kOffW3 + i]);
 }
@@ -306,23 +442,15 @@ struct pirrt_mlp {
   float* G = nullptr;
   float* m = nullptr;
   float* v = nullptr;
-  uint16_t* W1t = nullptr;  // bf16 W1 transposed [kHidden x kIn]
-  uint16_t* W2b = nullptr;  // bf16 W2 [kHidden x kHidden]
-  uint16_t* W2t = nullptr;  // bf16 W2 transposed
+  uint16_t* W1t = nullptr;  // bf16 W1 by columns, in fragment order
+  uint16_t* W2b = nullptr;  // bf16 W2 by rows
+  uint16_t* W2t = nullptr;  // bf16 W2 by columns
   uint16_t* w3b = nullptr;
   float* xin = nullptr;   // staging of host features
   float* yin = nullptr;
-  uint16_t* X = nullptr;
-  float* Z1 = nullptr;
-  uint16_t* A1 = nullptr;
-  float* Z2 = nullptr;
-  uint16_t* A2 = nullptr;
-  float* z = nullptr;
-  float* dz = nullptr;
-  uint16_t* dZ2 = nullptr;
-  uint16_t* dZ1 = nullptr;
-  float* dloss = nullptr;
-  float* part = nullptr;   // partial sums of the split reductions
+  float* z = nullptr;     // logits on their way to host memory
+  TrainOut T = {};        // operands of the weight gradients, column sums
+  float* part = nullptr;  // the weight gradients' splits
   float* hloss = nullptr;  // pinned
   bool poisoned = false;
   std::string err;
@@ -369,9 +497,8 @@ void free_dev(T*& p) {
 void release(pirrt_mlp* N) {
   free_dev(N->P); free_dev(N->G); free_dev(N->m); free_dev(N->v); free_dev(N->W1t); free_dev(N->W2b);
   free_dev(N->W2t);
-  free_dev(N->w3b); free_dev(N->xin); free_dev(N->yin); free_dev(N->X); free_dev(N->Z1); free_dev(N->A1);
-  free_dev(N->Z2); free_dev(N->A2); free_dev(N->z); free_dev(N->dz); free_dev(N->dZ2); free_dev(N->dZ1);
-  free_dev(N->dloss);
+  free_dev(N->w3b); free_dev(N->xin); free_dev(N->yin); free_dev(N->z); free_dev(N->T.XT); free_dev(N->T.A1T);
+  free_dev(N->T.dZ1T); free_dev(N->T.dZ2T); free_dev(N->T.colsum);
   free_dev(N->part);
   if (N->hloss) (void)hipHostFree(N->hloss);
   N->hloss = nullptr;
@@ -385,98 +512,50 @@ int mguard(pirrt_mlp* N) {
   return PIRRT_OK;
 }
 
-void launch_gemm(const GemmArgs& g, bool a_contig, bool b_contig, int epi, hipStream_t s, int splits = 1) {
-  const dim3 grid((unsigned)((g.N + 63) / 64), (unsigned)((g.M + 63) / 64), (unsigned)splits);
-#define GEMM(AC, BC, E) hipLaunchKernelGGL((k_gemm<AC, BC, E>), grid, dim3(kThreads), 0, s, g)
-  if (epi == kEpiFwd) {
-    if (a_contig && b_contig) GEMM(true, true, kEpiFwd); else GEMM(true, false, kEpiFwd);
-  } else if (epi == kEpiMaskBf16) {
-    GEMM(true, true, kEpiMaskBf16);
-  } else {
-    if (a_contig) GEMM(true, false, kEpiF32); else GEMM(false, false, kEpiF32);
-  }
-#undef GEMM
-}
-
-// Deterministic column sums of a bf16 [rows x cols] matrix (see k_colsum_part) into out.
-void launch_colsum(pirrt_mlp* N, int32_t rows, int32_t cols, bool ones, const uint16_t* M, const float* w,
-                   float* out) {
-  const int32_t ncol = cols + (ones ? 1 : 0);
-  const int32_t per = (rows + kColParts - 1) / kColParts;
-  hipLaunchKernelGGL(k_colsum_part, dim3((unsigned)((ncol + 63) / 64), kColParts), dim3(kThreads), 0, N->stream, rows,
-                     per, cols, ones, M, w, N->part);
-  hipLaunchKernelGGL(k_sum_parts, dim3(nblocks((ncol + 3) / 4)), dim3(kThreads), 0, N->stream, (int64_t)ncol,
-                     kColParts, N->part, out);
-}
-
-// A weight gradient (M x N, K = the batch): the K range is split over kSplitK
-// workgroup layers (an output tile alone would leave most of the chip idle), the
-// partial products go to N->part and are added in split order.
-void launch_weight_grad(pirrt_mlp* N, GemmArgs g, float* out) {
-  const int64_t kc = ((g.K + kSplitK - 1) / kSplitK + 15) / 16 * 16;
-  const int splits = (int)((g.K + kc - 1) / kc);
-  g.kchunk = kc;
-  g.zout = N->part;
-  launch_gemm(g, false, false, kEpiF32, N->stream, splits);
-  hipLaunchKernelGGL(k_sum_parts, dim3(nblocks(((int64_t)g.M * g.N + 3) / 4)), dim3(kThreads), 0, N->stream,
-                     (int64_t)g.M * g.N, splits, N->part, out);
-}
-
-// Features into X (padded rows and columns are zero); B rows, Bp = B rounded up to 64.
-int stage_inputs(pirrt_mlp* N, int32_t B, int32_t Bp, const float* x, const float* y, int mem_kind,
+// Host features and labels through the handle's staging buffers.
+int stage_inputs(pirrt_mlp* N, int32_t B, const float* x, const float* y, int mem_kind, const float** xd,
                  const float** yd) {
   hipStream_t s = N->stream;
-  const float* xd = x;
+  *xd = x;
   *yd = y;
   if (mem_kind == PIRRT_MEM_HOST) {
     MHIP(N, hipMemcpyAsync(N->xin, x, sizeof(float) * (size_t)B * N->in_dim, hipMemcpyHostToDevice, s));
-    xd = N->xin;
+    *xd = N->xin;
     if (y) {
       MHIP(N, hipMemcpyAsync(N->yin, y, sizeof(float) * (size_t)B, hipMemcpyHostToDevice, s));
       *yd = N->yin;
     }
   }
-  hipLaunchKernelGGL(k_features, dim3(nblocks((int64_t)Bp * kIn)), dim3(kThreads), 0, s, B, Bp, N->in_dim, xd, N->X);
-  MHIP(N, hipGetLastError());
   return PIRRT_OK;
 }
 
-// X [Bp x kIn] -> A1 -> A2 ([Bp x kHidden] each, bf16); keep_z also stores the fp32
-// pre-activations in the handle's Z1 / Z2 for the backward pass.
-void enqueue_forward(pirrt_mlp* N, int32_t Bp, bool keep_z, const uint16_t* X, uint16_t* A1, uint16_t* A2) {
-  hipStream_t s = N->stream;
-  // element (k, n) of W1 is W1t[n * kIn + k]: contiguous in k
-  GemmArgs g1{Bp, kHidden, kIn, X, kIn, 1, N->W1t, 1, kIn, N->P + kOffB1, nullptr, keep_z ? N->Z1 : nullptr,
-              A1, kIn};
-  launch_gemm(g1, true, true, kEpiFwd, s);
-  GemmArgs g2{Bp, kHidden, kHidden, A1, kHidden, 1, N->W2t, 1, kHidden, N->P + kOffB2, nullptr,
-              keep_z ? N->Z2 : nullptr, A2, kHidden};
-  launch_gemm(g2, true, true, kEpiFwd, s);
+inline int32_t row_tiles(int32_t B) { return (B + kRows - 1) / kRows; }
+
+void enqueue_forward(pirrt_mlp* N, int32_t B, const float* xd, float* logits) {
+  const int32_t tiles = row_tiles(B);
+  hipLaunchKernelGGL(k_net<false>, dim3((unsigned)tiles), dim3(kNetThreads), 0, N->stream, B, tiles, N->in_dim, xd,
+                     N->W1t, N->W2t, N->W2b, N->w3b, N->P, nullptr, logits, TrainOut{});
 }
 
-// Forward + loss + gradients into N->G (the loss lands in N->dloss).
-int enqueue_gradients(pirrt_mlp* N, int32_t B, int32_t Bp, const float* yd) {
+// Forward, loss and backward; then the gradients into G, or with `step` one Adam step.  The
+// loss lands in N->hloss (pinned: the kernel writes it there).
+int enqueue_training(pirrt_mlp* N, int32_t B, const float* xd, const float* yd, float* G, const AdamArgs* step) {
   hipStream_t s = N->stream;
-  enqueue_forward(N, Bp, true, N->X, N->A1, N->A2);
-  const unsigned nb3 = nblocks(Bp);
-  hipLaunchKernelGGL(k_layer3, dim3(nb3), dim3(kThreads), 0, s, B, Bp, N->A2, N->w3b, N->P, yd, N->z, N->dz,
-                     N->part);
-  hipLaunchKernelGGL(k_sum_parts, dim3(1), dim3(kThreads), 0, s, (int64_t)1, (int32_t)nb3, N->part, N->dloss);
-  // gw3 = A2^T dz and gb3 = sum dz: the weighted column sums of [A2 | 1]
-  launch_colsum(N, Bp, kHidden, true, N->A2, N->dz, N->G + kOffW3);
-  hipLaunchKernelGGL(k_dz2, dim3(nblocks((int64_t)Bp * kHidden)), dim3(kThreads), 0, s, Bp, N->dz, N->w3b, N->Z2,
-                     N->dZ2);
-  launch_colsum(N, Bp, kHidden, false, N->dZ2, nullptr, N->G + kOffB2);
-  // gW2[i][j] = sum_b A1[b][i] dZ2[b][j]
-  GemmArgs gw2{kHidden, kHidden, Bp, N->A1, 1, kHidden, N->dZ2, kHidden, 1, nullptr, nullptr, nullptr, nullptr, 0};
-  launch_weight_grad(N, gw2, N->G + kOffW2);
-  // dZ1 = bf16(dZ2 W2^T * [Z1 > 0]): element (k = j, n = i) of W2^T is W2b[i][j]
-  GemmArgs gd1{Bp, kHidden, kHidden, N->dZ2, kHidden, 1, N->W2b, 1, kHidden, nullptr, N->Z1, nullptr, N->dZ1, kHidden};
-  launch_gemm(gd1, true, true, kEpiMaskBf16, s);
-  launch_colsum(N, Bp, kHidden, false, N->dZ1, nullptr, N->G + kOffB1);
-  // gW1[i][j] = sum_b X[b][i] dZ1[b][j]
-  GemmArgs gw1{kIn, kHidden, Bp, N->X, 1, kIn, N->dZ1, kHidden, 1, nullptr, nullptr, nullptr, nullptr, 0};
-  launch_weight_grad(N, gw1, N->G + kOffW1);
+  const int32_t tiles = row_tiles(B), groups = std::min(tiles, (int32_t)kNetGroups);
+  hipLaunchKernelGGL(k_net<true>, dim3((unsigned)groups), dim3(kNetThreads), 0, s, B, tiles, N->in_dim, xd, N->W1t,
+                     N->W2t, N->W2b, N->w3b, N->P, yd, nullptr, N->T);
+  // splits of at least 256 rows: enough workgroups to fill the chip, few partial sums
+  const int64_t steps = (int64_t)tiles * (kRows / 16);
+  const int64_t want = std::min<int64_t>(kSplits, (steps + 15) / 16), per = (steps + want - 1) / want;
+  const int splits = (int)((steps + per - 1) / per);
+  hipLaunchKernelGGL(k_wgrad, dim3(kGradRows / 32, (unsigned)splits), dim3(kThreads), 0, s, steps, per, N->T, N->part);
+  const dim3 grid((unsigned)(kGradRows * kHidden / kThreads + (kColSums * 8 + kThreads - 1) / kThreads));
+  if (step)
+    hipLaunchKernelGGL(k_update<true>, grid, dim3(kThreads), 0, s, splits, groups, N->part, N->T.colsum, nullptr, N->P,
+                       *step, N->W1t, N->W2b, N->W2t, N->w3b, N->hloss);
+  else
+    hipLaunchKernelGGL(k_update<false>, grid, dim3(kThreads), 0, s, splits, groups, N->part, N->T.colsum, G, N->P,
+                       AdamArgs{}, N->W1t, N->W2b, N->W2t, N->w3b, N->hloss);
   MHIP(N, hipGetLastError());
   return PIRRT_OK;
 }
@@ -486,29 +565,6 @@ int check_batch(pirrt_mlp* N, int32_t B, const float* x, int mem_kind) {
   if (B < 1 || B > N->max_batch) return mfail(N, PIRRT_EINVAL, "batch size outside 1..max_batch");
   if (!x) return mfail(N, PIRRT_EINVAL, "x is NULL");
   return PIRRT_OK;
-}
-
-inline int32_t padded(int32_t B) { return (B + 63) / 64 * 64; }
-
-// Device address of `scratch` on each GPU, looked up once per device with that device
-// current (at pirrt_mlp_create, or at the first no-allocation call on the device).
-constexpr int kMaxDevices = 64;
-std::mutex g_scratch_mu;
-uint16_t* g_scratch_dev[kMaxDevices] = {};
-
-// dev must be the current device.  Returns nullptr when the lookup fails.
-uint16_t* noalloc_scratch(int dev) {
-  if (dev < 0 || dev >= kMaxDevices) return nullptr;
-  std::lock_guard<std::mutex> lock(g_scratch_mu);
-  if (!g_scratch_dev[dev]) {
-    void* p = nullptr;
-    if (hipGetSymbolAddress(&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) {
-      (void)hipGetLastError();
-      return nullptr;
-    }
-    g_scratch_dev[dev] = static_cast<uint16_t*>(p);
-  }
-  return g_scratch_dev[dev];
 }
 
 }  // namespace
@@ -538,11 +594,10 @@ int pirrt_mlp_create(pirrt_mlp** out, const pirrt_mlp_config* cfg) {
     return PIRRT_EDEVICE;
   }
   N->device = dev;
-  (void)noalloc_scratch(dev);  // set-up of the no-allocation forward on this device
   N->stream = (hipStream_t)cfg->hip_stream;
   N->in_dim = cfg->in_dim;
   N->max_batch = cfg->max_batch;
-  N->bcap = padded(cfg->max_batch);
+  N->bcap = row_tiles(cfg->max_batch) * kRows;
   N->lr = cfg->lr;
   N->beta1 = cfg->beta1;
   N->beta2 = cfg->beta2;
@@ -553,11 +608,11 @@ int pirrt_mlp_create(pirrt_mlp** out, const pirrt_mlp_config* cfg) {
             malloc_dev(&N->W2b, (int64_t)kHidden * kHidden) && malloc_dev(&N->W2t, (int64_t)kHidden * kHidden) &&
             malloc_dev(&N->w3b, kHidden) &&
             malloc_dev(&N->xin, (int64_t)N->max_batch * N->in_dim) && malloc_dev(&N->yin, N->max_batch) &&
-            malloc_dev(&N->X, bc * kIn) && malloc_dev(&N->Z1, bc * kHidden) && malloc_dev(&N->A1, bc * kHidden) &&
-            malloc_dev(&N->Z2, bc * kHidden) && malloc_dev(&N->A2, bc * kHidden) && malloc_dev(&N->z, bc) &&
-            malloc_dev(&N->dz, bc) && malloc_dev(&N->dZ2, bc * kHidden) && malloc_dev(&N->dZ1, bc * kHidden) &&
-            malloc_dev(&N->dloss, 1) &&
-            malloc_dev(&N->part, std::max<int64_t>((int64_t)kSplitK * kIn * kHidden, (int64_t)kColParts * (kHidden + 1)));
+            malloc_dev(&N->z, bc) && malloc_dev(&N->T.XT, bc * kIn) && malloc_dev(&N->T.A1T, bc * kHidden) &&
+            malloc_dev(&N->T.dZ1T, bc * kHidden) && malloc_dev(&N->T.dZ2T, bc * kHidden) &&
+            malloc_dev(&N->T.colsum, (int64_t)kNetGroups * kColSums) &&
+            malloc_dev(&N->part, (int64_t)kSplits * kGradRows * kHidden);
+  N->T.steps = bc / 16;
   if (ok && hipHostMalloc((void**)&N->hloss, sizeof(float), hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     N->hloss = nullptr;
@@ -630,15 +685,12 @@ int pirrt_mlp_forward(pirrt_mlp* N, int32_t B, const float* x, float* logits, in
   if (rc) return rc;
   if ((rc = check_batch(N, B, x, mem_kind))) return rc;
   if (!logits) return mfail(N, PIRRT_EINVAL, "logits is NULL");
-  const int32_t Bp = padded(B);
-  const float* yd = nullptr;
-  if ((rc = stage_inputs(N, B, Bp, x, nullptr, mem_kind, &yd))) return rc;
-  enqueue_forward(N, Bp, false, N->X, N->A1, N->A2);
-  hipLaunchKernelGGL(k_layer3, dim3(nblocks(Bp)), dim3(kThreads), 0, N->stream, B, Bp, N->A2, N->w3b, N->P, nullptr,
-                     N->z, nullptr, nullptr);
+  const float *xd = nullptr, *yd = nullptr;
+  if ((rc = stage_inputs(N, B, x, nullptr, mem_kind, &xd, &yd))) return rc;
+  const bool dev = mem_kind == PIRRT_MEM_DEVICE;
+  enqueue_forward(N, B, xd, dev ? logits : N->z);
   MHIP(N, hipGetLastError());
-  MHIP(N, hipMemcpyAsync(logits, N->z, sizeof(float) * (size_t)B,
-                         mem_kind == PIRRT_MEM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice, N->stream));
+  if (!dev) MHIP(N, hipMemcpyAsync(logits, N->z, sizeof(float) * (size_t)B, hipMemcpyDeviceToHost, N->stream));
   MHIP(N, hipStreamSynchronize(N->stream));
   return PIRRT_OK;
 }
@@ -646,19 +698,10 @@ int pirrt_mlp_forward(pirrt_mlp* N, int32_t B, const float* x, float* logits, in
 int pirrt_mlp_forward_noalloc(pirrt_mlp* N, int32_t B, const float* x, float* logits) {
   int rc = mguard(N);
   if (rc) return rc;
-  if (B < 1 || B > kNoAllocRows) return mfail(N, PIRRT_EINVAL, "batch size outside 1..PIRRT_MLP_NOALLOC_MAX_BATCH");
+  if (B < 1 || B > PIRRT_MLP_NOALLOC_MAX_BATCH)
+    return mfail(N, PIRRT_EINVAL, "batch size outside 1..PIRRT_MLP_NOALLOC_MAX_BATCH");
   if (!x || !logits) return mfail(N, PIRRT_EINVAL, "x or logits is NULL");
-  uint16_t* base = noalloc_scratch(N->device);
-  if (!base) return mfail(N, PIRRT_EDEVICE, "device address of the no-allocation scratch not available");
-  const int32_t Bp = padded(B);
-  hipStream_t s = N->stream;
-  uint16_t* X = base + kScratchX;
-  uint16_t* A1 = base + kScratchA1;
-  uint16_t* A2 = base + kScratchA2;
-  hipLaunchKernelGGL(k_features, dim3(nblocks((int64_t)Bp * kIn)), dim3(kThreads), 0, s, B, Bp, N->in_dim, x, X);
-  enqueue_forward(N, Bp, false, X, A1, A2);
-  hipLaunchKernelGGL(k_layer3, dim3(nblocks(Bp)), dim3(kThreads), 0, s, B, Bp, A2, N->w3b, N->P, nullptr, logits,
-                     nullptr, nullptr);
+  enqueue_forward(N, B, x, logits);
   MHIP(N, hipGetLastError());
   return PIRRT_OK;
 }
@@ -669,14 +712,12 @@ int pirrt_mlp_gradients(pirrt_mlp* N, int32_t B, const float* x, const float* y,
   if (rc) return rc;
   if ((rc = check_batch(N, B, x, mem_kind))) return rc;
   if (!y) return mfail(N, PIRRT_EINVAL, "y is NULL");
-  const int32_t Bp = padded(B);
-  const float* yd = nullptr;
-  if ((rc = stage_inputs(N, B, Bp, x, y, mem_kind, &yd))) return rc;
-  if ((rc = enqueue_gradients(N, B, Bp, yd))) return rc;
-  if (grads)
-    MHIP(N, hipMemcpyAsync(grads, N->G, sizeof(float) * kNumParams,
-                           mem_kind == PIRRT_MEM_HOST ? hipMemcpyDeviceToHost : hipMemcpyDeviceToDevice, N->stream));
-  MHIP(N, hipMemcpyAsync(N->hloss, N->dloss, sizeof(float), hipMemcpyDeviceToHost, N->stream));
+  const float *xd = nullptr, *yd = nullptr;
+  if ((rc = stage_inputs(N, B, x, y, mem_kind, &xd, &yd))) return rc;
+  const bool dev = mem_kind == PIRRT_MEM_DEVICE;
+  if ((rc = enqueue_training(N, B, xd, yd, dev && grads ? grads : N->G, nullptr))) return rc;
+  if (grads && !dev)
+    MHIP(N, hipMemcpyAsync(grads, N->G, sizeof(float) * kNumParams, hipMemcpyDeviceToHost, N->stream));
   MHIP(N, hipStreamSynchronize(N->stream));
   if (loss) *loss = *N->hloss;
   return PIRRT_OK;
@@ -687,18 +728,12 @@ int pirrt_mlp_train_step(pirrt_mlp* N, int32_t B, const float* x, const float* y
   if (rc) return rc;
   if ((rc = check_batch(N, B, x, mem_kind))) return rc;
   if (!y) return mfail(N, PIRRT_EINVAL, "y is NULL");
-  const int32_t Bp = padded(B);
-  const float* yd = nullptr;
-  if ((rc = stage_inputs(N, B, Bp, x, y, mem_kind, &yd))) return rc;
-  if ((rc = enqueue_gradients(N, B, Bp, yd))) return rc;
+  const float *xd = nullptr, *yd = nullptr;
+  if ((rc = stage_inputs(N, B, x, y, mem_kind, &xd, &yd))) return rc;
   N->t += 1;
-  const float c1 = 1.0f - powf(N->beta1, (float)N->t), c2 = 1.0f - powf(N->beta2, (float)N->t);
-  hipLaunchKernelGGL(k_adam, dim3(nblocks(kNumParams)), dim3(kThreads), 0, N->stream, kNumParams, N->P, N->G, N->m,
-                     N->v, N->lr, N->beta1, N->beta2, N->eps, c1, c2);
-  hipLaunchKernelGGL(k_refresh, dim3(nblocks((int64_t)kIn * kHidden)), dim3(kThreads), 0, N->stream, N->P, N->W1t,
-                     N->W2b, N->W2t, N->w3b);
-  MHIP(N, hipGetLastError());
-  MHIP(N, hipMemcpyAsync(N->hloss, N->dloss, sizeof(float), hipMemcpyDeviceToHost, N->stream));
+  const AdamArgs step{N->m, N->v, N->lr, N->beta1, N->beta2, N->eps, 1.0f - powf(N->beta1, (float)N->t),
+                      1.0f - powf(N->beta2, (float)N->t)};
+  if ((rc = enqueue_training(N, B, xd, yd, nullptr, &step))) return rc;
   MHIP(N, hipStreamSynchronize(N->stream));
   if (loss) *loss = *N->hloss;
   return PIRRT_OK;
