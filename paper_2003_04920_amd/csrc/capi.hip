@@ -712,20 +712,16 @@ int renumber(pirrt_graph* G) {
   return PIRRT_OK;
 }
 
-// Insertion-time policy of the n_new vertices appended after slot n_old, one
-// dependency level at a time (staged rows in brp / bcol / bslot / bcost, the new
-// adjacency built).  insert_root: the slot that becomes a root (g = 0), or -1.
-int insert_levels(pirrt_graph* G, int32_t n_new, int64_t n_old, int32_t insert_root, const int64_t* brp,
+// Insertion-time policy of the n_new vertices appended after slot n_old (staged rows in
+// brp / bcol / bslot / bcost, the new adjacency built).  insert_root: the slot that becomes a
+// root (g = 0), or -1.
+int insert_policy(pirrt_graph* G, int32_t n_new, int64_t n_old, int32_t insert_root, const int64_t* brp,
                   const int32_t* bcol, const float* bcost) {
   hipStream_t s = G->stream;
-  // dcount[0] / dcount[1]: the frontier sizes of alternate levels; dcount[2]: vertices
-  // placed.  Levels go out kLevelsPerCheck at a time (a level past the last one finds
-  // an empty frontier and does nothing), then one read-back tells whether more remain.
-  constexpr int kLevelsPerCheck = 4;
   HIP_OR_FAIL(G, hipMemsetAsync(G->dcount, 0, 3 * sizeof(int32_t), s));
-  launch_pending(n_new, n_old, brp, bcol, G->pending, G->fr0, &G->dcount[0], s);
-  HIP_OR_FAIL(G, hipGetLastError());
-  if (n_new <= kInsertBlockMax) {  // a small batch: every level in one single-workgroup launch
+  if (n_new <= kInsertBlockMax) {  // every dependency level in one single-workgroup launch
+    // dcount[0]: the first frontier's size; dcount[2]: vertices placed
+    launch_pending(n_new, n_old, brp, bcol, G->pending, G->fr0, &G->dcount[0], s);
     launch_insert_block(&G->dcount[0], &G->dcount[2], G->fr0, G->fr1, n_old, n_new, insert_root, brp, bcol, G->bslot,
                         bcost, G->rp, G->col, G->g, G->parent, G->pcost, G->pending, s);
     HIP_OR_FAIL(G, hipGetLastError());
@@ -735,22 +731,23 @@ int insert_levels(pirrt_graph* G, int32_t n_new, int64_t n_old, int32_t insert_r
       return fail_device(G, hipErrorUnknown, "insertion levels did not cover the batch");
     return PIRRT_OK;
   }
-  for (int64_t level = 0;;) {
-    for (int i = 0; i < kLevelsPerCheck; ++i, ++level) {
-      const int cur = (int)(level & 1), nxt = cur ^ 1;
-      HIP_OR_FAIL(G, hipMemsetAsync(&G->dcount[nxt], 0, sizeof(int32_t), s));
-      launch_insert_level(n_new, &G->dcount[cur], &G->dcount[2], cur ? G->fr1 : G->fr0, n_old, insert_root, brp, bcol,
-                          G->bslot, bcost, G->rp, G->col, G->g, G->parent, G->pcost, G->pending,
-                          nxt ? G->fr1 : G->fr0, &G->dcount[nxt], s);
-      HIP_OR_FAIL(G, hipGetLastError());
-    }
-    HIP_OR_FAIL(G, hipMemcpyAsync(G->host->count, G->dcount, 3 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+  // Rounds go out kRoundsPerCheck at a time (one past the fixpoint finds an empty frontier),
+  // then one read-back of the next frontier's size tells whether more remain.
+  constexpr int kRoundsPerCheck = 8;
+  launch_insert_start(n_new, n_old, insert_root, brp, G->bslot, bcost, G->g, G->pending, G->fr0, G->dcount, s);
+  for (int32_t round = 0;;) {
+    for (int i = 0; i < kRoundsPerCheck; ++i, ++round)
+      launch_insert_push(round, n_new, n_old, brp, G->rp, G->col, G->cst, G->g, G->pending,
+                         round % 2 ? G->fr1 : G->fr0, round % 2 ? G->fr0 : G->fr1, G->dcount, s);
+    HIP_OR_FAIL(G, hipGetLastError());
+    HIP_OR_FAIL(G, hipMemcpyAsync(&G->host->count[0], &G->dcount[round % 3], sizeof(int32_t), hipMemcpyDeviceToHost, s));
     HIP_OR_FAIL(G, hipStreamSynchronize(s));
-    if (G->host->count[level & 1] == 0) break;  // the next level's frontier is empty
-    if (G->host->count[2] > n_new || level > (int64_t)n_new + kLevelsPerCheck)
-      return fail_device(G, hipErrorUnknown, "insertion levels exceed the batch");
+    if (G->host->count[0] == 0) break;
+    if (round > (int64_t)n_new + kRoundsPerCheck)
+      return fail_device(G, hipErrorUnknown, "insertion rounds exceed the batch");
   }
-  if (G->host->count[2] != n_new) return fail_device(G, hipErrorUnknown, "insertion levels did not cover the batch");
+  launch_insert_parents(n_new, n_old, insert_root, brp, bcol, G->bslot, bcost, G->g, G->parent, G->pcost, s);
+  HIP_OR_FAIL(G, hipGetLastError());
   return PIRRT_OK;
 }
 
@@ -898,7 +895,7 @@ int insert_rows(pirrt_graph* G, int32_t n_new, const int64_t* row_ptr, const int
   drop_loops(G);
   if (small) HIP_OR_FAIL(G, hipStreamSynchronize(s));
   if (!(small && G->host->count[2] == n_new) &&
-      (rc = insert_levels(G, n_new, n_old, insert_root, brp, bcol, bcost)))
+      (rc = insert_policy(G, n_new, n_old, insert_root, brp, bcol, bcost)))
     return rc;
   if (new_problem) {
     G->renumber_pending = true;
@@ -1031,7 +1028,7 @@ int grow_problems(pirrt_graph* G, int32_t count, const int32_t* problems, const 
   G->nnz += 2 * nnz_b;
   G->adj_version++;
   drop_loops(G);
-  if ((rc = insert_levels(G, tot, n_old, -1, G->brp, G->bcol, G->bcost))) return rc;
+  if ((rc = insert_policy(G, tot, n_old, -1, G->brp, G->bcol, G->bcost))) return rc;
   // final caller ids, bases and host mirrors
   launch_reid(n1, n_old, nblk, dblk, G->dbase, dbase_new, G->prob, G->ext_of, G->slot_of, s);
   HIP_OR_FAIL(G, hipGetLastError());

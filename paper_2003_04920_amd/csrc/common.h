@@ -204,4 +204,31 @@ __device__ __forceinline__ unsigned long long group_bits(unsigned long long ball
   return width == 64 ? ballot : (ballot >> (grp * width)) & ((1ull << width) - 1ull);
 }
 
+// A workgroup's additions to a list in memory.  They gather in LDS and take their places with
+// one atomic: a counter that every wave adds to serves about one wave in 3 ns, whatever the
+// width of the chip.  start and flush are reached by every thread of the workgroup.
+struct PushList {
+  static constexpr int kCap = 1024;
+  int32_t count, place;
+  int32_t item[kCap];
+  __device__ __forceinline__ void start() {
+    if (threadIdx.x == 0) count = 0;
+    __syncthreads();
+  }
+  __device__ __forceinline__ void push(int32_t x, int32_t* out, int32_t* total) {
+    const int32_t i = atomicAdd(&count, 1);
+    if (i < kCap)
+      item[i] = x;
+    else
+      out[atomicAdd(total, 1)] = x;
+  }
+  __device__ __forceinline__ void flush(int32_t* out, int32_t* total) {
+    __syncthreads();
+    const int32_t n = count < kCap ? count : kCap;
+    if (threadIdx.x == 0 && n > 0) place = atomicAdd(total, n);
+    __syncthreads();
+    for (int32_t i = threadIdx.x; i < n; i += blockDim.x) out[place + i] = item[i];
+  }
+};
+
 }  // namespace pirrt

@@ -99,11 +99,15 @@ struct InsertArgs {
   void* scratch;
 };
 hipError_t launch_insert_small(const InsertArgs& a, hipStream_t s);
-void launch_insert_level(int32_t max_size, const int32_t* fsize, int32_t* done, const int32_t* frontier,
-                         int64_t n_old, int32_t insert_root, const int64_t* brp, const int32_t* bcol,
-                         const int32_t* bslot, const float* bcost, const int64_t* rp, const int32_t* col, float* g,
-                         int32_t* parent, float* pcost, int32_t* pending, int32_t* next, int32_t* ncount,
+void launch_insert_start(int32_t n_new, int64_t n_old, int32_t insert_root, const int64_t* brp, const int32_t* bslot,
+                         const float* bcost, float* g, int32_t* stamp, int32_t* frontier, int32_t* count,
                          hipStream_t s);
+void launch_insert_push(int32_t round, int32_t n_new, int64_t n_old, const int64_t* brp, const int64_t* rp,
+                        const int32_t* col, const float* cst, float* g, int32_t* stamp, const int32_t* frontier,
+                        int32_t* next, int32_t* count, hipStream_t s);
+void launch_insert_parents(int32_t n_new, int64_t n_old, int32_t insert_root, const int64_t* brp, const int32_t* bcol,
+                           const int32_t* bslot, const float* bcost, const float* g, int32_t* parent, float* pcost,
+                           hipStream_t s);
 
 // ---- reorder.hip ----
 struct PermuteArgs {
