@@ -23,7 +23,8 @@ constexpr int64_t kMinEdgeCap = 4096;
 constexpr int kGraphIterCounts = 4;  // captured loop bodies of 1, 2, 4 and 8 iterations
 constexpr int64_t kAdjSlack = 4;     // entries past the end of the adjacency arrays (quad loads)
 
-// Pinned host block for small read-backs.
+// Pinned host block for small read-backs; kernels whose result is a few words write it here
+// (a copy back costs 6 to 8 us of a short call).
 struct HostBlock {
   LoopCtl ctl;
   unsigned long long hops;
@@ -33,10 +34,6 @@ struct HostBlock {
 };
 
 // Validation kernels for device-resident inputs of replan / set_policy.
-__global__ void k_check_h(int32_t n, const float* __restrict__ h, int* __restrict__ bad) {
-  int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (v < n && !(h[v] >= 0.0f)) atomicOr(bad, 1);
-}
 
 // parent ids are local to the problem [base, base + len) of each vertex.
 __global__ void k_check_policy(int32_t n, const int32_t* __restrict__ parent, const float* __restrict__ pcost,
@@ -567,7 +564,9 @@ int32_t* walk_tiles(pirrt_graph* G) {
 
 // Copies the policy out in caller order (device outputs are written directly;
 // host outputs go through device staging).  In a batch, parents are local ids.
-int policy_out(pirrt_graph* G, float* g_out, int32_t* parent_out, float* pcost_out, int mem_kind) {
+// report (nullable, pinned): the first problem's state goes there.
+int policy_out(pirrt_graph* G, float* g_out, int32_t* parent_out, float* pcost_out, int mem_kind,
+               ProblemState* report = nullptr) {
   const int32_t n = (int32_t)G->n;
   hipStream_t s = G->stream;
   if (n == 0) return PIRRT_OK;
@@ -576,7 +575,7 @@ int policy_out(pirrt_graph* G, float* g_out, int32_t* parent_out, float* pcost_o
   int32_t* pd = parent_out ? (dev ? parent_out : G->parent2) : nullptr;
   float* cd = pcost_out ? (dev ? pcost_out : G->pcost2) : nullptr;
   launch_policy_to_ext(n, G->slot_of, G->ext_of, problem_map(G), base_map(G), G->g, G->parent, G->pcost, gd, pd,
-                       cd, s);
+                       cd, G->ps, report, s);
   HIP_OR_FAIL(G, hipGetLastError());
   if (!dev) {
     if (g_out) HIP_OR_FAIL(G, hipMemcpyAsync(g_out, G->g2, sizeof(float) * (size_t)n, hipMemcpyDeviceToHost, s));
@@ -853,12 +852,12 @@ int insert_rows(pirrt_graph* G, int32_t n_new, const int64_t* row_ptr, const int
     ia.add = G->add;
     ia.add0 = G->add0;
     ia.dcount = G->dcount;
+    ia.placed = &G->host->count[2];
     ia.g = G->g;
     ia.parent = G->parent;
     ia.pcost = G->pcost;
     ia.scratch = G->rsync + 1;
     HIP_OR_FAIL(G, launch_insert_small(ia, s));
-    HIP_OR_FAIL(G, hipMemcpyAsync(G->host->count, G->dcount, 3 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     std::swap(G->rp, G->rp2);
     std::swap(G->col, G->col2);
     std::swap(G->cst, G->cst2);
@@ -1329,9 +1328,11 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
     ra.lookahead = G->lookahead;
     ra.tree = G->tree;
     HIP_OR_FAIL(G, launch_replan_resident(ra, s));
-    if (out && (out->g || out->parent) && (rc = policy_out(G, out->g, out->parent, nullptr, out->mem_kind)))
-      return rc;
-    HIP_OR_FAIL(G, hipMemcpyAsync(G->hps, G->ps, sizeof(ProblemState), hipMemcpyDeviceToHost, s));
+    if (out && (out->g || out->parent)) {
+      if ((rc = policy_out(G, out->g, out->parent, nullptr, out->mem_kind, G->hps))) return rc;
+    } else {
+      HIP_OR_FAIL(G, hipMemcpyAsync(G->hps, G->ps, sizeof(ProblemState), hipMemcpyDeviceToHost, s));
+    }
     HIP_OR_FAIL(G, hipStreamSynchronize(s));
     const ProblemState& q = G->hps[0];
     if (q.status == 2) return fail_device(G, hipErrorUnknown, "the resident Replan's barrier did not complete");
@@ -1429,9 +1430,12 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
       plan = 1;
     }
   }
-  if (out && (out->g || out->parent) && (rc = policy_out(G, out->g, out->parent, nullptr, out->mem_kind)))
+  const bool reported = P == 1 && out && (out->g || out->parent);
+  if (out && (out->g || out->parent) &&
+      (rc = policy_out(G, out->g, out->parent, nullptr, out->mem_kind, reported ? G->hps : nullptr)))
     return rc;
-  HIP_OR_FAIL(G, hipMemcpyAsync(G->hps, G->ps, sizeof(ProblemState) * (size_t)P, hipMemcpyDeviceToHost, s));
+  if (!reported)
+    HIP_OR_FAIL(G, hipMemcpyAsync(G->hps, G->ps, sizeof(ProblemState) * (size_t)P, hipMemcpyDeviceToHost, s));
   HIP_OR_FAIL(G, hipStreamSynchronize(s));
   int32_t most = 0;
   bool capped = false;
@@ -1590,14 +1594,15 @@ int stage_h(pirrt_graph* G, const float* h, int mem_kind, const float** out) {
     HIP_OR_FAIL(G, hipMemcpyAsync(G->g2, h, sizeof(float) * (size_t)n, hipMemcpyHostToDevice, s));
     hsrc = G->g2;
   } else {
-    HIP_OR_FAIL(G, hipMemsetAsync(G->dflag, 0, sizeof(int32_t), s));
-    hipLaunchKernelGGL(k_check_h, dim3(grid_for(n)), dim3(256), 0, s, n, h, G->dflag);
+    G->host->flag = 0;
+    launch_gather_by_slot(n, G->ext_of, hsrc, G->hbuf, &G->host->flag, s);
     HIP_OR_FAIL(G, hipGetLastError());
-    int32_t bad = 0;
-    if ((rc = read_flag(G, &bad))) return rc;
-    if (bad) return fail(G, PIRRT_EINVAL, "h has a NaN or negative entry");
+    HIP_OR_FAIL(G, hipStreamSynchronize(s));
+    if (G->host->flag) return fail(G, PIRRT_EINVAL, "h has a NaN or negative entry");
+    *out = G->hbuf;
+    return PIRRT_OK;
   }
-  launch_gather_by_slot(n, G->ext_of, hsrc, G->hbuf, s);
+  launch_gather_by_slot(n, G->ext_of, hsrc, G->hbuf, nullptr, s);
   HIP_OR_FAIL(G, hipGetLastError());
   *out = G->hbuf;
   return PIRRT_OK;
@@ -2086,10 +2091,15 @@ int pirrt_promising_count(pirrt_graph* G, int32_t goal, const float* h, int64_t 
       hd = h + first;
     }
   }
-  HIP_OR_FAIL(G, hipMemsetAsync(G->dhops, 0, sizeof(unsigned long long), s));
-  launch_count_promising(first, count, G->hslot[(size_t)goal], G->slot_of, G->g, hd, G->dhops, s);
-  HIP_OR_FAIL(G, hipGetLastError());
-  HIP_OR_FAIL(G, hipMemcpyAsync(&G->host->hops, G->dhops, sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
+  if (count <= kPromisingBlockMax) {
+    launch_count_promising(first, count, G->hslot[(size_t)goal], G->slot_of, G->g, hd, &G->host->hops, s);
+    HIP_OR_FAIL(G, hipGetLastError());
+  } else {
+    HIP_OR_FAIL(G, hipMemsetAsync(G->dhops, 0, sizeof(unsigned long long), s));
+    launch_count_promising(first, count, G->hslot[(size_t)goal], G->slot_of, G->g, hd, G->dhops, s);
+    HIP_OR_FAIL(G, hipGetLastError());
+    HIP_OR_FAIL(G, hipMemcpyAsync(&G->host->hops, G->dhops, sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
+  }
   HIP_OR_FAIL(G, hipStreamSynchronize(s));
   *out = (int64_t)G->host->hops;
   return PIRRT_OK;

@@ -207,7 +207,8 @@ constexpr int kPer = kInsertBlockMax / kPolThreads;
 __global__ void __launch_bounds__(kPolThreads) k_insert_policy(int32_t n_new, int64_t n_old, int32_t insert_root,
                                                               const uint4* __restrict__ base,
                                                               const InsertEdge* __restrict__ inner,
-                                                              int32_t* __restrict__ dcount, float* __restrict__ g,
+                                                              const int32_t* __restrict__ dcount,
+                                                              int32_t* __restrict__ placed, float* __restrict__ g,
                                                               int32_t* __restrict__ parent,
                                                               float* __restrict__ pcost) {
   extern __shared__ uint32_t lds[];
@@ -220,7 +221,7 @@ __global__ void __launch_bounds__(kPolThreads) k_insert_policy(int32_t n_new, in
   const int t = threadIdx.x, lane = t & (kWave - 1), wid = t / kWave;
   const int32_t E = dcount[0];
   if (E > kInsertInner) {  // too many inner edges: the host takes the level path
-    if (t == 0) dcount[2] = 0;
+    if (t == 0) *placed = 0;
     return;
   }
   for (int i = t; i < kInsertBlockMax; i += kPolThreads) off[i] = 0;
@@ -315,7 +316,7 @@ __global__ void __launch_bounds__(kPolThreads) k_insert_policy(int32_t n_new, in
     parent[n_old + i] = found ? (int32_t)m.w : -1;
     pcost[n_old + i] = found ? __uint_as_float(m.z) : 0.0f;
   }
-  if (t == 0) dcount[2] = n_new;
+  if (t == 0) *placed = n_new;
 }
 
 }  // namespace
@@ -338,7 +339,7 @@ hipError_t launch_insert_small(const InsertArgs& a, hipStream_t s) {
                                            (int)lds);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_insert_policy, dim3(1), dim3(kPolThreads), lds, s, a.n_new, a.n_old, a.insert_root, base, inner,
-                     a.dcount, a.g, a.parent, a.pcost);
+                     a.dcount, a.placed, a.g, a.parent, a.pcost);
   return hipGetLastError();
 }
 

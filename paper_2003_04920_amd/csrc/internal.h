@@ -93,6 +93,7 @@ struct InsertArgs {
   int32_t* add;
   int32_t* add0;
   int32_t* dcount;
+  int32_t* placed;  // pinned host memory: n_new, or 0 if the level path must do the policy
   float* g;
   int32_t* parent;
   float* pcost;
@@ -163,12 +164,16 @@ void launch_cluster_order(int32_t n, const int64_t* rp, const int32_t* col, cons
 void launch_append_unvisited(int32_t n, const int32_t* visited, int32_t* order, const int32_t* prob, int32_t* pcnt,
                              hipStream_t s);
 void launch_permute(const PermuteArgs& a, hipStream_t s);
-void launch_gather_by_slot(int32_t n, const int32_t* ext_of, const float* src_ext, float* dst_slot, hipStream_t s);
+// bad (nullable, pinned host memory): set to 1 if a value is negative or NaN.
+void launch_gather_by_slot(int32_t n, const int32_t* ext_of, const float* src_ext, float* dst_slot, int32_t* bad,
+                           hipStream_t s);
+// report (nullable, pinned host memory): *ps goes there.
 // prob/base (nullable): parents are reported relative to the first id of the
 // vertex's problem.
 void launch_policy_to_ext(int32_t n, const int32_t* slot_of, const int32_t* ext_of, const int32_t* prob,
                           const int64_t* base, const float* g, const int32_t* parent, const float* pcost,
-                          float* g_ext, int32_t* parent_ext, float* pcost_ext, hipStream_t s);
+                          float* g_ext, int32_t* parent_ext, float* pcost_ext, const ProblemState* ps,
+                          ProblemState* report, hipStream_t s);
 void launch_policy_from_ext(int32_t n, const int32_t* slot_of, const int32_t* prob, const int64_t* base,
                             const float* g_ext, const int32_t* parent_ext, const float* pcost_ext, float* g,
                             int32_t* parent, float* pcost, hipStream_t s);
@@ -354,6 +359,9 @@ void launch_mark(const StepArgs& a, int variant, hipStream_t s);
 void launch_domain_list(const StepArgs& a, hipStream_t s);
 // out += number of ids in [first, first + count) with fl(g + h) < g(goal); h is indexed
 // from `first` (nullable).
+// Counts of at most kPromisingBlockMax ids are written to *out (pinned host memory); larger
+// ones are added to it (device memory, cleared before).
+constexpr int64_t kPromisingBlockMax = 16384;
 void launch_count_promising(int64_t first, int64_t count, int32_t goal_slot, const int32_t* slot_of, const float* g,
                             const float* h, unsigned long long* out, hipStream_t s);
 void launch_improve(const StepArgs& a, int variant, hipStream_t s);

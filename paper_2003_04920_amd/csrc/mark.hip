@@ -492,11 +492,38 @@ __global__ void __launch_bounds__(kThreads) k_count_promising(int64_t first, int
   if ((threadIdx.x & (kWave - 1)) == 0 && b) atomicAdd(out, (unsigned long long)__popcll(b));
 }
 
+// The same in one workgroup, the count written and not added: nothing to clear, and *out may
+// be host memory (21 us a call of 100 to 1,000 ids through a counter and a copy, 15 so).
+constexpr int kCountThreads = 1024;
+
+__global__ void __launch_bounds__(kCountThreads) k_count_promising_block(int64_t first, int32_t count,
+                                                                        int32_t goal_slot,
+                                                                        const int32_t* __restrict__ slot_of,
+                                                                        const float* __restrict__ g,
+                                                                        const float* __restrict__ h,
+                                                                        unsigned long long* __restrict__ out) {
+  __shared__ int32_t sum;
+  if (threadIdx.x == 0) sum = 0;
+  __syncthreads();
+  const float gg = g[goal_slot];
+  int32_t mine = 0;
+  for (int32_t i = threadIdx.x; i < count; i += kCountThreads)
+    mine += add_rn(g[slot_of[first + i]], h ? h[i] : 0.0f) < gg;
+#pragma unroll
+  for (int off = kWave / 2; off > 0; off >>= 1) mine += __shfl_xor(mine, off, kWave);
+  if ((threadIdx.x & (kWave - 1)) == 0) atomicAdd(&sum, mine);
+  __syncthreads();
+  if (threadIdx.x == 0) *out = (unsigned long long)sum;
+}
+
 }  // namespace
 
 void launch_count_promising(int64_t first, int64_t count, int32_t goal_slot, const int32_t* slot_of, const float* g,
                             const float* h, unsigned long long* out, hipStream_t s) {
-  if (count > 0)
+  if (count > 0 && count <= kPromisingBlockMax)
+    hipLaunchKernelGGL(k_count_promising_block, dim3(1), dim3(kCountThreads), 0, s, first, (int32_t)count, goal_slot,
+                       slot_of, g, h, out);
+  else if (count > 0)
     hipLaunchKernelGGL(k_count_promising, dim3((unsigned)((count + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
                        first, count, goal_slot, slot_of, g, h, out);
 }

@@ -382,9 +382,12 @@ __global__ void __launch_bounds__(kThreads) k_permute_vertices(int32_t n, const 
 
 __global__ void __launch_bounds__(kThreads) k_gather_by_slot(int32_t n, const int32_t* __restrict__ ext_of,
                                                             const float* __restrict__ src_ext,
-                                                            float* __restrict__ dst_slot) {
+                                                            float* __restrict__ dst_slot, int32_t* __restrict__ bad) {
   int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s < n) dst_slot[s] = src_ext[ext_of[s]];
+  if (s >= n) return;
+  const float x = src_ext[ext_of[s]];
+  dst_slot[s] = x;
+  if (bad && !(x >= 0.0f)) *bad = 1;
 }
 
 __global__ void __launch_bounds__(kThreads) k_policy_to_ext(int32_t n, const int32_t* __restrict__ slot_of,
@@ -395,8 +398,11 @@ __global__ void __launch_bounds__(kThreads) k_policy_to_ext(int32_t n, const int
                                                            const int32_t* __restrict__ parent,
                                                            const float* __restrict__ pcost, float* __restrict__ g_ext,
                                                            int32_t* __restrict__ parent_ext,
-                                                           float* __restrict__ pcost_ext) {
+                                                           float* __restrict__ pcost_ext,
+                                                           const ProblemState* __restrict__ ps,
+                                                           ProblemState* __restrict__ report) {
   int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (report && e == 0) *report = *ps;
   if (e >= n) return;
   const int32_t s = slot_of[e];
   if (g_ext) g_ext[e] = g[s];
@@ -507,15 +513,18 @@ void launch_permute(const PermuteArgs& a, hipStream_t s) {
                      a.parent, a.pcost, a.ext_of, a.g2, a.parent2, a.pcost2, a.ext2, a.slot_of);
 }
 
-void launch_gather_by_slot(int32_t n, const int32_t* ext_of, const float* src_ext, float* dst_slot, hipStream_t s) {
-  hipLaunchKernelGGL(k_gather_by_slot, dim3(blocks_for(n)), dim3(kThreads), 0, s, n, ext_of, src_ext, dst_slot);
+void launch_gather_by_slot(int32_t n, const int32_t* ext_of, const float* src_ext, float* dst_slot, int32_t* bad,
+                           hipStream_t s) {
+  hipLaunchKernelGGL(k_gather_by_slot, dim3(blocks_for(n)), dim3(kThreads), 0, s, n, ext_of, src_ext, dst_slot,
+                     bad);
 }
 
 void launch_policy_to_ext(int32_t n, const int32_t* slot_of, const int32_t* ext_of, const int32_t* prob,
                           const int64_t* base, const float* g, const int32_t* parent, const float* pcost,
-                          float* g_ext, int32_t* parent_ext, float* pcost_ext, hipStream_t s) {
+                          float* g_ext, int32_t* parent_ext, float* pcost_ext, const ProblemState* ps,
+                          ProblemState* report, hipStream_t s) {
   hipLaunchKernelGGL(k_policy_to_ext, dim3(blocks_for(n)), dim3(kThreads), 0, s, n, slot_of, ext_of, prob, base, g,
-                     parent, pcost, g_ext, parent_ext, pcost_ext);
+                     parent, pcost, g_ext, parent_ext, pcost_ext, ps, report);
 }
 
 void launch_policy_from_ext(int32_t n, const int32_t* slot_of, const int32_t* prob, const int64_t* base,

@@ -57,41 +57,79 @@ __device__ __forceinline__ void philox(uint32_t c0, uint32_t c1, uint32_t c2, ui
   out[3] = c3;
 }
 
-// Candidates k0 .. k0 + T - 1: coordinates into cbuf, free flag into flag.
+// Candidates k0 .. k0 + T - 1: coordinates into cbuf, free flag into flag, each workgroup's
+// free ones into freed.
 template <int D>
 __global__ void __launch_bounds__(kThreads) k_candidates(int64_t T, uint64_t k0, uint64_t seed, uint32_t stream,
                                                          ObsView ob, double* __restrict__ cbuf,
-                                                         int32_t* __restrict__ flag) {
+                                                         int32_t* __restrict__ flag, int32_t* __restrict__ freed) {
   __shared__ NearObstacles<D> spheres;
   spheres.load(ob);
   __syncthreads();
   const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (t >= T) return;
-  const uint64_t k = k0 + (uint64_t)t;
-  uint32_t w[8];
-  philox((uint32_t)k, (uint32_t)(k >> 32), stream, 0u, (uint32_t)seed, (uint32_t)(seed >> 32), w);
-  if (D > 4) philox((uint32_t)k, (uint32_t)(k >> 32), stream, 1u, (uint32_t)seed, (uint32_t)(seed >> 32), w + 4);
-  double x[D];
+  int free_one = 0;
+  if (t < T) {
+    const uint64_t k = k0 + (uint64_t)t;
+    uint32_t w[8];
+    philox((uint32_t)k, (uint32_t)(k >> 32), stream, 0u, (uint32_t)seed, (uint32_t)(seed >> 32), w);
+    if (D > 4) philox((uint32_t)k, (uint32_t)(k >> 32), stream, 1u, (uint32_t)seed, (uint32_t)(seed >> 32), w + 4);
+    double x[D];
 #pragma unroll
-  for (int i = 0; i < D; ++i) x[i] = (double)(w[i] >> 8) * (1.0 / 16777216.0);
+    for (int i = 0; i < D; ++i) x[i] = (double)(w[i] >> 8) * (1.0 / 16777216.0);
 #pragma unroll
-  for (int i = 0; i < D; ++i) cbuf[t * D + i] = x[i];
-  flag[t] = spheres.point_blocked(x, ob) ? 0 : 1;
+    for (int i = 0; i < D; ++i) cbuf[t * D + i] = x[i];
+    free_one = spheres.point_blocked(x, ob) ? 0 : 1;
+    flag[t] = free_one;
+  }
+  const int n = __syncthreads_count(free_one);
+  if (threadIdx.x == 0) freed[blockIdx.x] = n;
 }
 
-// Appends the free candidates whose rank (pos) is below `need`; records one past
-// the candidate of rank need - 1 in *last.
+// Appends the free candidates whose rank is below `need`.  result (pinned host memory):
+// [0] the free candidates of all T, [1] one past the candidate of rank need - 1.
+//
+// Bound by launches: ranks were a three-launch scan over the flags, a counter to clear and
+// two copies back, 48 us a call of 100 to 1,000 samples; each workgroup adds the counts before
+// it by itself now: 18.  That is quadratic in the workgroups, so past kTakeSums of them
+// `before` is their scan.
+constexpr int64_t kTakeSums = 2048;
+
 template <int D>
 __global__ void __launch_bounds__(kThreads) k_take(int64_t T, int64_t need, const double* __restrict__ cbuf,
-                                                   const int32_t* __restrict__ flag, const int64_t* __restrict__ pos,
-                                                   double* __restrict__ pts, int64_t* __restrict__ last) {
+                                                   const int32_t* __restrict__ flag,
+                                                   const int32_t* __restrict__ freed,
+                                                   const int64_t* __restrict__ before, double* __restrict__ pts,
+                                                   int64_t* __restrict__ result) {
+  __shared__ int64_t wave_sum[kThreads / kWave];
+  __shared__ int wave_free[kThreads / kWave];
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  int64_t sum = 0;
+  if (!before) {
+    for (int64_t i = threadIdx.x; i < blockIdx.x; i += kThreads) sum += freed[i];
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, kWave);
+  }
   const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (t >= T || !flag[t]) return;
-  const int64_t p = pos[t];
-  if (p >= need) return;
+  const bool mine = t < T && flag[t];
+  const unsigned long long bits = __ballot(mine);
+  if (lane == 0) {
+    wave_sum[wave] = sum;
+    wave_free[wave] = __popcll(bits);
+  }
+  __syncthreads();
+  int64_t p = before ? before[blockIdx.x] : 0;
+  int rank = __popcll(bits & ((1ull << lane) - 1)), all = 0;
+  for (int w = 0; w < kThreads / kWave; ++w) {
+    if (!before) p += wave_sum[w];
+    rank += w < wave ? wave_free[w] : 0;
+    all += wave_free[w];
+  }
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) result[0] = p + all;
+  p += rank;
+  if (!mine || p >= need) return;
 #pragma unroll
   for (int i = 0; i < D; ++i) pts[p * D + i] = cbuf[t * D + i];
-  if (p == need - 1) *last = t + 1;
+  if (p == need - 1) result[1] = t + 1;
 }
 
 // Radius search over a grid of (256 new vertices) x (kChunk earlier points).
@@ -284,6 +322,8 @@ inline unsigned blocks(int64_t n) { return (unsigned)((n + kThreads - 1) / kThre
 
 }  // namespace
 
+constexpr int kHostWords = 4;
+
 struct pirrt_rrg {
   int device = 0;
   hipStream_t stream = nullptr;
@@ -297,6 +337,7 @@ struct pirrt_rrg {
   // scratch (grown on demand)
   double* cbuf = nullptr;
   int32_t* flag = nullptr;
+  int32_t* freed = nullptr;
   int64_t* pos = nullptr;
   int64_t cand_cap_s = 0;  // sampler candidates
   int32_t* cnt = nullptr;
@@ -338,9 +379,8 @@ struct pirrt_rrg {
   int32_t* lsel = nullptr;
   void* scan = nullptr;
   size_t scan_bytes = 0;
-  int64_t* dword = nullptr;
   int32_t* dflag = nullptr;
-  int64_t* host = nullptr;  // pinned, 4 words
+  int64_t* host = nullptr;  // pinned, kHostWords words: the kernels write small results there
   bool poisoned = false;
   std::string err;
 };
@@ -427,13 +467,13 @@ ObsView obs_view(const pirrt_rrg* R) { return ObsView{R->nobs, R->okind, R->ocen
 template <int D>
 void launch_candidates(pirrt_rrg* R, int64_t T, uint64_t k0, uint64_t seed, uint32_t stream) {
   hipLaunchKernelGGL(k_candidates<D>, dim3(blocks(T)), dim3(kThreads), 0, R->stream, T, k0, seed, stream,
-                     obs_view(R), R->cbuf, R->flag);
+                     obs_view(R), R->cbuf, R->flag, R->freed);
 }
 
 template <int D>
 void launch_take(pirrt_rrg* R, int64_t T, int64_t need, double* dst) {
-  hipLaunchKernelGGL(k_take<D>, dim3(blocks(T)), dim3(kThreads), 0, R->stream, T, need, R->cbuf, R->flag, R->pos, dst,
-                     R->dword);
+  hipLaunchKernelGGL(k_take<D>, dim3(blocks(T)), dim3(kThreads), 0, R->stream, T, need, R->cbuf, R->flag, R->freed,
+                     (int64_t)blocks(T) > kTakeSums ? R->pos : nullptr, dst, R->host);
 }
 
 template <int D>
@@ -523,6 +563,9 @@ int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direc
   a.obs = obs_view(R);
   a.rec = R->rec;
   a.state = R->sstate;
+  static_assert(sizeof(SearchState) <= sizeof(int64_t) * kHostWords, "R->host holds it");
+  SearchState* st = reinterpret_cast<SearchState*>(R->host);
+  a.report = st;
   // enough workgroups to fill the chip: a row's earlier points are cut into chunks, each
   // with its own candidate list
   const int64_t groups = (rows + (rows >= kSearchWideRows ? 511 : 127)) / (rows >= kSearchWideRows ? 512 : 128);
@@ -571,8 +614,6 @@ int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direc
     launch_search_rows(a, base, own ? R->col_cap : direct->capacity, rp, own ? R->col : direct->col,
                        own ? R->cost : direct->cost, R->soff, R->scan, s);
     RHIP(R, hipGetLastError());
-    SearchState* st = reinterpret_cast<SearchState*>(R->host);
-    RHIP(R, hipMemcpyAsync(st, R->sstate, sizeof(SearchState), hipMemcpyDeviceToHost, s));
     RHIP(R, hipStreamSynchronize(s));
     if (st->outside) {
       R->outside = true;
@@ -693,28 +734,28 @@ int draw_free(pirrt_rrg* R, uint64_t seed, uint32_t stream_id, uint64_t* counter
   int64_t need = count, got_all = 0, tried = 0;
   while (need > 0) {
     const int64_t T = need + need / 2 + 4096;
+    const int64_t groups = blocks(T);
     if (T > R->cand_cap_s) {
-      rfree(R->cbuf); rfree(R->flag); rfree(R->pos);
+      rfree(R->cbuf); rfree(R->flag); rfree(R->freed); rfree(R->pos);
       R->cand_cap_s = 0;
-      if (!ralloc(&R->cbuf, T * d) || !ralloc(&R->flag, T) || !ralloc(&R->pos, T + 1))
+      if (!ralloc(&R->cbuf, T * d) || !ralloc(&R->flag, T) || !ralloc(&R->freed, groups) || !ralloc(&R->pos, groups + 1))
         return rfail(R, PIRRT_ENOMEM, "device allocation of sampler candidates failed");
       R->cand_cap_s = T;
     }
-    if ((rc = ensure_scan(R, T + 1))) return rc;
 #define CANDS(D) launch_candidates<D>(R, T, k, seed, stream_id)
     PIRRT_BY_DIM(d, CANDS);
 #undef CANDS
     RHIP(R, hipGetLastError());
-    scan_i32_to_i64(R->flag, T, R->pos, R->scan, R->stream);
-    RHIP(R, hipGetLastError());
-    RHIP(R, hipMemsetAsync(R->dword, 0, sizeof(int64_t), R->stream));
+    if (groups > kTakeSums) {
+      if ((rc = ensure_scan(R, groups + 1))) return rc;
+      scan_i32_to_i64(R->freed, groups, R->pos, R->scan, R->stream);
+      RHIP(R, hipGetLastError());
+    }
     double* out = dst + got_all * d;
 #define TAKE(D) launch_take<D>(R, T, need, out)
     PIRRT_BY_DIM(d, TAKE);
 #undef TAKE
     RHIP(R, hipGetLastError());
-    RHIP(R, hipMemcpyAsync(R->host, R->pos + T, sizeof(int64_t), hipMemcpyDeviceToHost, R->stream));
-    RHIP(R, hipMemcpyAsync(R->host + 1, R->dword, sizeof(int64_t), hipMemcpyDeviceToHost, R->stream));
     RHIP(R, hipStreamSynchronize(R->stream));
     const int64_t got = R->host[0];
     if (got >= need) {
@@ -735,9 +776,9 @@ int draw_free(pirrt_rrg* R, uint64_t seed, uint32_t stream_id, uint64_t* counter
 }
 
 void release(pirrt_rrg* R) {
-  rfree(R->okind); rfree(R->ocentre); rfree(R->osize); rfree(R->pts); rfree(R->cbuf); rfree(R->flag); rfree(R->pos);
-  rfree(R->cnt); rfree(R->cptr); rfree(R->cand_u); rfree(R->cand_v); rfree(R->keep); rfree(R->kpos); rfree(R->ccost);
-  rfree(R->rp); rfree(R->col); rfree(R->cost); rfree(R->hbuf); rfree(R->dword); rfree(R->dflag);
+  rfree(R->okind); rfree(R->ocentre); rfree(R->osize); rfree(R->pts); rfree(R->cbuf); rfree(R->flag); rfree(R->freed);
+  rfree(R->pos); rfree(R->cnt); rfree(R->cptr); rfree(R->cand_u); rfree(R->cand_v); rfree(R->keep); rfree(R->kpos); rfree(R->ccost);
+  rfree(R->rp); rfree(R->col); rfree(R->cost); rfree(R->hbuf); rfree(R->dflag);
   rfree(R->rec); rfree(R->scand); rfree(R->sccost); rfree(R->scnt); rfree(R->sdeg); rfree(R->soff); rfree(R->sstate);
   rfree(R->lpts); rfree(R->lfeat); rfree(R->llogit); rfree(R->lenc); rfree(R->lflag); rfree(R->lsel);
   if (R->scan) (void)hipFree(R->scan);
@@ -795,8 +836,8 @@ int pirrt_rrg_create(pirrt_rrg** out, const pirrt_rrg_config* cfg) {
   R->d = d;
   R->nobs = m;
   bool ok = ralloc(&R->okind, m) && ralloc(&R->ocentre, (int64_t)m * d) && ralloc(&R->osize, (int64_t)m * d) &&
-            ralloc(&R->dword, 1) && ralloc(&R->dflag, 1);
-  if (ok && hipHostMalloc((void**)&R->host, 4 * sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {
+            ralloc(&R->dflag, 1);
+  if (ok && hipHostMalloc((void**)&R->host, kHostWords * sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     R->host = nullptr;
     ok = false;

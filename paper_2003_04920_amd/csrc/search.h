@@ -39,6 +39,7 @@ struct SearchArgs {
   float* ccost;           // [rows][nch * cap] costs of the finished rows
   int32_t* deg;           // [rows] entries of the finished rows
   SearchState* state;
+  SearchState* report;    // pinned host memory: *state at the end
 };
 
 // Packs points [first, n) and clears the state's counters.
@@ -49,7 +50,7 @@ void launch_search_pack(int d, int64_t first, int64_t n, const double* pts, uint
 void launch_search(const SearchArgs& a, hipStream_t s);
 // The finished rows of a slab into CSR: row_ptr[row0 + i], col / cost from entry `base`
 // on (written only when the total fits `capacity`; either may be NULL), the total into
-// state->nnz.  off: rows + 1 int64 of scratch, scan: scan scratch for rows.
+// report->nnz.  off: rows + 1 int64 of scratch, scan: scan scratch for rows.
 void launch_search_rows(const SearchArgs& a, int64_t base, int64_t capacity, int64_t* row_ptr, int32_t* col,
                         float* cost, int64_t* off, void* scan, hipStream_t s);
 

@@ -315,9 +315,15 @@ __global__ void __launch_bounds__(kThreads) k_search_rows(int32_t rows, int32_t 
                                                           const float* __restrict__ ccost, int64_t base,
                                                           int64_t capacity, int64_t* __restrict__ rp,
                                                           int32_t* __restrict__ col, float* __restrict__ cost,
-                                                          SearchState* __restrict__ state) {
+                                                          const SearchState* __restrict__ state,
+                                                          SearchState* __restrict__ report) {
   __shared__ int64_t start[kCsrRows + 1];
   __shared__ int64_t part[2][kThreads / kWave];
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    report->outside = state->outside;
+    report->most = state->most;
+    report->listed = state->listed;
+  }
   if (state->outside || state->most || state->listed) return;
   const int32_t first = blockIdx.x * kCsrRows;
   const int32_t last = first + kCsrRows < rows ? first + kCsrRows : rows;
@@ -358,7 +364,7 @@ __global__ void __launch_bounds__(kThreads) k_search_rows(int32_t rows, int32_t 
     }
   }
   __syncthreads();
-  if (blockIdx.x == 0 && threadIdx.x == 0) state->nnz = base + total;
+  if (blockIdx.x == 0 && threadIdx.x == 0) report->nnz = base + total;
   if (base + total > capacity) return;
   if (threadIdx.x < last - first) rp[first + threadIdx.x] = base + start[threadIdx.x];
   if (last == rows && threadIdx.x == 0) rp[rows] = base + total;
@@ -433,7 +439,8 @@ void launch_search_rows(const SearchArgs& a, int64_t base, int64_t capacity, int
     offs = off;
   }
   hipLaunchKernelGGL(k_search_rows, dim3(blocks_for(a.rows, kCsrRows)), dim3(kThreads), 0, s, a.rows, a.nch * a.cap,
-                     a.deg, offs, a.cand, a.ccost, base, capacity, row_ptr + a.row0, col, cost, a.state);
+                     a.deg, offs, a.cand, a.ccost, base, capacity, row_ptr + a.row0, col, cost, a.state,
+                     a.report);
 }
 
 }  // namespace pirrt
