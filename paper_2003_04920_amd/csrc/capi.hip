@@ -747,6 +747,7 @@ int insert_policy(pirrt_graph* G, int32_t n_new, int64_t n_old, int32_t insert_r
   }
   launch_insert_parents(n_new, n_old, insert_root, brp, bcol, G->bslot, bcost, G->g, G->parent, G->pcost, s);
   HIP_OR_FAIL(G, hipGetLastError());
+  HIP_OR_FAIL(G, hipStreamSynchronize(s));  // the rows may be the caller's device arrays
   return PIRRT_OK;
 }
 
