@@ -11,6 +11,7 @@
 #include <string>
 #include <vector>
 
+#include "arena.h"
 #include "internal.h"
 #include "pirrt.h"
 
@@ -67,15 +68,17 @@ struct LoopKey {
 }  // namespace
 
 // Device memory source of a handle: the caller's allocator callbacks (called with the
-// handle's device current) or hipMalloc / hipFree.
+// handle's device current) or the handle's arena.
 struct DevAlloc {
   void* (*alloc)(size_t bytes, void* ctx) = nullptr;
   void (*free)(void* ptr, void* ctx) = nullptr;
   void* ctx = nullptr;
+  Arena* arena = nullptr;
 };
 
 struct pirrt_graph {
   DevAlloc A;
+  Arena arena;  // (unused with the caller's callbacks)
   int device = 0;
   hipStream_t stream = nullptr;
   hipStream_t cap_stream = nullptr;  // private stream used only to capture loop bodies
@@ -250,22 +253,14 @@ int fail_device(pirrt_graph* G, hipError_t e, const char* what) {
     if (e_ != hipSuccess) return fail_device(G, e_, #expr); \
   } while (0)
 
-void* raw_alloc(const DevAlloc& A, size_t bytes) {
-  if (A.alloc) return A.alloc(bytes, A.ctx);
-  void* p = nullptr;
-  if (hipMalloc(&p, bytes) != hipSuccess) {
-    (void)hipGetLastError();
-    return nullptr;
-  }
-  return p;
-}
+void* raw_alloc(const DevAlloc& A, size_t bytes) { return A.alloc ? A.alloc(bytes, A.ctx) : A.arena->alloc(bytes); }
 
 void raw_free(const DevAlloc& A, void* p) {
   if (!p) return;
   if (A.free)
     A.free(p, A.ctx);
   else
-    (void)hipFree(p);
+    A.arena->free(p);
 }
 
 template <class T>
@@ -409,7 +404,8 @@ int ensure_pcap(pirrt_graph* G, int64_t need) {
     return fail(G, PIRRT_ENOMEM, "allocation of per-problem state failed");
   }
   if (G->nroots > 0)
-    HIP_OR_FAIL(G, hipMemcpy(roots, G->droots, sizeof(int32_t) * (size_t)G->nroots, hipMemcpyDeviceToDevice));
+    HIP_OR_FAIL(G, hipMemcpyAsync(roots, G->droots, sizeof(int32_t) * (size_t)G->nroots, hipMemcpyDeviceToDevice,
+                                  G->stream));
   dfree(G->A, G->ps); dfree(G->A, G->ctr); dfree(G->A, G->pscratch); dfree(G->A, G->droots); dfree(G->A, G->pstart);
   if (G->hps) (void)hipHostFree(G->hps);
   G->ps = ps; G->ctr = ctr; G->pscratch = scr; G->droots = roots; G->hps = hps; G->pstart = pst;
@@ -527,6 +523,7 @@ void release_all(pirrt_graph* G) {
   G->hps = nullptr;
   raw_free(G->A, G->scan_scratch);
   G->scan_scratch = nullptr;
+  G->arena.release();
   if (G->host) (void)hipHostFree(G->host);
   G->host = nullptr;
   for (auto& e : G->ev)
@@ -1710,6 +1707,7 @@ pirrt_graph* new_graph(const pirrt_config* cfg, int* rc_out) {
   G->A.alloc = c.alloc;
   G->A.free = c.free;
   G->A.ctx = c.alloc_ctx;
+  G->A.arena = &G->arena;
   int dev = c.device;
   if (dev < 0) {
     if (hipGetDevice(&dev) != hipSuccess) {
@@ -1760,7 +1758,7 @@ pirrt_graph* new_graph(const pirrt_config* cfg, int* rc_out) {
     G->cap_stream = nullptr;
     ok = false;
   }
-  if (ok && hipMemset(G->ctl, 0, sizeof(LoopCtl)) != hipSuccess) {
+  if (ok && hipMemsetAsync(G->ctl, 0, sizeof(LoopCtl), G->stream) != hipSuccess) {
     (void)hipGetLastError();
     ok = false;
   }

@@ -24,6 +24,7 @@
 #include <string>
 #include <vector>
 
+#include "arena.h"
 #include "geom.h"
 #include "internal.h"
 #include "pirrt.h"
@@ -325,6 +326,7 @@ inline unsigned blocks(int64_t n) { return (unsigned)((n + kThreads - 1) / kThre
 constexpr int kHostWords = 4;
 
 struct pirrt_rrg {
+  Arena arena;
   int device = 0;
   hipStream_t stream = nullptr;
   int d = 0;
@@ -407,20 +409,14 @@ int rdev(pirrt_rrg* R, hipError_t e, const char* what) {
   } while (0)
 
 template <class T>
-bool ralloc(T** p, int64_t count) {
-  *p = nullptr;
-  if (count <= 0) count = 1;
-  if (hipMalloc((void**)p, sizeof(T) * (size_t)count) != hipSuccess) {
-    (void)hipGetLastError();
-    *p = nullptr;
-    return false;
-  }
-  return true;
+bool ralloc(pirrt_rrg* R, T** p, int64_t count) {
+  *p = static_cast<T*>(R->arena.alloc(sizeof(T) * (size_t)(count > 0 ? count : 1)));
+  return *p != nullptr;
 }
 
 template <class T>
-void rfree(T*& p) {
-  if (p) (void)hipFree(p);
+void rfree(pirrt_rrg* R, T*& p) {
+  R->arena.free(p);
   p = nullptr;
 }
 
@@ -439,10 +435,10 @@ int grow(pirrt_rrg* R, T** p, int64_t* cap, int64_t need, int64_t keep) {
   int64_t c = *cap + *cap / 2;
   if (c < need) c = need;
   T* q = nullptr;
-  if (!ralloc(&q, c)) return rfail(R, PIRRT_ENOMEM, "device allocation failed");
+  if (!ralloc(R, &q, c)) return rfail(R, PIRRT_ENOMEM, "device allocation failed");
   if (keep > 0) RHIP(R, hipMemcpyAsync(q, *p, sizeof(T) * (size_t)keep, hipMemcpyDeviceToDevice, R->stream));
   RHIP(R, hipStreamSynchronize(R->stream));
-  rfree(*p);
+  rfree(R, *p);
   *p = q;
   *cap = c;
   return PIRRT_OK;
@@ -451,12 +447,9 @@ int grow(pirrt_rrg* R, T** p, int64_t* cap, int64_t need, int64_t keep) {
 int ensure_scan(pirrt_rrg* R, int64_t n) {
   const size_t need = scan_scratch_bytes(n);
   if (need <= R->scan_bytes) return PIRRT_OK;
-  void* p = nullptr;
-  if (hipMalloc(&p, need) != hipSuccess) {
-    (void)hipGetLastError();
-    return rfail(R, PIRRT_ENOMEM, "device allocation of scan scratch failed");
-  }
-  if (R->scan) (void)hipFree(R->scan);
+  void* p = R->arena.alloc(need);
+  if (!p) return rfail(R, PIRRT_ENOMEM, "device allocation of scan scratch failed");
+  R->arena.free(R->scan);
   R->scan = p;
   R->scan_bytes = need;
   return PIRRT_OK;
@@ -546,7 +539,7 @@ int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direc
   *done = *wrote = false;
   if (R->outside) return PIRRT_OK;
   if (!R->sstate) {
-    if (!ralloc(&R->sstate, 1)) return rfail(R, PIRRT_ENOMEM, "device allocation of the search state failed");
+    if (!ralloc(R, &R->sstate, 1)) return rfail(R, PIRRT_ENOMEM, "device allocation of the search state failed");
     RHIP(R, hipMemsetAsync(R->sstate, 0, sizeof(SearchState), s));
   }
   if (R->n + kSearchPad > R->rec_cap) {
@@ -581,22 +574,22 @@ int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direc
     a.row0 = row0;
     a.rows = (int32_t)slab;
     if (slab * stride > R->scand_cap) {
-      rfree(R->scand); rfree(R->sccost);
+      rfree(R, R->scand); rfree(R, R->sccost);
       R->scand_cap = 0;
-      if (!ralloc(&R->scand, slab * stride) || !ralloc(&R->sccost, slab * stride))
+      if (!ralloc(R, &R->scand, slab * stride) || !ralloc(R, &R->sccost, slab * stride))
         return rfail(R, PIRRT_ENOMEM, "device allocation of candidate lists failed");
       R->scand_cap = slab * stride;
     }
     if (slab * a.nch > R->scnt_cap) {
-      rfree(R->scnt);
+      rfree(R, R->scnt);
       R->scnt_cap = 0;
-      if (!ralloc(&R->scnt, slab * a.nch)) return rfail(R, PIRRT_ENOMEM, "device allocation of list lengths failed");
+      if (!ralloc(R, &R->scnt, slab * a.nch)) return rfail(R, PIRRT_ENOMEM, "device allocation of list lengths failed");
       R->scnt_cap = slab * a.nch;
     }
     if (slab + 1 > R->sdeg_cap) {
-      rfree(R->sdeg); rfree(R->soff);
+      rfree(R, R->sdeg); rfree(R, R->soff);
       R->sdeg_cap = 0;
-      if (!ralloc(&R->sdeg, slab + 1) || !ralloc(&R->soff, slab + 1))
+      if (!ralloc(R, &R->sdeg, slab + 1) || !ralloc(R, &R->soff, slab + 1))
         return rfail(R, PIRRT_ENOMEM, "device allocation of row lengths failed");
       R->sdeg_cap = slab + 1;
     }
@@ -650,9 +643,9 @@ int build_rows(pirrt_rrg* R, int64_t n_old, double radius, int64_t* nnz, const R
   int rc;
   *nnz = 0;
   if (rows + 1 > R->rp_cap) {
-    rfree(R->rp);
+    rfree(R, R->rp);
     R->rp_cap = 0;
-    if (!ralloc(&R->rp, rows + 1 + (rows + 1) / 2)) return rfail(R, PIRRT_ENOMEM, "device allocation of rows failed");
+    if (!ralloc(R, &R->rp, rows + 1 + (rows + 1) / 2)) return rfail(R, PIRRT_ENOMEM, "device allocation of rows failed");
     R->rp_cap = rows + 1 + (rows + 1) / 2;
   }
   if (rows == 0) {
@@ -669,11 +662,11 @@ int build_rows(pirrt_rrg* R, int64_t n_old, double radius, int64_t* nnz, const R
   const int32_t nch = (int32_t)((R->n + kChunk - 1) / kChunk);
   const int64_t cells = rows * nch;
   if (cells + 1 > R->rows_cap) {
-    rfree(R->cnt);
-    rfree(R->cptr);
+    rfree(R, R->cnt);
+    rfree(R, R->cptr);
     R->rows_cap = 0;
     const int64_t c = cells + 1 + (cells + 1) / 2;
-    if (!ralloc(&R->cnt, c) || !ralloc(&R->cptr, c))
+    if (!ralloc(R, &R->cnt, c) || !ralloc(R, &R->cptr, c))
       return rfail(R, PIRRT_ENOMEM, "device allocation of row offsets failed");
     R->rows_cap = c;
   }
@@ -690,11 +683,11 @@ int build_rows(pirrt_rrg* R, int64_t n_old, double radius, int64_t* nnz, const R
   const int64_t m = R->host[0];
   if (m > ((int64_t)1 << 40)) return rdev(R, hipErrorUnknown, "candidate count out of range");
   if (m + 1 > R->cand_cap) {
-    rfree(R->cand_u); rfree(R->cand_v); rfree(R->keep); rfree(R->kpos); rfree(R->ccost);
+    rfree(R, R->cand_u); rfree(R, R->cand_v); rfree(R, R->keep); rfree(R, R->kpos); rfree(R, R->ccost);
     R->cand_cap = 0;
     const int64_t c = (m + 1) + (m + 1) / 4 + 1024;
-    if (!ralloc(&R->cand_u, c) || !ralloc(&R->cand_v, c) || !ralloc(&R->keep, c) || !ralloc(&R->kpos, c + 1) ||
-        !ralloc(&R->ccost, c))
+    if (!ralloc(R, &R->cand_u, c) || !ralloc(R, &R->cand_v, c) || !ralloc(R, &R->keep, c) || !ralloc(R, &R->kpos, c + 1) ||
+        !ralloc(R, &R->ccost, c))
       return rfail(R, PIRRT_ENOMEM, "device allocation of candidate edges failed");
     R->cand_cap = c;
   }
@@ -736,9 +729,9 @@ int draw_free(pirrt_rrg* R, uint64_t seed, uint32_t stream_id, uint64_t* counter
     const int64_t T = need + need / 2 + 4096;
     const int64_t groups = blocks(T);
     if (T > R->cand_cap_s) {
-      rfree(R->cbuf); rfree(R->flag); rfree(R->freed); rfree(R->pos);
+      rfree(R, R->cbuf); rfree(R, R->flag); rfree(R, R->freed); rfree(R, R->pos);
       R->cand_cap_s = 0;
-      if (!ralloc(&R->cbuf, T * d) || !ralloc(&R->flag, T) || !ralloc(&R->freed, groups) || !ralloc(&R->pos, groups + 1))
+      if (!ralloc(R, &R->cbuf, T * d) || !ralloc(R, &R->flag, T) || !ralloc(R, &R->freed, groups) || !ralloc(R, &R->pos, groups + 1))
         return rfail(R, PIRRT_ENOMEM, "device allocation of sampler candidates failed");
       R->cand_cap_s = T;
     }
@@ -776,13 +769,14 @@ int draw_free(pirrt_rrg* R, uint64_t seed, uint32_t stream_id, uint64_t* counter
 }
 
 void release(pirrt_rrg* R) {
-  rfree(R->okind); rfree(R->ocentre); rfree(R->osize); rfree(R->pts); rfree(R->cbuf); rfree(R->flag); rfree(R->freed);
-  rfree(R->pos); rfree(R->cnt); rfree(R->cptr); rfree(R->cand_u); rfree(R->cand_v); rfree(R->keep); rfree(R->kpos); rfree(R->ccost);
-  rfree(R->rp); rfree(R->col); rfree(R->cost); rfree(R->hbuf); rfree(R->dflag);
-  rfree(R->rec); rfree(R->scand); rfree(R->sccost); rfree(R->scnt); rfree(R->sdeg); rfree(R->soff); rfree(R->sstate);
-  rfree(R->lpts); rfree(R->lfeat); rfree(R->llogit); rfree(R->lenc); rfree(R->lflag); rfree(R->lsel);
-  if (R->scan) (void)hipFree(R->scan);
+  rfree(R, R->okind); rfree(R, R->ocentre); rfree(R, R->osize); rfree(R, R->pts); rfree(R, R->cbuf); rfree(R, R->flag); rfree(R, R->freed);
+  rfree(R, R->pos); rfree(R, R->cnt); rfree(R, R->cptr); rfree(R, R->cand_u); rfree(R, R->cand_v); rfree(R, R->keep); rfree(R, R->kpos); rfree(R, R->ccost);
+  rfree(R, R->rp); rfree(R, R->col); rfree(R, R->cost); rfree(R, R->hbuf); rfree(R, R->dflag);
+  rfree(R, R->rec); rfree(R, R->scand); rfree(R, R->sccost); rfree(R, R->scnt); rfree(R, R->sdeg); rfree(R, R->soff); rfree(R, R->sstate);
+  rfree(R, R->lpts); rfree(R, R->lfeat); rfree(R, R->llogit); rfree(R, R->lenc); rfree(R, R->lflag); rfree(R, R->lsel);
+  R->arena.free(R->scan);
   R->scan = nullptr;
+  R->arena.release();
   if (R->host) (void)hipHostFree(R->host);
   R->host = nullptr;
 }
@@ -835,8 +829,8 @@ int pirrt_rrg_create(pirrt_rrg** out, const pirrt_rrg_config* cfg) {
   R->stream = (hipStream_t)cfg->hip_stream;
   R->d = d;
   R->nobs = m;
-  bool ok = ralloc(&R->okind, m) && ralloc(&R->ocentre, (int64_t)m * d) && ralloc(&R->osize, (int64_t)m * d) &&
-            ralloc(&R->dflag, 1);
+  bool ok = ralloc(R, &R->okind, m) && ralloc(R, &R->ocentre, (int64_t)m * d) && ralloc(R, &R->osize, (int64_t)m * d) &&
+            ralloc(R, &R->dflag, 1);
   if (ok && hipHostMalloc((void**)&R->host, kHostWords * sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     R->host = nullptr;
@@ -927,9 +921,9 @@ int pirrt_rrg_sample_learned(pirrt_rrg* R, pirrt_mlp* net, const float* enc, int
   if (R->n + count > (int64_t)INT32_MAX - 1) return rfail(R, PIRRT_EINVAL, "point ids beyond INT32_MAX");
   if (count == 0) return PIRRT_OK;
   if (!R->lpts) {
-    if (!ralloc(&R->lpts, (int64_t)kSelMax * kMaxDim) || !ralloc(&R->lfeat, (int64_t)kSelMax * 288) ||
-        !ralloc(&R->llogit, kSelMax) || !ralloc(&R->lenc, 288) || !ralloc(&R->lflag, kSelMax) ||
-        !ralloc(&R->lsel, kSelMax))
+    if (!ralloc(R, &R->lpts, (int64_t)kSelMax * kMaxDim) || !ralloc(R, &R->lfeat, (int64_t)kSelMax * 288) ||
+        !ralloc(R, &R->llogit, kSelMax) || !ralloc(R, &R->lenc, 288) || !ralloc(R, &R->lflag, kSelMax) ||
+        !ralloc(R, &R->lsel, kSelMax))
       return rfail(R, PIRRT_ENOMEM, "device allocation of the learned sampler failed");
   }
   if ((rc = grow(R, &R->pts, &R->cap, (R->n + count) * d, R->n * d))) return rc;
