@@ -1,7 +1,8 @@
 // Device memory of one handle.  A handle keeps some forty arrays, most of them small, and
-// every hipFree costs 100 to 200 us whatever its size: destroying the two handles of a
-// 200,000-vertex layout took 5.0 ms of its 18, and a growing planner paid for every array it
-// replaced.  Here pieces come from a few slabs that go back to the device with the handle.
+// every hipFree costs 100 to 300 us whatever its size: destroying the two handles of a
+// 200,000-vertex layout took 5.0 ms of its 18 (now 2.9, with slabs of 64 MiB 3.7), and a
+// growing planner paid for every array it replaced.  Here pieces come from a few slabs that go
+// back to the device with the handle.
 //
 // A freed piece is used again by the same handle only, and all of a handle's work is on its
 // one stream, so a new user is ordered after the old one without a wait.  Requests past
@@ -22,6 +23,7 @@ class Arena {
   static constexpr size_t kAlign = 256;
   static constexpr size_t kFirst = (size_t)1 << 20;
   static constexpr size_t kDirect = (size_t)32 << 20;
+  static constexpr size_t kSlabMax = (size_t)256 << 20;
 
   Arena() = default;
   Arena(const Arena&) = delete;
@@ -38,7 +40,8 @@ class Arena {
         if (it->second >= bytes && (best == free_.end() || it->second < best->second)) best = it;
       if (best == free_.end()) {
         // slabs grow with the handle, so that their number stays small
-        size_t size = std::max(bytes, std::min(std::max(2 * total_, kFirst), 2 * kDirect));
+        size_t size = std::max(bytes, std::min(std::max({2 * total_, kFirst, expected_}), kSlabMax));
+        expected_ = 0;
         slabs_.reserve(slabs_.size() + 1);
         char* p = static_cast<char*>(device(size));
         if (!p && size > bytes) p = static_cast<char*>(device(size = bytes));
@@ -57,6 +60,9 @@ class Arena {
       return nullptr;
     }
   }
+
+  // About this many bytes will be asked for soon: the next slab holds them.
+  void expect(size_t bytes) { expected_ = bytes; }
 
   void free(void* ptr) {
     if (!ptr) return;
@@ -108,7 +114,7 @@ class Arena {
 
   std::vector<char*> slabs_;
   std::map<char*, size_t> free_, used_;  // pieces by address
-  size_t total_ = 0;
+  size_t total_ = 0, expected_ = 0;
 };
 
 }  // namespace pirrt

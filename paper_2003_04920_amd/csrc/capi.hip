@@ -20,6 +20,7 @@ using namespace pirrt;
 namespace {
 
 constexpr int64_t kMinVertexCap = 1024;
+constexpr size_t kVertexBytes = 140;  // of all per-vertex arrays, about
 constexpr int64_t kMinEdgeCap = 4096;
 constexpr int kGraphIterCounts = 4;  // captured loop bodies of 1, 2, 4 and 8 iterations
 constexpr int64_t kAdjSlack = 4;     // entries past the end of the adjacency arrays (quad loads)
@@ -340,6 +341,7 @@ int ensure_vcap(pirrt_graph* G, int64_t need) {
   if (cap < kMinVertexCap) cap = kMinVertexCap;
   pirrt_graph T;  // holds the new arrays until all allocations succeeded
   T.A = G->A;
+  if ((size_t)cap * sizeof(int64_t) <= Arena::kDirect) G->arena.expect((size_t)cap * kVertexBytes + Arena::kFirst);
   bool ok = dalloc(G->A, &T.rp, cap + 1) && dalloc(G->A, &T.rp2, cap + 1) && dalloc(G->A, &T.g, cap) && dalloc(G->A, &T.parent, cap) &&
             dalloc(G->A, &T.pcost, cap) && dalloc(G->A, &T.child_cnt, cap) && dalloc(G->A, &T.child_ptr, cap + 1) &&
             dalloc(G->A, &T.child, cap) && dalloc(G->A, &T.fr0, cap) && dalloc(G->A, &T.fr1, cap) &&

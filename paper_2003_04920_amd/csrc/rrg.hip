@@ -829,6 +829,9 @@ int pirrt_rrg_create(pirrt_rrg** out, const pirrt_rrg_config* cfg) {
   R->stream = (hipStream_t)cfg->hip_stream;
   R->d = d;
   R->nobs = m;
+  // points, their records and the sampler's candidates
+  if ((size_t)cfg->point_capacity <= Arena::kDirect / (sizeof(double) * d))
+    R->arena.expect((size_t)cfg->point_capacity * (20 * (size_t)d + 80));
   bool ok = ralloc(R, &R->okind, m) && ralloc(R, &R->ocentre, (int64_t)m * d) && ralloc(R, &R->osize, (int64_t)m * d) &&
             ralloc(R, &R->dflag, 1);
   if (ok && hipHostMalloc((void**)&R->host, kHostWords * sizeof(int64_t), hipHostMallocDefault) != hipSuccess) {

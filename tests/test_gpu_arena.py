@@ -43,7 +43,7 @@ def test_growth_keeps_the_graph(P, sizes):
 
 
 def test_memory_is_given_back(P):
-    """Slabs of 64 MiB at most and larger arrays of their own: all returned (2 MiB of slack for
+    """Slabs and larger arrays of their own: all returned (2 MiB of slack for
     the runtime's own bookkeeping, after one pass that loads the kernels)."""
     obs = W.make_obstacles(3, 5, "mixed", 1)
 
