@@ -23,6 +23,7 @@ constexpr int64_t kMinVertexCap = 1024;
 constexpr size_t kVertexBytes = 140;  // of all per-vertex arrays, about
 constexpr int64_t kMinEdgeCap = 4096;
 constexpr int kGraphIterCounts = 4;  // captured loop bodies of 1, 2, 4 and 8 iterations
+constexpr int kGraphs = 2 * kGraphIterCounts;  // those with jumps after the others
 constexpr int64_t kAdjSlack = 4;     // entries past the end of the adjacency arrays (quad loads)
 
 // Pinned host block for small read-backs; kernels whose result is a few words write it here
@@ -59,7 +60,7 @@ thread_local std::string g_create_error;
 
 // Identity of a captured loop body: every pointer and size baked into its nodes.
 struct LoopKey {
-  const void* ptrs[17];
+  const void* ptrs[18];
   int64_t n, nnz;
   int32_t P, prune, variant, walk_parts, walk_coherent, eval_levels, has_h, iters, mid, lookahead, truncated, blocks;
   int32_t bitmap_tiles, walk_rank, pull;
@@ -167,6 +168,7 @@ struct pirrt_graph {
   std::vector<int32_t> hroots;       // host copy of droots
   std::vector<int32_t> snap_roots;   // the root marks held by the snapshot
   int64_t pcap = 0;
+  float4* seg = nullptr;        // records of the walk by jumps, 2 a vertex (allocated when first needed)
   // insertion / renumbering / translation scratch
   int32_t* add = nullptr;
   int32_t* add0 = nullptr;  // per-slot counts of an insert's new entries (zero between inserts)
@@ -195,8 +197,8 @@ struct pirrt_graph {
   hipEvent_t ev[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   // captured loop bodies
   bool use_graph = true;
-  hipGraphExec_t loop_exec[kGraphIterCounts] = {nullptr, nullptr, nullptr, nullptr};
-  LoopKey loop_key[kGraphIterCounts];
+  hipGraphExec_t loop_exec[kGraphs] = {};
+  LoopKey loop_key[kGraphs];
   int32_t last_iterations = 0;  // iterations of the previous Replan (loop planning)
   // tuning
   int32_t mid_hint = 64;
@@ -301,7 +303,7 @@ int ensure_scan(pirrt_graph* G, int64_t n) {
 }
 
 void drop_loops(pirrt_graph* G) {
-  for (int k = 0; k < kGraphIterCounts; ++k)
+  for (int k = 0; k < kGraphs; ++k)
     if (G->loop_exec[k]) {
       (void)hipGraphExecDestroy(G->loop_exec[k]);
       G->loop_exec[k] = nullptr;
@@ -313,7 +315,7 @@ void free_vertex_arrays(pirrt_graph* G) {
   dfree(G->A, G->child_ptr); dfree(G->A, G->child); dfree(G->A, G->fr0); dfree(G->A, G->fr1); dfree(G->A, G->lvl); dfree(G->A, G->stamp);
   dfree(G->A, G->add); dfree(G->A, G->deg); dfree(G->A, G->pending); dfree(G->A, G->hbuf); dfree(G->A, G->ext_of); dfree(G->A, G->slot_of);
   dfree(G->A, G->g2); dfree(G->A, G->parent2); dfree(G->A, G->pcost2); dfree(G->A, G->ext2); dfree(G->A, G->word); dfree(G->A, G->prob);
-  dfree(G->A, G->dlist); dfree(G->A, G->tiles); dfree(G->A, G->add0);
+  dfree(G->A, G->dlist); dfree(G->A, G->tiles); dfree(G->A, G->add0); dfree(G->A, G->seg);
 }
 
 void forget_vertex_arrays(pirrt_graph* T) {
@@ -325,6 +327,7 @@ void forget_vertex_arrays(pirrt_graph* T) {
   T->dlist = nullptr;
   T->tiles = nullptr;
   T->add0 = nullptr;
+  T->seg = nullptr;
   T->word = nullptr;
 }
 
@@ -1105,9 +1108,9 @@ void enqueue_iteration(pirrt_graph* G, LoopArgs& L, hipStream_t s, bool timing) 
 LoopKey loop_key(pirrt_graph* G, const LoopArgs& L, int iters) {
   LoopKey k;
   memset(&k, 0, sizeof(k));
-  const void* p[17] = {G->rp,     G->col,         G->cst, G->g,   G->parent, G->pcost,  G->stamp,
+  const void* p[18] = {G->rp,     G->col,         G->cst, G->g,   G->parent, G->pcost,  G->stamp,
                        G->word,   G->ext_of,      problem_map(G), base_map(G), G->ps,    G->ctr,
-                       G->ctl,    L.sa.h,         G->child,       G->lvl};
+                       G->ctl,    L.sa.h,         G->child,       G->lvl,    L.wa.seg};
   memcpy(k.ptrs, p, sizeof(p));
   k.n = G->n;
   k.nnz = G->nnz;
@@ -1134,6 +1137,7 @@ LoopKey loop_key(pirrt_graph* G, const LoopArgs& L, int iters) {
 int loop_graph(pirrt_graph* G, LoopArgs& L, int k, hipGraphExec_t* out) {
   const int iters = 1 << k;
   const LoopKey key = loop_key(G, L, iters);
+  if (L.wa.seg) k += kGraphIterCounts;
   if (G->loop_exec[k] && G->loop_key[k] == key) {
     *out = G->loop_exec[k];
     return PIRRT_OK;
@@ -1180,6 +1184,18 @@ bool pulls(const pirrt_graph* G, bool prune) {
   if (G->batched || G->truncated || G->pull == 0) return false;
   return G->pull == 1 || !prune || (G->n <= kPullMax && G->nnz <= kPullEdges);
 }
+
+// Whether Evaluate climbs by jumps (evaluate.hip) or link by link.  The jumps are a launch and
+// a 36-byte record per vertex more and shorten the climb eightfold.  Measured, link by link
+// against jumps from the start: 2D 20,000 vertices 1,925 / 1,338 us, 200,000: 15.3 / 9.4 ms;
+// 3D 60,001: 883 / 741 us; 6D 100,002: 480 / 480, 400,000: 1,157 / 1,115, 700,000: 1,673 /
+// 1,708, 1M: 2,268 / 2,374; 64 problems of 5,000 to 100,000 vertices 17.3 / 12.9 ms.  Past
+// kJumpMax vertices a problem the records cost more than shallow trees' climbs, so there
+// Replan waits kJumpIterations: a vertex k edges from the root settles in iteration k at the
+// earliest, so one that goes on that long has deep trees (2D 400,000: 31.3 ms link by link,
+// 21.3 with jumps from iteration 16 on).
+constexpr int64_t kJumpMax = (int64_t)1 << 19;
+constexpr int64_t kJumpIterations = 16;
 
 // Statistics and return code of a Replan done in one launch, from its final state.
 int finish_single(pirrt_graph* G, const ProblemState& q, std::chrono::steady_clock::time_point t_start,
@@ -1292,6 +1308,8 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
   wa.blocks = std::min(G->batch_blocks, G->cus * kWalkResidentPerCu);
   wa.ctr = G->ctr;
   wa.finish = false;
+  wa.jump = nullptr;
+  wa.seg = nullptr;
   EvalArgs& ea = L.ea;
   ea.n = n;
   ea.ps = G->ps;
@@ -1344,6 +1362,16 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
   HIP_OR_FAIL(G, hipMemsetAsync(G->stamp, 0, (size_t)n, s));
   pirrt_stats agg;
   memset(&agg, 0, sizeof(agg));
+  // Without room for the records, link by link.
+  const bool may_jump = !G->truncated && !G->eval_levels && !G->trace && (wa.prob || wa.parts <= 1);
+  const int64_t jump_from = n / P <= kJumpMax ? 0 : kJumpIterations;
+  auto take_jumps = [&](int64_t iters) {
+    if (!may_jump || wa.seg || iters < jump_from) return;
+    if (!G->seg && !dalloc(G->A, &G->seg, 2 * G->vcap)) return;
+    wa.jump = G->pending;
+    wa.seg = G->seg;
+  };
+  take_jumps(0);
   // first Evaluate of every problem
   if (timing) HIP_OR_FAIL(G, hipEventRecord(G->ev[0], s));
   if (G->trace) HIP_OR_FAIL(G, hipMemsetAsync(G->dhops, 0, sizeof(unsigned long long), s));
@@ -1364,6 +1392,7 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
   int64_t done_iters = 0;
   if (direct) {
     for (int it = 0;; ++it) {
+      take_jumps(it);
       if (G->trace) HIP_OR_FAIL(G, hipMemsetAsync(G->dhops, 0, sizeof(unsigned long long), s));
       enqueue_iteration(G, L, s, timing);
       HIP_OR_FAIL(G, hipGetLastError());
@@ -1412,6 +1441,7 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
     int64_t plan = G->last_iterations > 0 ? G->last_iterations : 8;
     for (;;) {
       const int k = plan >= 8 ? 3 : plan >= 4 ? 2 : plan >= 2 ? 1 : 0;
+      take_jumps(done_iters);
       if (graphs) {
         hipGraphExec_t exec = nullptr;
         if ((rc = loop_graph(G, L, k, &exec))) return rc;

@@ -220,8 +220,53 @@ __global__ void __launch_bounds__(kWgThreads) k_bfs_tail(int32_t j0, int32_t tai
 // one whose children are not visited -- and detached or cyclic chains -- are stamped
 // kWalkNoChildren and keep the g they had.  The stamps of this walk are what the
 // next promising list reads.
+//
+// kJump: Every thread of the launch climbs at about the same time, before the
+// others' stamps are there to be met, so a tree of depth 120 costs 120 dependent round trips
+// and 120 gathers a vertex: 60 to 85 us in the late iterations of 64 mixed problems, when a
+// few 2D ones of some 50,000 vertices are left, and 20 by jumps.  k_walk_jumps first takes kJumpHops links of every vertex at
+// once: the ancestor that far up, and the costs on the way as one 32-byte record.  The walk
+// then climbs by ancestors and folds a record's costs per step, the same additions in the same
+// order (a shorter path is padded with zeros above, and x + 0 is x).
 constexpr int kWalkThreads = 256;
 constexpr int kRing = 16;
+constexpr int kJumpHops = 8;
+
+// jump[v]: the ancestor kJumpHops up (or the root, if it is nearer), kRootMark for a root, -1
+// on a detached chain; seg[2 v], seg[2 v + 1]: the costs from v upwards.
+template <bool kBatched>
+__global__ void __launch_bounds__(kWalkThreads) k_walk_jumps(int32_t n, const int32_t* __restrict__ prob,
+                                                            const ProblemState* __restrict__ ps,
+                                                            const LoopCtl* __restrict__ ctl,
+                                                            const int32_t* __restrict__ parent,
+                                                            const float* __restrict__ pcost,
+                                                            const int32_t* __restrict__ tiles,
+                                                            int32_t* __restrict__ jump, float4* __restrict__ seg) {
+  if (kBatched ? ctl->any_eval == 0 : ps->active == 0) return;
+  const int64_t units = kBatched ? tile_units(ctl, n, kWalkThreads) : 1;
+  for (int64_t wu = kBatched ? blockIdx.x : 0; wu < units; wu += kBatched ? gridDim.x : 1) {
+    const int64_t v = (kBatched ? tile_unit_slot(ctl, tiles, kWalkThreads, wu) : (int64_t)blockIdx.x * kWalkThreads) +
+                      threadIdx.x;
+    if (v >= n || (kBatched && !ps[prob[v]].needs_eval)) continue;
+    float c[kJumpHops];
+    int32_t u = (int32_t)v, p = 0;
+#pragma unroll
+    for (int i = 0; i < kJumpHops; ++i) {
+      c[i] = 0.0f;
+      if (p >= 0) {  // (kRootMark and -1 are negative)
+        p = parent[u];
+        const float cu = pcost[u];
+        if (p >= 0) {
+          c[i] = cu;
+          u = p;
+        }
+      }
+    }
+    jump[v] = p >= 0 || (p == kRootMark && u != (int32_t)v) ? u : p;
+    seg[2 * v] = make_float4(c[0], c[1], c[2], c[3]);
+    seg[2 * v + 1] = make_float4(c[4], c[5], c[6], c[7]);
+  }
+}
 
 // kCoherent: stamps are read and written at device scope (visible across XCDs
 // within the launch); otherwise they are plain accesses (visible within the XCD
@@ -298,7 +343,7 @@ __device__ __forceinline__ bool walk_finish(ProblemState* __restrict__ ps, LoopC
   return run_flag != 0;
 }
 
-template <bool kCountHops, bool kCoherent, bool kBatched, bool kTrunc, bool kFinish = false>
+template <bool kCountHops, bool kCoherent, bool kBatched, bool kTrunc, bool kFinish = false, bool kJump = false>
 __global__ void __launch_bounds__(kWalkThreads) k_eval_walk(int32_t lo, int32_t hi, int32_t n,
                                                            const int32_t* __restrict__ prob,
                                                            ProblemState* __restrict__ ps,
@@ -309,10 +354,13 @@ __global__ void __launch_bounds__(kWalkThreads) k_eval_walk(int32_t lo, int32_t 
                                                            unsigned long long* __restrict__ hops,
                                                            const int32_t* __restrict__ tiles,
                                                            const float* __restrict__ h,
-                                                           const IterCounters* __restrict__ ctr, int book) {
+                                                           const IterCounters* __restrict__ ctr, int book,
+                                                           const int32_t* __restrict__ jump = nullptr,
+                                                           const float4* __restrict__ seg = nullptr) {
   static_assert(!(kTrunc && kBatched), "the truncated Evaluate takes a single graph");
+  static_assert(!(kTrunc && kJump), "the truncated Evaluate tests every vertex of a path");
   __shared__ int32_t ring_v[kRing][kWalkThreads];
-  constexpr bool kRingCost = !kBatched;  // the ring holds the edge costs too
+  constexpr bool kRingCost = !kBatched && !kJump;  // the ring holds the edge costs too
   __shared__ float ring_c[kRingCost ? kRing : 1][kWalkThreads];
   static_assert(!(kFinish && kBatched), "batches keep their finish step");
   if (!walk_finish<kFinish>(ps, ctl, ctr, book)) return;  // no parent switched in this iteration
@@ -333,8 +381,8 @@ __global__ void __launch_bounds__(kWalkThreads) k_eval_walk(int32_t lo, int32_t 
     for (;;) {
       // the stamp, parent and parent-edge cost of u in one round trip
       const unsigned long long w = load_word<kCoherent>(&word[u]);
-      const int32_t p = parent[u];
-      const float c = pcost[u];
+      const int32_t p = kJump ? jump[u] : parent[u];
+      const float c = kJump ? 0.0f : pcost[u];
       if ((w & 0xffffffff00000000ull) == tag) {
         top = (uint32_t)w;
         break;
@@ -372,6 +420,25 @@ __global__ void __launch_bounds__(kWalkThreads) k_eval_walk(int32_t lo, int32_t 
       continue;
     }
     float acc = __uint_as_float(top);
+    if (kJump) {
+      if (k == 0) break;
+      int32_t x = ring_v[(k - 1) % kRing][threadIdx.x];
+      float4 lo4 = seg[2 * (int64_t)x], hi4 = seg[2 * (int64_t)x + 1];
+      for (int64_t i = k - 1; i >= stop; --i) {
+        // the next record is on its way while this one is added up
+        const int32_t y = ring_v[(i > stop ? i - 1 : i) % kRing][threadIdx.x];
+        const float4 lon = seg[2 * (int64_t)y], hin = seg[2 * (int64_t)y + 1];
+        acc = add_rn(add_rn(add_rn(add_rn(acc, hi4.w), hi4.z), hi4.y), hi4.x);
+        acc = add_rn(add_rn(add_rn(add_rn(acc, lo4.w), lo4.z), lo4.y), lo4.x);
+        store_word<kCoherent>(&word[x], tag | __float_as_uint(acc));
+        g[x] = acc;
+        x = y;
+        lo4 = lon;
+        hi4 = hin;
+      }
+      if (stop == 0) break;
+      continue;
+    }
     for (int64_t i = k - 1; i >= stop; --i) {
       const int32_t x = ring_v[i % kRing][threadIdx.x];
       acc = add_rn(acc, kRingCost ? ring_c[i % kRing][threadIdx.x] : pcost[x]);
@@ -411,6 +478,29 @@ void launch_eval_walk(const WalkArgs& a, hipStream_t s) {
     else PIRRT_WALK1(H, C, false, true, false);                          \
   } while (0)
     const bool b = a.prob != nullptr;
+    if (a.seg) {  // by jumps (one part, no hop count, not truncated: see run_replan)
+      if (b)
+        hipLaunchKernelGGL(k_walk_jumps<true>, grid, dim3(kWalkThreads), 0, s, a.n, a.prob, a.ps, a.ctl, a.parent,
+                           a.pcost, a.tiles, a.jump, a.seg);
+      else
+        hipLaunchKernelGGL(k_walk_jumps<false>, grid, dim3(kWalkThreads), 0, s, a.n, a.prob, a.ps, a.ctl, a.parent,
+                           a.pcost, a.tiles, a.jump, a.seg);
+#define PIRRT_WALK_JUMP(C, B, F)                                                                                  \
+  hipLaunchKernelGGL((k_eval_walk<false, C, B, false, F, true>), grid, dim3(kWalkThreads), 0, s, lo, hi, a.n,     \
+                     a.prob, a.ps, a.ctl, a.parent, a.pcost, a.g, a.word, a.hops, a.tiles, a.h, a.ctr, 1, a.jump, \
+                     a.seg)
+      if (a.coherent) {
+        if (b) PIRRT_WALK_JUMP(true, true, false);
+        else if (a.finish) PIRRT_WALK_JUMP(true, false, true);
+        else PIRRT_WALK_JUMP(true, false, false);
+      } else {
+        if (b) PIRRT_WALK_JUMP(false, true, false);
+        else if (a.finish) PIRRT_WALK_JUMP(false, false, true);
+        else PIRRT_WALK_JUMP(false, false, false);
+      }
+#undef PIRRT_WALK_JUMP
+      continue;
+    }
     if (a.truncated && !b) {  // the host rejects the truncated Evaluate for batches
       if (a.hops) {
         if (a.coherent) PIRRT_WALK_TRUNC(true, true); else PIRRT_WALK_TRUNC(true, false);

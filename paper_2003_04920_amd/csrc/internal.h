@@ -222,6 +222,10 @@ struct WalkArgs {
   bool truncated;
   const float* h;          // nullable (h = 0)
   int blocks;              // batches: workgroups of the grid-stride launch
+  // Scratch of the walk by jumps (not truncated, one part): n ints and 2 n records; NULL:
+  // climb link by link.
+  int32_t* jump;
+  float4* seg;
 };
 void launch_eval_walk(const WalkArgs& a, hipStream_t s);
 // Workgroups of the batched walk resident on one compute unit (256 threads and 16 KB
