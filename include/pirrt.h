@@ -192,12 +192,12 @@ int pirrt_replan(pirrt_graph* g, int32_t root, int32_t goal, const float* h, uin
 /*
  * Autotuner: runs the Replan this call describes (arguments as pirrt_replan) once
  * per kernel configuration -- the Improve / promising-set row split (lanes per row
- * x 16-byte quads in flight: 16x1, 8x2, 4x4, 8x1) and the scope of the walk
- * Evaluate's stamps (device, workgroup) -- each from the current policy, keeps the
- * fastest for later calls on this handle and restores the policy (results never
- * depend on the configuration).  *config (nullable) receives the index chosen,
- * row split + 4 x (workgroup-scope stamps).  Without a tuning call a handle uses
- * configuration 5 (8x2, workgroup-scope stamps).
+ * x 16-byte quads in flight: 16x1, 8x2, 4x4, 8x1, or, where Improve finds its domain
+ * by itself, 4x2, 4x3, 4x4, 8x2) and the scope of the walk Evaluate's stamps (device,
+ * workgroup) -- each from the current policy, keeps the fastest for later calls on this
+ * handle and restores the policy (results never depend on the configuration).  *config
+ * (nullable) receives the index chosen, row split + 4 x (workgroup-scope stamps).  Without
+ * a tuning call the row split goes by the graph's size, with workgroup-scope stamps.
  */
 int pirrt_tune(pirrt_graph* g, int32_t root, int32_t goal, const float* h, uint32_t flags, int mem_kind,
                int32_t* config);

@@ -202,7 +202,9 @@ struct pirrt_graph {
   int32_t last_iterations = 0;  // iterations of the previous Replan (loop planning)
   // tuning
   int32_t mid_hint = 64;
-  int row_variant = 1;  // 8 lanes x 2 quads per row; the autotuner tries the others
+  // Row splits of the marks and of Improve's pull form (launch_mark, launch_improve): set by
+  // the autotuner or PIRRT_ROW_VARIANT, -1 by the rule (row_variant()).
+  int mark_variant = -1, pull_variant = -1;
   int batch_blocks = kBatchBlocks;  // batches: workgroups per grid-stride launch (autotuned)
   int cus = 256;                     // compute units of the device
   int32_t bitmap_tiles = INT32_MAX;  // batches: tile lists from the bitmap up to this many tiles
@@ -1058,6 +1060,7 @@ int grow_problems(pirrt_graph* G, int32_t count, const int32_t* problems, const 
 struct LoopArgs {
   int32_t P;
   bool prune;
+  int variant;
   StepArgs sa;
   WalkArgs wa;
   EvalArgs ea;
@@ -1088,11 +1091,11 @@ void enqueue_iteration(pirrt_graph* G, LoopArgs& L, hipStream_t s, bool timing) 
   if (L.sa.pull) {
     launch_promising_signs(L.sa, s);
   } else {
-    launch_mark(L.sa, G->row_variant, s);
+    launch_mark(L.sa, L.variant, s);
     launch_domain_list(L.sa, s);
   }
   if (timing) (void)hipEventRecord(G->ev[3], s);
-  launch_improve(L.sa, G->row_variant, s);
+  launch_improve(L.sa, L.variant, s);
   if (timing) (void)hipEventRecord(G->ev[4], s);
   const bool single = L.sa.prob == nullptr;
   if (!walk_finishes(G, L)) launch_finish(L.P, G->ps, G->ctr, G->ctl, single, s);
@@ -1116,7 +1119,7 @@ LoopKey loop_key(pirrt_graph* G, const LoopArgs& L, int iters) {
   k.nnz = G->nnz;
   k.P = L.P;
   k.prune = L.prune;
-  k.variant = G->row_variant;
+  k.variant = L.variant;
   k.walk_parts = G->walk_parts;
   k.walk_coherent = G->walk_coherent;
   k.eval_levels = G->eval_levels;
@@ -1172,17 +1175,32 @@ struct PolicyOut {
 // two streams of n and one of the whole adjacency an iteration) or the domain is marked
 // and listed first (three launches more, but only the domain's rows, and the promising
 // ones twice).  Without pruning the domain is every reachable row.  With pruning about
-// half the rows are in it, and up to some hundred thousand vertices the launches cost more
-// than the other half.  Measured, marks against pull: 6D with pruning 60,000 vertices 510
-// against 386 us, 100,002: 623 / 527, 200,000: 799 / 745, 400,000: 1,196 / 1,278, 1M:
-// 2,695 / 3,245; 2D 200,000: 15,959 / 14,923; without pruning 6D 200,000: 1,142 / 823, 1M:
-// 5,073 / 3,266.
-constexpr int32_t kPullMax = 1 << 18;
-constexpr int64_t kPullEdges = (int64_t)12 << 20;
+// half the rows are in it, and up to half a million vertices the launches and the marks'
+// scattered writes cost more than the other half.  Measured, marks against pull: with pruning
+// 6D 200,000 vertices 807 / 676 us, 300,000: 956 / 861, 400,000: 1,102 / 1,046, 1M: 2,277 /
+// 2,993; 3D 400,000: 3.65 / 2.79 ms; 2D 400,000: 21.1 / 18.8 ms; without pruning 6D 1M: 5.06 /
+// 3.23 ms.  A batch (64 problems, 1.7M vertices) took 17.4 / 17.5 ms and keeps the marks.
+constexpr int32_t kPullMax = 1 << 19;
+constexpr int64_t kPullEdges = (int64_t)24 << 20;
 
 bool pulls(const pirrt_graph* G, bool prune) {
   if (G->batched || G->truncated || G->pull == 0) return false;
   return G->pull == 1 || !prune || (G->n <= kPullMax && G->nnz <= kPullEdges);
+}
+
+// Row splits (lanes a row x quads in flight: see launch_mark and launch_improve).  Rows have
+// about 30 entries, so 4 lanes with 2 quads each hold one in a pass, and 16 rows to a wave
+// share its index work and its counters; with more rows than the chip keeps in flight, 3 quads
+// leave fewer second passes.  Measured, 8 x 2 against 4 x 2 and 4 x 3 in pull form: 3D 60,001
+// vertices 733 / 697 / 692 us, 6D 100,002: 463 / 446 / 465, 8D 200,000: 657 / 552 / 587, 6D
+// 300,000: 980 / 880 / 861, 1M without pruning 3.25 / 3.48 / 3.23 ms.  With marks 8 x 2 is
+// the fastest on single graphs (1M: 2.28 ms, 4 x 4 2.35); a batch's flat passes over all rows
+// of its tiles take 4 x 4 (64 problems 12.8 -> 11.2 ms).
+constexpr int32_t kNarrowPull = 1 << 18;
+
+int row_variant(const pirrt_graph* G, bool pull) {
+  if (pull) return G->pull_variant >= 0 ? G->pull_variant : (G->n <= kNarrowPull ? 0 : 1);
+  return G->mark_variant >= 0 ? G->mark_variant : (G->batched ? 2 : 1);
 }
 
 // Whether Evaluate climbs by jumps (evaluate.hip) or link by link.  The jumps are a launch and
@@ -1288,6 +1306,7 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
   sa.blocks = G->batch_blocks;
   sa.gs = reinterpret_cast<float*>(G->fr1);  // (in the place of the promising list)
   sa.pull = pulls(G, prune);
+  L.variant = row_variant(G, sa.pull);
   WalkArgs& wa = L.wa;
   wa.n = n;
   wa.prob = problem_map(G);
@@ -1682,7 +1701,7 @@ int tune(pirrt_graph* G, int32_t P, const int32_t* rid, const int32_t* rs, const
   double best = 1e300;
   int bestc = 0;
   auto apply = [&](int c) {
-    G->row_variant = c % kRowVariants;
+    (pulls(G, prune) ? G->pull_variant : G->mark_variant) = c % kRowVariants;
     G->walk_coherent = (c / kRowVariants) % 2 == 0;
     G->batch_blocks = kTuneBlocks[c / kTuneConfigs];
   };
@@ -1852,7 +1871,7 @@ pirrt_graph* new_graph(const pirrt_config* cfg, int* rc_out) {
   const char* variant = getenv("PIRRT_ROW_VARIANT");
   if (variant) {
     int v = atoi(variant);
-    if (v >= 0 && v < kRowVariants) G->row_variant = v;
+    if (v >= 0 && v < kRowVariants) G->mark_variant = G->pull_variant = v;
   }
   return G;
 }

@@ -7,7 +7,7 @@
 // independent.
 //
 // Work split: one group of GW lanes per domain entry, Q aligned quads of row entries
-// per lane in flight (GW x Q x 4 = 64 entries per pass over a row by default).  Loads
+// per lane in flight (GW x Q x 4 entries per pass over a row).  Loads
 // are issued unconditionally (quads past the end of the row re-read the first one
 // and are masked): `vmcnt` is an in-order counter, so a load under a branch would
 // make every later load wait for it.  The per-row minimum is a DPP butterfly.
@@ -215,11 +215,12 @@ void launch_improve_pull(const StepArgs& a, hipStream_t s) {
 }
 
 template <int GW, int U>
+void launch_improve_p(const StepArgs& a, hipStream_t s) {
+  if (a.lookahead) launch_improve_pull<GW, U, true>(a, s); else launch_improve_pull<GW, U, false>(a, s);
+}
+
+template <int GW, int U>
 void launch_improve_b(const StepArgs& a, hipStream_t s) {
-  if (a.pull) {
-    if (a.lookahead) launch_improve_pull<GW, U, true>(a, s); else launch_improve_pull<GW, U, false>(a, s);
-    return;
-  }
   if (a.prob)
     launch_improve_t<GW, U, true, false>(a, s);
   else if (a.truncated)
@@ -237,6 +238,15 @@ void launch_promising_signs(const StepArgs& a, hipStream_t s) {
 }
 
 void launch_improve(const StepArgs& a, int variant, hipStream_t s) {
+  if (a.pull) {
+    switch (variant) {
+      case 0: launch_improve_p<4, 2>(a, s); break;
+      case 1: launch_improve_p<4, 3>(a, s); break;
+      case 2: launch_improve_p<4, 4>(a, s); break;
+      default: launch_improve_p<8, 2>(a, s); break;
+    }
+    return;
+  }
   switch (variant) {
     case 0: launch_improve_b<16, 1>(a, s); break;
     case 1: launch_improve_b<8, 2>(a, s); break;
