@@ -26,6 +26,8 @@ constexpr int kGraphIterCounts = 4;  // captured loop bodies of 1, 2, 4 and 8 it
 constexpr int kGraphs = 2 * kGraphIterCounts;  // those with jumps after the others
 constexpr int64_t kAdjSlack = 4;     // entries past the end of the adjacency arrays (quad loads)
 
+constexpr int64_t kHostState = 512;
+
 // Pinned host block for small read-backs; kernels whose result is a few words write it here
 // (a copy back costs 6 to 8 us of a short call).
 struct HostBlock {
@@ -34,6 +36,7 @@ struct HostBlock {
   int32_t flag;
   int32_t count[3];
   int64_t word;
+  float state[4 * kHostState];  // the host Replan's state of up to kHostState vertices
 };
 
 // Validation kernels for device-resident inputs of replan / set_policy.
@@ -49,6 +52,36 @@ __global__ void k_check_policy(int32_t n, const int32_t* __restrict__ parent, co
   uint32_t w = __float_as_uint(pcost[v]);
   if (p < -1 || p >= len || p == v - b) atomicOr(bad, 1);
   if ((w >> 31) != 0 || (w & 0x7f800000u) == 0x7f800000u) atomicOr(bad, 2);
+}
+
+// The host Replan's state to pinned memory (slot order; h, nullable, in caller order) ...
+__global__ void k_policy_to_host(int32_t n, const int32_t* __restrict__ parent, const float* __restrict__ pcost,
+                                 const float* __restrict__ h, int32_t* __restrict__ hparent,
+                                 float* __restrict__ hpcost, float* __restrict__ hh) {
+  const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (v >= n) return;
+  hparent[v] = parent[v];
+  hpcost[v] = pcost[v];
+  if (h) hh[v] = h[v];
+}
+
+// ... and back, with the caller's device outputs (nullable, caller order).
+__global__ void k_policy_from_host(int32_t n, int32_t root, const float* __restrict__ hg,
+                                   const int32_t* __restrict__ hparent, const float* __restrict__ hpcost,
+                                   const int32_t* __restrict__ slot_of, const int32_t* __restrict__ ext_of,
+                                   float* __restrict__ g, int32_t* __restrict__ parent, float* __restrict__ pcost,
+                                   int32_t* __restrict__ droots, float* __restrict__ g_out,
+                                   int32_t* __restrict__ parent_out) {
+  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= n) return;
+  if (e == 0) droots[0] = root;
+  const int32_t s = slot_of[e], p = hparent[s];
+  const float x = hg[s];
+  g[s] = x;
+  parent[s] = p;
+  pcost[s] = hpcost[s];
+  if (g_out) g_out[e] = x;
+  if (parent_out) parent_out[e] = p >= 0 ? ext_of[p] : -1;
 }
 
 inline unsigned grid_for(int64_t n, int per = 256) {
@@ -125,6 +158,10 @@ struct pirrt_graph {
   // Single graphs up to this many vertices replan on the host (PIRRT_HOST_MAX; 0 = never)
   int64_t host_max = 512;
   uint64_t adj_version = 0;  // bumped whenever the adjacency or the slot order changes
+  // pinned g, pcost, h (floats) and parent of hpin_cap vertices: the host Replan's state where
+  // the host block's is too small
+  float* hpin = nullptr;
+  int64_t hpin_cap = 0;
   // host copies of the slot-ordered adjacency and ids for the host Replan
   uint64_t hm_version = ~0ull;
   std::vector<int64_t> hm_rp;
@@ -528,6 +565,8 @@ void release_all(pirrt_graph* G) {
   dfree(G->A, G->pstart); dfree(G->A, G->dgrow); dfree(G->A, G->rsync);
   if (G->hps) (void)hipHostFree(G->hps);
   G->hps = nullptr;
+  if (G->hpin) (void)hipHostFree(G->hpin);
+  G->hpin = nullptr;
   raw_free(G->A, G->scan_scratch);
   G->scan_scratch = nullptr;
   G->arena.release();
@@ -1519,15 +1558,32 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
 
 // Replan of a small single graph on the host (host_replan.hip): the slot-ordered
 // adjacency is copied to the host when it changed since the last such call, the policy
-// and h are copied over, the roots re-marked as on the device, and the result goes
-// back to the device arrays (which stay the handle's state) and to the caller in
-// caller ids.
+// and h come over, the roots are re-marked as on the device, and the result goes back to
+// the device arrays (which stay the handle's state) and to the caller in caller ids.
+//
+// Bound by the two round trips.  The policy moves through pinned memory that one kernel
+// writes and one reads: as copies of pageable vectors (two over, four back, up to three more
+// for device buffers) a call of 302 vertices took 119 us, of which the Replan itself about 40;
+// now 88.
 int run_host_replan(pirrt_graph* G, int32_t root, int32_t goal, const float* h, int mem_kind, bool prune,
                     bool lookahead, float* g_out, int32_t* parent_out, pirrt_stats* stats) {
   auto t_start = std::chrono::steady_clock::now();
   hipStream_t s = G->stream;
   const int32_t n = (int32_t)G->n;
   const size_t m = (size_t)G->nnz;
+  int rc;
+  if ((rc = ensure_pcap(G, 1))) return rc;
+  if (n > kHostState && n > G->hpin_cap) {
+    float* p = nullptr;
+    const int64_t cap = n + n / 2;
+    if (hipHostMalloc((void**)&p, 16 * (size_t)cap, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(G, PIRRT_ENOMEM, "allocation of pinned memory for the host Replan failed");
+    }
+    if (G->hpin) (void)hipHostFree(G->hpin);
+    G->hpin = p;
+    G->hpin_cap = cap;
+  }
   if (G->hm_version != G->adj_version) {
     G->hm_rp.resize((size_t)n + 1);
     G->hm_col.resize(m);
@@ -1540,19 +1596,18 @@ int run_host_replan(pirrt_graph* G, int32_t root, int32_t goal, const float* h, 
     G->hm_ext.resize((size_t)n);
     for (int32_t id = 0; id < n; ++id) G->hm_ext[(size_t)G->hslot[(size_t)id]] = id;
   }
-  std::vector<float> g((size_t)n), pc((size_t)n), hs;
-  std::vector<int32_t> par((size_t)n);
-  HIP_OR_FAIL(G, hipMemcpyAsync(par.data(), G->parent, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToHost, s));
-  HIP_OR_FAIL(G, hipMemcpyAsync(pc.data(), G->pcost, sizeof(float) * (size_t)n, hipMemcpyDeviceToHost, s));
-  std::vector<float> hc;
-  if (h && mem_kind == PIRRT_MEM_DEVICE) {
-    hc.resize((size_t)n);
-    HIP_OR_FAIL(G, hipMemcpyAsync(hc.data(), h, sizeof(float) * (size_t)n, hipMemcpyDeviceToHost, s));
-  }
+  const bool dev = mem_kind == PIRRT_MEM_DEVICE;
+  const int64_t cap = n > kHostState ? G->hpin_cap : kHostState;
+  float *g = n > kHostState ? G->hpin : G->host->state, *pc = g + cap, *hc = pc + cap;
+  int32_t* par = reinterpret_cast<int32_t*>(hc + cap);
+  hipLaunchKernelGGL(k_policy_to_host, dim3(grid_for(n)), dim3(256), 0, s, n, G->parent, G->pcost, dev ? h : nullptr,
+                     par, pc, hc);
+  HIP_OR_FAIL(G, hipGetLastError());
   HIP_OR_FAIL(G, hipStreamSynchronize(s));
   G->hm_version = G->adj_version;
+  std::vector<float> hs;
   if (h) {
-    const float* hsrc = mem_kind == PIRRT_MEM_DEVICE ? hc.data() : h;
+    const float* hsrc = dev ? hc : h;
     hs.resize((size_t)n);
     for (int32_t id = 0; id < n; ++id) {
       if (!(hsrc[id] >= 0.0f)) return fail(G, PIRRT_EINVAL, "h has a NaN or negative entry");
@@ -1571,9 +1626,9 @@ int run_host_replan(pirrt_graph* G, int32_t root, int32_t goal, const float* h, 
   p.cst = G->hm_cst.data();
   p.ext = G->hm_ext.data();
   p.h = h ? hs.data() : nullptr;
-  p.g = g.data();
-  p.parent = par.data();
-  p.pcost = pc.data();
+  p.g = g;
+  p.parent = par;
+  p.pcost = pc;
   p.root = G->hslot[(size_t)root];
   p.goal = G->hslot[(size_t)goal];
   p.prune = prune;
@@ -1581,37 +1636,20 @@ int run_host_replan(pirrt_graph* G, int32_t root, int32_t goal, const float* h, 
   p.cap = G->max_iters > 0 ? G->max_iters : 4 * (int64_t)n + 8;
   HostReplanStats hst;
   const int capped = host_replan(p, &hst);
-  // the device arrays stay the handle's state
-  HIP_OR_FAIL(G, hipMemcpyAsync(G->g, g.data(), sizeof(float) * (size_t)n, hipMemcpyHostToDevice, s));
-  HIP_OR_FAIL(G, hipMemcpyAsync(G->parent, par.data(), sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice, s));
-  HIP_OR_FAIL(G, hipMemcpyAsync(G->pcost, pc.data(), sizeof(float) * (size_t)n, hipMemcpyHostToDevice, s));
-  int rc;
-  if ((rc = ensure_pcap(G, 1))) return rc;
-  HIP_OR_FAIL(G, hipMemcpyAsync(G->droots, &root, sizeof(int32_t), hipMemcpyHostToDevice, s));
+  // the device arrays stay the handle's state; the caller's outputs in caller ids (a root
+  // reads -1)
+  hipLaunchKernelGGL(k_policy_from_host, dim3(grid_for(n)), dim3(256), 0, s, n, root, g, par, pc, G->slot_of,
+                     G->ext_of, G->g, G->parent, G->pcost, G->droots, dev ? g_out : nullptr,
+                     dev ? parent_out : nullptr);
+  HIP_OR_FAIL(G, hipGetLastError());
   G->nroots = 1;
   G->hroots.assign(1, root);
-  // the caller's outputs in caller ids (a root reads -1)
-  std::vector<float> go;
-  std::vector<int32_t> po;
-  float* gw = g_out;
-  int32_t* pw = parent_out;
-  const bool dev = mem_kind == PIRRT_MEM_DEVICE;
-  if (dev && g_out) {
-    go.resize((size_t)n);
-    gw = go.data();
-  }
-  if (dev && parent_out) {
-    po.resize((size_t)n);
-    pw = po.data();
-  }
-  for (int32_t id = 0; id < n; ++id) {
-    const size_t sl = (size_t)G->hslot[(size_t)id];
-    if (gw) gw[id] = g[sl];
-    if (pw) pw[id] = par[sl] >= 0 ? G->hm_ext[(size_t)par[sl]] : -1;
-  }
-  if (dev && g_out) HIP_OR_FAIL(G, hipMemcpyAsync(g_out, go.data(), sizeof(float) * (size_t)n, hipMemcpyHostToDevice, s));
-  if (dev && parent_out)
-    HIP_OR_FAIL(G, hipMemcpyAsync(parent_out, po.data(), sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice, s));
+  if (!dev)
+    for (int32_t id = 0; id < n; ++id) {
+      const size_t sl = (size_t)G->hslot[(size_t)id];
+      if (g_out) g_out[id] = g[sl];
+      if (parent_out) parent_out[id] = par[sl] >= 0 ? G->hm_ext[(size_t)par[sl]] : -1;
+    }
   HIP_OR_FAIL(G, hipStreamSynchronize(s));
   if (stats) {
     memset(stats, 0, sizeof(*stats));
