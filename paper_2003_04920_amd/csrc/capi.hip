@@ -96,7 +96,7 @@ struct LoopKey {
   const void* ptrs[18];
   int64_t n, nnz;
   int32_t P, prune, variant, walk_parts, walk_coherent, eval_levels, has_h, iters, mid, lookahead, truncated, blocks;
-  int32_t bitmap_tiles, walk_rank, pull;
+  int32_t bitmap_tiles, walk_rank, pull, dense;
   bool operator==(const LoopKey& o) const { return memcmp(this, &o, sizeof(LoopKey)) == 0; }
 };
 
@@ -246,7 +246,9 @@ struct pirrt_graph {
   int cus = 256;                     // compute units of the device
   int32_t bitmap_tiles = INT32_MAX;  // batches: tile lists from the bitmap up to this many tiles
   bool walk_rank = true;  // batches: the walk takes the active tiles by their rank inside their problem
-  int pull = -1;  // Improve's pull form: 0 never, 1 always, -1 by the rule (PIRRT_PULL)
+  // Improve's pull form: 0 never, 1 always, 2 where the promising set is dense, -1 by the rule
+  // (PIRRT_PULL)
+  int pull = -1;
   bool lookahead = false;  // narrowed Improve domain for the current call (PIRRT_LOOKAHEAD)
   bool truncated = false;  // truncated Evaluate for the current call (PIRRT_TRUNCATED)
   LoopKey prev_key;          // loop arguments of the previous Replan (graphs when they repeat)
@@ -1171,6 +1173,7 @@ LoopKey loop_key(pirrt_graph* G, const LoopArgs& L, int iters) {
   k.bitmap_tiles = G->bitmap_tiles;
   k.walk_rank = G->walk_rank;
   k.pull = L.sa.pull;
+  k.dense = L.sa.dense;
   return k;
 }
 
@@ -1218,12 +1221,13 @@ struct PolicyOut {
 // scattered writes cost more than the other half.  Measured, marks against pull: with pruning
 // 6D 200,000 vertices 807 / 676 us, 300,000: 956 / 861, 400,000: 1,102 / 1,046, 1M: 2,277 /
 // 2,993; 3D 400,000: 3.65 / 2.79 ms; 2D 400,000: 21.1 / 18.8 ms; without pruning 6D 1M: 5.06 /
-// 3.23 ms.  A batch (64 problems, 1.7M vertices) took 17.4 / 17.5 ms and keeps the marks.
+// 3.23 ms.  Past these sizes, with pruning, the iterations whose promising set is dense pull all
+// the same (k_improve_auto: 6D 1M 2,277 -> 2,050 us).  A batch (64 problems, 1.7M vertices) took 17.4 / 17.5 ms and keeps the marks.
 constexpr int32_t kPullMax = 1 << 19;
 constexpr int64_t kPullEdges = (int64_t)24 << 20;
 
 bool pulls(const pirrt_graph* G, bool prune) {
-  if (G->batched || G->truncated || G->pull == 0) return false;
+  if (G->batched || G->truncated || G->pull == 0 || G->pull == 2) return false;
   return G->pull == 1 || !prune || (G->n <= kPullMax && G->nnz <= kPullEdges);
 }
 
@@ -1345,6 +1349,8 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
   sa.blocks = G->batch_blocks;
   sa.gs = reinterpret_cast<float*>(G->fr1);  // (in the place of the promising list)
   sa.pull = pulls(G, prune);
+  sa.dense = !sa.pull && prune && !G->batched && !G->truncated && G->pull != 0;
+  if (sa.dense) sa.gs = reinterpret_cast<float*>(G->deg);  // (the list has fr1)
   L.variant = row_variant(G, sa.pull);
   WalkArgs& wa = L.wa;
   wa.n = n;
@@ -1893,7 +1899,7 @@ pirrt_graph* new_graph(const pirrt_config* cfg, int* rc_out) {
   if (sm) G->resident = atoi(sm) != 0;
   if (getenv("PIRRT_ROW_VARIANT") || wc || wp || gr) G->resident = false;
   const char* pl = getenv("PIRRT_PULL");
-  if (pl) G->pull = atoi(pl) != 0;
+  if (pl) G->pull = atoi(pl) == 2 ? 2 : atoi(pl) != 0;
   const char* fi = getenv("PIRRT_FAULT_INJECT");
   if (fi) {
     G->fault_launch = strcmp(fi, "launch") == 0;

@@ -47,16 +47,16 @@ using rows::batch_grid;
 //
 // Improve runs over the compacted domain: group i takes entry i of dlist; workgroups
 // past the domain's end leave at once.
-template <int GW, int Q, typename Idx, bool kBatched, bool kTrunc, bool kPull = false, bool kLook = false>
-__global__ void __launch_bounds__(kThreads) k_improve(int32_t n, const int32_t* __restrict__ prob,
-                                                     const ProblemState* __restrict__ ps,
-                                                     const LoopCtl* __restrict__ ctl, const float* __restrict__ g,
-                                                     const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
-                                                     const float* __restrict__ cst, const int32_t* __restrict__ dlist,
-                                                     const int32_t* __restrict__ ext_of,
-                                                     int32_t* __restrict__ parent, float* __restrict__ pcost,
-                                                     IterCounters* __restrict__ ctr,
-                                                     const float* __restrict__ h = nullptr) {
+//
+// kCountP: the pull form counts the promising set too (else its list did).
+template <int GW, int Q, typename Idx, bool kBatched, bool kTrunc, bool kPull, bool kLook, bool kCountP>
+__device__ __forceinline__ void improve(int32_t n, const int32_t* __restrict__ prob,
+                                        const ProblemState* __restrict__ ps, const LoopCtl* __restrict__ ctl,
+                                        const float* __restrict__ g, const int64_t* __restrict__ rp,
+                                        const int32_t* __restrict__ col, const float* __restrict__ cst,
+                                        const int32_t* __restrict__ dlist, const int32_t* __restrict__ ext_of,
+                                        int32_t* __restrict__ parent, float* __restrict__ pcost,
+                                        IterCounters* __restrict__ ctr, const float* __restrict__ h) {
   static_assert(!(kPull && (kBatched || kTrunc)) && (kPull || !kLook), "pull: single graphs");
   if (ctl->any_active == 0) return;  // every problem has converged
   const int64_t cnt = kPull ? n : ctl->ndomain;
@@ -154,9 +154,47 @@ __global__ void __launch_bounds__(kThreads) k_improve(int32_t n, const int32_t* 
     rows::flush_counters_wave<false, true, true, true, false>(ctr, p, valid && gl == 0, 0, in ? 1 : 0,
                                                               in ? (unsigned long long)(b - a) : 0ull, changed);
   else
-    flush_counters(ctr, p, valid && gl == 0, px ? 1 : 0, in ? 1 : 0, in ? (unsigned long long)(b - a) : 0ull, changed,
-                   px ? (int)(rb - ra) : 0);
+    flush_counters(ctr, p, valid && gl == 0, kCountP && px ? 1 : 0, in ? 1 : 0, in ? (unsigned long long)(b - a) : 0ull,
+                   changed, kCountP && px ? (int)(rb - ra) : 0);
   }
+}
+
+template <int GW, int Q, typename Idx, bool kBatched, bool kTrunc, bool kPull = false, bool kLook = false>
+__global__ void __launch_bounds__(kThreads) k_improve(int32_t n, const int32_t* __restrict__ prob,
+                                                     const ProblemState* __restrict__ ps,
+                                                     const LoopCtl* __restrict__ ctl, const float* __restrict__ g,
+                                                     const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
+                                                     const float* __restrict__ cst, const int32_t* __restrict__ dlist,
+                                                     const int32_t* __restrict__ ext_of,
+                                                     int32_t* __restrict__ parent, float* __restrict__ pcost,
+                                                     IterCounters* __restrict__ ctr,
+                                                     const float* __restrict__ h = nullptr) {
+  improve<GW, Q, Idx, kBatched, kTrunc, kPull, kLook, true>(n, prob, ps, ctl, g, rp, col, cst, dlist, ext_of, parent,
+                                                            pcost, ctr, h);
+}
+
+// Large single graphs with pruning: pull form in the iterations whose promising set is dense
+// (its marks and domain list then did nothing), over the listed domain in the others.  The
+// domain of a third of 1M 6D vertices is three quarters of them: marking it took 63 to 113 us,
+// more than the rows it saves.
+template <int GW, int Q, typename Idx, bool kLook>
+__global__ void __launch_bounds__(kThreads) k_improve_auto(int32_t n, const ProblemState* __restrict__ ps,
+                                                          const LoopCtl* __restrict__ ctl,
+                                                          const float* __restrict__ g, const float* __restrict__ gs,
+                                                          const int64_t* __restrict__ rp,
+                                                          const int32_t* __restrict__ col,
+                                                          const float* __restrict__ cst,
+                                                          const int32_t* __restrict__ dlist,
+                                                          const int32_t* __restrict__ ext_of,
+                                                          int32_t* __restrict__ parent, float* __restrict__ pcost,
+                                                          IterCounters* __restrict__ ctr,
+                                                          const float* __restrict__ h) {
+  if (dense_promising(ctl, n))
+    improve<GW, Q, Idx, false, false, true, kLook, false>(n, nullptr, ps, ctl, gs, rp, col, cst, dlist, ext_of, parent,
+                                                          pcost, ctr, h);
+  else
+    improve<GW, Q, Idx, false, false, false, false, true>(n, nullptr, ps, ctl, g, rp, col, cst, dlist, ext_of, parent,
+                                                          pcost, ctr, h);
 }
 
 // The promising set as signs, for Improve's pull form: gs(v) = -g(v) where fl(g + h) < G,
@@ -203,6 +241,16 @@ void launch_improve_t(const StepArgs& a, hipStream_t s) {
 }
 
 template <int GW, int U, bool L>
+void launch_improve_auto(const StepArgs& a, hipStream_t s) {
+  if (a.nnz < ((int64_t)1 << 32) - 64 * GW)
+    hipLaunchKernelGGL((k_improve_auto<GW, U, uint32_t, L>), grid_for(a.n, GW), dim3(kThreads), 0, s, a.n, a.ps, a.ctl,
+                       a.g, a.gs, a.rp, a.col, a.cst, a.dlist, a.ext_of, a.parent, a.pcost, a.ctr, a.h);
+  else
+    hipLaunchKernelGGL((k_improve_auto<GW, U, int64_t, L>), grid_for(a.n, GW), dim3(kThreads), 0, s, a.n, a.ps, a.ctl,
+                       a.g, a.gs, a.rp, a.col, a.cst, a.dlist, a.ext_of, a.parent, a.pcost, a.ctr, a.h);
+}
+
+template <int GW, int U, bool L>
 void launch_improve_pull(const StepArgs& a, hipStream_t s) {
   if (a.nnz < ((int64_t)1 << 32) - 64 * GW)
     hipLaunchKernelGGL((k_improve<GW, U, uint32_t, false, false, true, L>), grid_for(a.n, GW), dim3(kThreads), 0, s,
@@ -225,6 +273,10 @@ void launch_improve_b(const StepArgs& a, hipStream_t s) {
     launch_improve_t<GW, U, true, false>(a, s);
   else if (a.truncated)
     launch_improve_t<GW, U, false, true>(a, s);
+  else if (a.dense && a.lookahead)
+    launch_improve_auto<GW, U, true>(a, s);
+  else if (a.dense)
+    launch_improve_auto<GW, U, false>(a, s);
   else
     launch_improve_t<GW, U, false, false>(a, s);
 }

@@ -312,7 +312,8 @@ struct StepArgs {
   const unsigned long long* word;  // the walk stamps
   int blocks;                // batches: workgroups of each grid-stride launch
   bool pull;                 // single graphs: Improve over every slot, from the signed g
-  float* gs;                 // pull: g with the promising set as signs (n entries of room)
+  float* gs;                 // pull, dense: g with the promising set as signs (n entries of room)
+  bool dense;                // single graphs, marks: pull form where the promising set is dense
 };
 void launch_promising_signs(const StepArgs& a, hipStream_t s);
 constexpr int kRowVariants = 4;

@@ -114,11 +114,12 @@ __global__ void __launch_bounds__(kThreads) k_domain_list(int32_t n, LoopCtl* __
                                                          uint8_t* __restrict__ stamp, int32_t* __restrict__ dlist,
                                                          const int32_t* __restrict__ prob,
                                                          const ProblemState* __restrict__ ps,
-                                                         const int32_t* __restrict__ tiles) {
+                                                         const int32_t* __restrict__ tiles, int dense) {
   if (ctl->any_active == 0) return;  // every problem has converged
   const uint32_t epoch = ctl->epoch;
   const uint8_t ep = (uint8_t)epoch;
   const bool wrap = (epoch & 0xffu) == 0xffu;
+  if (dense && !wrap && dense_promising(ctl, n)) return;  // Improve takes every row
   const int64_t units = prob ? tile_units(ctl, n, kThreads * kListPer) : 1;
   for (int64_t wu = prob ? blockIdx.x : 0; wu < units; wu += prob ? gridDim.x : 1) {
   const int64_t bbase =
@@ -212,7 +213,7 @@ __global__ void __launch_bounds__(kThreads) k_promising_list(int32_t n, ProblemS
                                                             uint8_t* __restrict__ stamp, int32_t* __restrict__ plist,
                                                             IterCounters* __restrict__ ctr,
                                                             const unsigned long long* __restrict__ word, int prune,
-                                                            const int64_t* __restrict__ rp) {
+                                                            const int64_t* __restrict__ rp, float* __restrict__ gs) {
   const bool active = ps[0].active != 0;
   const float G = active ? (prune ? g[ps[0].goal] : pos_inf()) : -pos_inf();
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -245,10 +246,18 @@ __global__ void __launch_bounds__(kThreads) k_promising_list(int32_t n, ProblemS
       if (add_rn(a.y, b.y) < G) mask |= 1u << (4 * q + 1);
       if (add_rn(a.z, b.z) < G) mask |= 1u << (4 * q + 2);
       if (add_rn(a.w, b.w) < G) mask |= 1u << (4 * q + 3);
+      if (gs) {  // signs for Improve's pull form
+        const uint32_t m = mask >> (4 * q);
+        reinterpret_cast<float4*>(gs + v0)[q] =
+            make_float4(m & 1u ? -a.x : a.x, m & 2u ? -a.y : a.y, m & 4u ? -a.z : a.z, m & 8u ? -a.w : a.w);
+      }
     }
   } else {
-    for (int i = 0; i < kListPer && v0 + i < n; ++i)
-      if (add_rn(g[v0 + i], h ? h[v0 + i] : 0.0f) < G) mask |= 1u << i;
+    for (int i = 0; i < kListPer && v0 + i < n; ++i) {
+      const bool p = add_rn(g[v0 + i], h ? h[v0 + i] : 0.0f) < G;
+      if (p) mask |= 1u << i;
+      if (gs) gs[v0 + i] = p ? -g[v0 + i] : g[v0 + i];
+    }
   }
   // the degrees of the listed rows (the rows the mark walks), for the counters: the
   // thread's kListPer + 1 row offsets in one batch of 16-byte loads
@@ -343,12 +352,14 @@ __global__ void __launch_bounds__(kThreads) k_mark_rows(const ProblemState* __re
                                                        const int32_t* __restrict__ plist,
                                                        const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
                                                        const float* __restrict__ cst, const float* __restrict__ g,
-                                                       const float* __restrict__ h, uint8_t* __restrict__ stamp) {
+                                                       const float* __restrict__ h, uint8_t* __restrict__ stamp,
+                                                       int32_t dense_n) {
   constexpr int kSlots = tab_slots<GW>();
   constexpr int kPer = kSlots / kThreads;
   __shared__ int32_t keys[kSlots];
   __shared__ uint32_t offer[kLook ? kSlots : 1];  // best offer (binary32 bits, >= 0) per position
   if (ctl->any_active == 0) return;
+  if (dense_n && dense_promising(ctl, dense_n)) return;  // Improve takes every row
   const int64_t cnt = ctl->npromising;
   const uint8_t ep = (uint8_t)ctl->epoch;
   const int64_t step = (int64_t)gridDim.x * (kThreads / GW);  // one pass when the grid covers the list
@@ -442,16 +453,16 @@ void launch_mark_t(const StepArgs& a, hipStream_t s) {
     const dim3 pgrid((unsigned)((a.n + per_block - 1) / per_block));
     if (a.truncated)
       hipLaunchKernelGGL(k_promising_list<true>, pgrid, dim3(kThreads), 0, s, a.n, a.ps, a.ctl, a.g, a.h, a.stamp,
-                         a.plist, a.ctr, a.word, a.prune, a.rp);
+                         a.plist, a.ctr, a.word, a.prune, a.rp, a.dense ? a.gs : nullptr);
     else
       hipLaunchKernelGGL(k_promising_list<false>, pgrid, dim3(kThreads), 0, s, a.n, a.ps, a.ctl, a.g, a.h, a.stamp,
-                         a.plist, a.ctr, a.word, a.prune, a.rp);
+                         a.plist, a.ctr, a.word, a.prune, a.rp, a.dense ? a.gs : nullptr);
     const bool narrow = a.nnz < ((int64_t)1 << 32) - 64 * GW;
     const int div = a.n >= kMarkRowsHalfGridMin ? kMarkRowsGridDiv : 1;
     const dim3 rgrid = grid_for((a.n + div - 1) / div, GW);
 #define PIRRT_MARK_ROWS(I, L)                                                                                   \
   hipLaunchKernelGGL((k_mark_rows<GW, U, I, L>), rgrid, dim3(kThreads), 0, s, a.ps, a.ctl, a.plist, a.rp, a.col, \
-                     a.cst, a.g, a.h, a.stamp)
+                     a.cst, a.g, a.h, a.stamp, a.dense ? a.n : 0)
     if (narrow) {
       if (a.lookahead) PIRRT_MARK_ROWS(uint32_t, true); else PIRRT_MARK_ROWS(uint32_t, false);
     } else {
@@ -533,7 +544,7 @@ void launch_domain_list(const StepArgs& a, hipStream_t s) {
   static_assert(kThreads * kListPer == kTileSlots, "one domain-list workgroup per tile");
   const dim3 grid = a.prob ? batch_grid(a.n, (int)per_block, a.blocks) : dim3((unsigned)((a.n + per_block - 1) / per_block));
   hipLaunchKernelGGL(k_domain_list, grid, dim3(kThreads), 0, s, a.n, a.ctl, a.stamp, a.dlist, a.prob, a.ps,
-                     a.tiles);
+                     a.tiles, a.dense ? 1 : 0);
 }
 
 // Variants: lanes per row x quads per lane in flight (GW x Q x 4 entries per pass).
