@@ -415,10 +415,22 @@ hipError_t launch_replan_resident(ResidentArgs a, hipStream_t s) {
   static_assert(kResidentMax <= 15 * kResThreads && kResidentMax <= kResRows * kResidentGroups, "sizes covered");
   const int W = (a.n + kResRows - 1) / kResRows;  // one row a group
   a.rows = (a.n + W - 1) / W;
-  if (a.n <= kResThreads) return launch_k<1>(a, W, s);
-  if (a.n <= 2 * kResThreads) return launch_k<2>(a, W, s);
-  if (a.n <= 4 * kResThreads) return launch_k<4>(a, W, s);
-  if (a.n <= 8 * kResThreads) return launch_k<8>(a, W, s);
+  // A thread's vertices, by steps: those it has no use for are evaluated all the same (10,000 2D
+  // vertices took 140 us with 15 to a thread, 117 with 10; 5,000 95 with 8, 88 with 5).
+  switch ((a.n + kResThreads - 1) / kResThreads) {
+    case 1: return launch_k<1>(a, W, s);
+    case 2: return launch_k<2>(a, W, s);
+    case 3: return launch_k<3>(a, W, s);
+    case 4: return launch_k<4>(a, W, s);
+    case 5: return launch_k<5>(a, W, s);
+    case 6: return launch_k<6>(a, W, s);
+    case 7:
+    case 8: return launch_k<8>(a, W, s);
+    case 9:
+    case 10: return launch_k<10>(a, W, s);
+    case 11:
+    case 12: return launch_k<12>(a, W, s);
+  }
   return launch_k<15>(a, W, s);
 }
 
