@@ -18,9 +18,9 @@
 // Bound by: a launch, the chain of a layer's 16 to 18 matrix instructions at one wave each and
 // three barriers, not by the matrix cores or memory.  Weights and gradient operands lie in
 // the order in which the lanes load them (fragment); by rows, each load touched a line a lane:
-// k_net 13.5 and 22.3 us, k_wgrad 16.1, now 10.6, 17.9 and 10.3.  Measured as a call: the
-// forward pass of 8,192 rows 48.5 us as five kernels through memory, now 23.5; loss and
-// gradients of 4,096 rows 136 us as sixteen, now 40.
+// k_net 13.5 and 22.3 us, k_wgrad 16.1, now 8.6, 16.0 and 8.2.  Measured as a call: the
+// forward pass of 8,192 rows 48.5 us as five kernels through memory, now 21.8; loss and
+// gradients of 4,096 rows 136 us as sixteen, now 37.
 #include <string.h>
 
 #include <algorithm>
@@ -135,12 +135,13 @@ __global__ void __launch_bounds__(kNetThreads, 2) k_net(int32_t B, int32_t tiles
   __shared__ __align__(16) uint16_t sx[kRows * kXStride];  // X, then dZ2
   __shared__ __align__(16) uint16_t sa[kRows * kAStride];  // A1
   __shared__ __align__(16) uint16_t sb[kRows * kAStride];  // A2
-  __shared__ float w3[kHidden], sdz[kRows], sloss[kRows];
+  __shared__ __align__(16) float w3[kHidden];
+  __shared__ float sdz[kRows], sloss[kRows];
   const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
   const int c = lane & 31, half = lane >> 5;
   const int n = 32 * wave + c;  // the lane's hidden unit
   if (t < kHidden) w3[t] = from_bf16(w3b[t]);
-  const float b1 = P[kOffB1 + n], b2 = P[kOffB2 + n];
+  const float b1 = P[kOffB1 + n], b2 = P[kOffB2 + n], b3 = P[kOffB3];
   float g1 = 0.0f, g2 = 0.0f, g3 = 0.0f, gb3 = 0.0f, gl = 0.0f;  // column sums
   Weights<kIn> w1;
   Weights<kHidden> w2;
@@ -195,32 +196,36 @@ __global__ void __launch_bounds__(kNetThreads, 2) k_net(int32_t B, int32_t tiles
       for (int e = 0; e < 4; ++e)
         sb[(8 * q + 4 * half + e) * kAStride + n] = activate<kTrain>(acc[4 * q + e] + b2);
     __syncthreads();
-    // layer 3: one thread a row, k ascending
-    if (t < kRows) {
+    // layer 3: 16 threads a row, 16 hidden units each, then pairwise (a thread a row took 5,200
+    // of the forward pass's 16,000 cycles)
+    {
+      const int r = t / 16, k0 = 16 * (t % 16);
       float z = 0.0f;
-#pragma unroll 4
-      for (int q = 0; q < kHidden / 8; ++q) {
-        const uint4 w = *reinterpret_cast<const uint4*>(sb + t * kAStride + 8 * q);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const uint4 w = *reinterpret_cast<const uint4*>(sb + r * kAStride + k0 + 8 * q);
         const uint32_t h[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          z += __uint_as_float(h[e] << 16) * w3[8 * q + 2 * e];
-          z += __uint_as_float(h[e] & 0xffff0000u) * w3[8 * q + 2 * e + 1];
+          z += __uint_as_float(h[e] << 16) * w3[k0 + 8 * q + 2 * e];
+          z += __uint_as_float(h[e] & 0xffff0000u) * w3[k0 + 8 * q + 2 * e + 1];
         }
       }
-      z += P[kOffB3];
-      const int64_t row = row0 + t;
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) z += __shfl_xor(z, o, kWave);
+      z += b3;
+      const int64_t row = row0 + r;
       if (!kTrain) {
-        if (row < B) logits[row] = z;
-      } else {
+        if (t % 16 == 0 && row < B) logits[row] = z;
+      } else if (t % 16 == 0) {
         float dz = 0.0f, l = 0.0f;
         if (row < B) {
           const float yb = y[row];
           dz = (1.0f / (1.0f + expf(-z)) - yb) / (float)B;
           l = (fmaxf(z, 0.0f) - z * yb + log1pf(expf(-fabsf(z)))) / (float)B;
         }
-        sdz[t] = dz;
-        sloss[t] = l;
+        sdz[r] = dz;
+        sloss[r] = l;
       }
     }
     if (!kTrain) return;  // one tile a workgroup
@@ -244,11 +249,16 @@ __global__ void __launch_bounds__(kNetThreads, 2) k_net(int32_t B, int32_t tiles
         *reinterpret_cast<uint4*>(out.dZ2T + fragment(col, row0 + r0 + 8 * q, out.steps)) =
             make_uint4(v[8 * q] | (uint32_t)v[8 * q + 1] << 16, v[8 * q + 2] | (uint32_t)v[8 * q + 3] << 16,
                        v[8 * q + 4] | (uint32_t)v[8 * q + 5] << 16, v[8 * q + 6] | (uint32_t)v[8 * q + 7] << 16);
-      if (t == 0)
-        for (int r = 0; r < kRows; ++r) {
-          gb3 += sdz[r];
-          gl += sloss[r];
+      if (t < kRows) {  // pairwise over the rows (thread 0's sums count)
+        float d = sdz[t], l = sloss[t];
+#pragma unroll
+        for (int o = kRows / 2; o > 0; o >>= 1) {
+          d += __shfl_xor(d, o, kWave);
+          l += __shfl_xor(l, o, kWave);
         }
+        gb3 += d;
+        gl += l;
+      }
     }
     __syncthreads();
     // dZ1 = bf16(dZ2 W2^T [Z1 > 0]): element (k, n) of W2^T is W2b[n][k]
@@ -544,9 +554,10 @@ int enqueue_training(pirrt_mlp* N, int32_t B, const float* xd, const float* yd, 
   const int32_t tiles = row_tiles(B), groups = std::min(tiles, (int32_t)kNetGroups);
   hipLaunchKernelGGL(k_net<true>, dim3((unsigned)groups), dim3(kNetThreads), 0, s, B, tiles, N->in_dim, xd, N->W1t,
                      N->W2t, N->W2b, N->w3b, N->P, yd, nullptr, N->T);
-  // splits of at least 256 rows: enough workgroups to fill the chip, few partial sums
+  // splits of at least 256 rows; up to 8,192 rows eight of them (136 workgroups, half the partial
+  // sums to write: 8.2 us for 4,096 rows, 10.0 with 16), beyond that enough to fill the chip
   const int64_t steps = (int64_t)tiles * (kRows / 16);
-  const int64_t want = std::min<int64_t>(kSplits, (steps + 15) / 16), per = (steps + want - 1) / want;
+  const int64_t want = std::min<int64_t>(steps > 512 ? kSplits : kSplits / 2, (steps + 15) / 16), per = (steps + want - 1) / want;
   const int splits = (int)((steps + per - 1) / per);
   hipLaunchKernelGGL(k_wgrad, dim3(kGradRows / 32, (unsigned)splits), dim3(kThreads), 0, s, steps, per, N->T, N->part);
   const dim3 grid((unsigned)(kGradRows * kHidden / kThreads + (kColSums * 8 + kThreads - 1) / kThreads));
