@@ -39,6 +39,13 @@ struct HostBlock {
   float state[4 * kHostState];  // the host Replan's state of up to kHostState vertices
 };
 
+// The one-launch Replan's heuristic: in caller order, device memory to be checked or pinned
+// memory that is checked already.
+struct RawH {
+  const float* h;
+  bool check;
+};
+
 // Validation kernels for device-resident inputs of replan / set_policy.
 
 // parent ids are local to the problem [base, base + len) of each vertex.
@@ -161,6 +168,7 @@ struct pirrt_graph {
   // pinned g, pcost, h (floats) and parent of hpin_cap vertices: the host Replan's state where
   // the host block's is too small
   float* hpin = nullptr;
+  float* rpin = nullptr;  // pinned h, g and parents of the one-launch Replan, kResidentMax each
   int64_t hpin_cap = 0;
   // host copies of the slot-ordered adjacency and ids for the host Replan
   uint64_t hm_version = ~0ull;
@@ -569,6 +577,8 @@ void release_all(pirrt_graph* G) {
   G->hps = nullptr;
   if (G->hpin) (void)hipHostFree(G->hpin);
   G->hpin = nullptr;
+  if (G->rpin) (void)hipHostFree(G->rpin);
+  G->rpin = nullptr;
   raw_free(G->A, G->scan_scratch);
   G->scan_scratch = nullptr;
   G->arena.release();
@@ -1258,6 +1268,17 @@ int row_variant(const pirrt_graph* G, bool pull) {
 constexpr int64_t kJumpMax = (int64_t)1 << 19;
 constexpr int64_t kJumpIterations = 16;
 
+// Pinned room of the one-launch Replan's heuristic, g and parents (allocated when first
+// needed).
+int ensure_resident_pin(pirrt_graph* G) {
+  if (G->rpin) return PIRRT_OK;
+  if (hipHostMalloc((void**)&G->rpin, 3 * sizeof(float) * (size_t)kResidentMax, hipHostMallocDefault) == hipSuccess)
+    return PIRRT_OK;
+  (void)hipGetLastError();
+  G->rpin = nullptr;
+  return fail(G, PIRRT_ENOMEM, "allocation of pinned memory for the Replan's results failed");
+}
+
 // Statistics and return code of a Replan done in one launch, from its final state.
 int finish_single(pirrt_graph* G, const ProblemState& q, std::chrono::steady_clock::time_point t_start,
                   pirrt_stats* stats) {
@@ -1281,10 +1302,11 @@ int finish_single(pirrt_graph* G, const ProblemState& q, std::chrono::steady_clo
 // Runs Replan for P problems with the given root ids and root / goal slots.  h is
 // a device array in slot order (or NULL).  Fills per-problem stats (P entries,
 // nullable).  out (nullable): the policy copy-out is enqueued before the final wait,
-// so a call waits for the device once at its end.
+// so a call waits for the device once at its end.  raw (one-launch Replan only, with h ==
+// hbuf): the heuristic is brought to h by the set-up kernel.
 int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t* root_slots,
                const int32_t* goal_slots, const float* h, bool prune, bool timing, pirrt_stats* stats,
-               const PolicyOut* out = nullptr) {
+               const PolicyOut* out = nullptr, const RawH* raw = nullptr) {
   hipStream_t s = G->stream;
   int rc;
   auto t_start = std::chrono::steady_clock::now();
@@ -1302,8 +1324,11 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
   }
   if (P == 1 && !G->batched) {
     // one launch from scalar arguments: no host-to-device copies on the latency path
+    G->host->flag = 0;
     launch_replan_init_single(G->ps, root_slots[0], goal_slots[0], G->hps[0].cap, root_ids[0], G->nroots, G->droots,
-                              G->slot_of, G->parent, G->pcost, G->ctr, G->ctl, G->g, prune ? 1 : 0, G->rsync, G->fault_gate ? 2u : 0u, s);
+                              G->slot_of, G->parent, G->pcost, G->ctr, G->ctl, G->g, prune ? 1 : 0, G->rsync,
+                              G->fault_gate ? 2u : 0u, n, raw ? raw->h : nullptr, G->hbuf,
+                              raw && raw->check ? &G->host->flag : nullptr, s);
     G->fault_gate = false;
   } else {
     HIP_OR_FAIL(G, hipMemcpyAsync(G->ps, G->hps, sizeof(ProblemState) * (size_t)P, hipMemcpyHostToDevice, s));
@@ -1312,8 +1337,11 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
     HIP_OR_FAIL(G, hipMemcpyAsync(G->droots, root_ids, sizeof(int32_t) * (size_t)P, hipMemcpyHostToDevice, s));
     launch_replan_init(P, G->ps, G->parent, G->pcost, G->ctr, G->ctl, G->g, prune ? 1 : 0, s);
   }
-  G->nroots = P;
-  G->hroots.assign(root_ids, root_ids + P);
+  auto roots_moved = [&] {
+    G->nroots = P;
+    G->hroots.assign(root_ids, root_ids + P);
+  };
+  if (!raw) roots_moved();  // (with raw: once the heuristic is known to be good)
   HIP_OR_FAIL(G, hipGetLastError());
   if (G->fault_launch) {  // injected failure: behave as a failed launch would
     G->fault_launch = false;
@@ -1409,14 +1437,24 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
     ra.prune = prune ? 1 : 0;
     ra.lookahead = G->lookahead;
     ra.tree = G->tree;
+    ra.slot_of = G->slot_of;
+    const bool to_host = out && out->mem_kind == PIRRT_MEM_HOST;
+    ra.g_out = !out || !out->g ? nullptr : to_host ? G->rpin + kResidentMax : out->g;
+    ra.parent_out = !out || !out->parent ? nullptr
+                    : to_host            ? reinterpret_cast<int32_t*>(G->rpin + 2 * kResidentMax)
+                                         : out->parent;
+    ra.report = G->hps;  // (active until then)
     HIP_OR_FAIL(G, launch_replan_resident(ra, s));
-    if (out && (out->g || out->parent)) {
-      if ((rc = policy_out(G, out->g, out->parent, nullptr, out->mem_kind, G->hps))) return rc;
-    } else {
-      HIP_OR_FAIL(G, hipMemcpyAsync(G->hps, G->ps, sizeof(ProblemState), hipMemcpyDeviceToHost, s));
-    }
     HIP_OR_FAIL(G, hipStreamSynchronize(s));
+    if (raw) {
+      if (G->host->flag) return fail(G, PIRRT_EINVAL, "h has a NaN or negative entry");
+      roots_moved();
+    }
     const ProblemState& q = G->hps[0];
+    if (to_host && !q.active && q.status != 2) {
+      if (out->g) memcpy(out->g, ra.g_out, sizeof(float) * (size_t)n);
+      if (out->parent) memcpy(out->parent, ra.parent_out, sizeof(int32_t) * (size_t)n);
+    }
     if (q.status == 2) return fail_device(G, hipErrorUnknown, "the resident Replan's barrier did not complete");
     if (!q.active) return finish_single(G, q, t_start, stats);
     // its workgroups did not all become resident and left: the loop does the Replan
@@ -2010,14 +2048,29 @@ int pirrt_replan(pirrt_graph* G, int32_t root, int32_t goal, const float* h, uin
   }
   if (G->renumber_due && (flags & (PIRRT_TIMING | PIRRT_TRUNCATED)) && (rc = renumber(G))) return rc;  // the loop
   const float* hdev = nullptr;
-  if ((rc = stage_h(G, h, mem_kind, &hdev))) return rc;
+  RawH raw{nullptr, false};
+  const bool one_launch = resident_size(G) && !(flags & (PIRRT_TIMING | PIRRT_TRUNCATED));
+  if (one_launch && mem_kind == PIRRT_MEM_HOST && (rc = ensure_resident_pin(G))) return rc;
+  if (h && one_launch) {
+    raw = {h, mem_kind == PIRRT_MEM_DEVICE};
+    hdev = G->hbuf;
+    if (!raw.check) {
+      for (int64_t v = 0; v < G->n; ++v) {
+        if (!(h[v] >= 0.0f)) return fail(G, PIRRT_EINVAL, "h has a NaN or negative entry");
+        G->rpin[v] = h[v];
+      }
+      raw.h = G->rpin;
+    }
+  } else if ((rc = stage_h(G, h, mem_kind, &hdev))) {
+    return rc;
+  }
   const int32_t rslot = G->hslot[(size_t)root], gslot = G->hslot[(size_t)goal];
   pirrt_stats st;
   G->lookahead = (flags & PIRRT_LOOKAHEAD) != 0;
   G->truncated = (flags & PIRRT_TRUNCATED) != 0;
   const PolicyOut po{g_out, parent_out, mem_kind};
   rc = run_replan(G, 1, &root, &rslot, &gslot, hdev, (flags & PIRRT_NO_PRUNE) == 0, (flags & PIRRT_TIMING) != 0,
-                  &st, &po);
+                  &st, &po, raw.h ? &raw : nullptr);
   if (rc != PIRRT_OK && rc != PIRRT_ENOTCONVERGED) return rc;
   if (stats) *stats = st;
   return rc;

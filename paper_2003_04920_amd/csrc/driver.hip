@@ -50,23 +50,47 @@ __global__ void k_replan_init(int32_t P, ProblemState* __restrict__ ps, int32_t*
 // roots (caller ids in droots[0..nold)) lose their mark, the new root gets it and is
 // recorded in droots[0], and the problem state starts from the kernel arguments.
 // Otherwise as k_replan_init.
-__global__ void __launch_bounds__(kCounterSlots) k_replan_init_single(
+// h_in (nullable; one-launch Replan): the heuristic in caller order, brought into slot order
+// here.  bad (nullable, pinned): h_in is checked, and if a value is negative or NaN, *bad is
+// set, the problem is inactive and nothing else changed.
+constexpr int kInitThreads = 1024;
+
+__global__ void __launch_bounds__(kInitThreads) k_replan_init_single(
     ProblemState* __restrict__ ps, int32_t root, int32_t goal, int32_t cap, int32_t root_id, int32_t nold,
     int32_t* __restrict__ droots, const int32_t* __restrict__ slot_of, int32_t* __restrict__ parent,
     float* __restrict__ pcost, IterCounters* __restrict__ ctr, LoopCtl* __restrict__ ctl, const float* __restrict__ g,
-    int prune, ResidentSync* __restrict__ sync, uint32_t gate) {
+    int prune, ResidentSync* __restrict__ sync, uint32_t gate, int32_t n, const float* __restrict__ h_in,
+    float* __restrict__ h, int32_t* __restrict__ bad) {
   const int t = threadIdx.x;
+  if (h_in) {
+    int wrong = 0;
+    for (int32_t e = t; e < n; e += kInitThreads) {
+      const float x = h_in[e];
+      h[slot_of[e]] = x;
+      wrong |= !(x >= 0.0f);
+    }
+    if (bad && __syncthreads_or(wrong)) {
+      if (t == 0) {
+        *bad = 1;
+        ps[0].active = 0;
+      }
+      return;
+    }
+  }
   if (t < 4) sync->word[t][0] = 0ull;
   if (t == 0) {
     sync->arrived = 0u;
     sync->gate = gate;
+    sync->done = 0u;
   }
-  IterCounters& c = ctr[t];
-  c.changed = 0;
-  c.nP = 0;
-  c.nD = 0;
-  c.pedges = 0;
-  c.edges = 0ull;
+  if (t < kCounterSlots) {
+    IterCounters& c = ctr[t];
+    c.changed = 0;
+    c.nP = 0;
+    c.nD = 0;
+    c.pedges = 0;
+    c.edges = 0ull;
+  }
   if (t == 0) {
     for (int32_t i = 0; i < nold; ++i) {  // in order, before the new mark (a root may repeat)
       const int32_t s = slot_of[droots[i]];
@@ -319,9 +343,9 @@ void launch_replan_init(int32_t P, ProblemState* ps, int32_t* parent, float* pco
 void launch_replan_init_single(ProblemState* ps, int32_t root, int32_t goal, int32_t cap, int32_t root_id,
                                int32_t nold, int32_t* droots, const int32_t* slot_of, int32_t* parent, float* pcost,
                                IterCounters* ctr, LoopCtl* ctl, const float* g, int prune, ResidentSync* sync,
-                               uint32_t gate, hipStream_t s) {
-  hipLaunchKernelGGL(k_replan_init_single, dim3(1), dim3(kCounterSlots), 0, s, ps, root, goal, cap, root_id, nold,
-                     droots, slot_of, parent, pcost, ctr, ctl, g, prune, sync, gate);
+                               uint32_t gate, int32_t n, const float* h_in, float* h, int32_t* bad, hipStream_t s) {
+  hipLaunchKernelGGL(k_replan_init_single, dim3(1), dim3(h_in ? kInitThreads : kCounterSlots), 0, s, ps, root, goal, cap, root_id, nold,
+                     droots, slot_of, parent, pcost, ctr, ctl, g, prune, sync, gate, n, h_in, h, bad);
 }
 
 void launch_finish(int32_t P, ProblemState* ps, IterCounters* ctr, LoopCtl* ctl, bool single, hipStream_t s) {

@@ -269,7 +269,7 @@ void launch_replan_init(int32_t P, ProblemState* ps, int32_t* parent, float* pco
 void launch_replan_init_single(ProblemState* ps, int32_t root, int32_t goal, int32_t cap, int32_t root_id,
                                int32_t nold, int32_t* droots, const int32_t* slot_of, int32_t* parent, float* pcost,
                                IterCounters* ctr, LoopCtl* ctl, const float* g, int prune, ResidentSync* sync,
-                               uint32_t gate, hipStream_t s);
+                               uint32_t gate, int32_t n, const float* h_in, float* h, int32_t* bad, hipStream_t s);
 // single: one graph (P == 1, no problem map); see launch_after_eval.
 void launch_finish(int32_t P, ProblemState* ps, IterCounters* ctr, LoopCtl* ctl, bool single, hipStream_t s);
 // prob / base / tiles: a batch's problem map, its problems' slot ranges (P + 1
@@ -336,8 +336,8 @@ constexpr int kResidentGroups = 128;  // workgroups at most
 constexpr int64_t kResidentLists = 2 * (kResidentMax + 2 * kResidentGroups);
 static_assert(kResidentLists * 8 >= (int64_t)kInsertScratch, "inserts use the lists' room");
 struct ResidentSync {  // cleared by the single graph's set-up kernel
-  uint32_t arrived, gate;
-  uint32_t pad[30];
+  uint32_t arrived, gate, done;
+  uint32_t pad[29];
   unsigned long long word[4][16];  // a 128-byte line each
 };
 struct ResidentArgs {
@@ -356,6 +356,11 @@ struct ResidentArgs {
   int prune;
   bool lookahead;
   bool tree;  // the stored policy has no cycle: Evaluate may start from the stored g
+  // results (nullable): g and parent in caller order, device or pinned host memory
+  const int32_t* slot_of;
+  float* g_out;
+  int32_t* parent_out;
+  ProblemState* report;  // pinned: *ps at the end, left alone if the workgroups did not all run
 };
 hipError_t launch_replan_resident(ResidentArgs a, hipStream_t s);
 void launch_mark(const StepArgs& a, int variant, hipStream_t s);

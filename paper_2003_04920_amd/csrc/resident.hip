@@ -31,6 +31,12 @@
 // for its stores before its workgroup arrives.  So no cache is written back or
 // invalidated, and the adjacency stays in them.
 //
+// Results: every workgroup has every vertex, so each writes a range of caller ids to the
+// caller's arrays, and the one that is done last the counters to host memory; the set-up kernel
+// before brings the heuristic into storage order and checks it.  Two launches and one wait a
+// call (2,002 2D vertices 193 -> 173 us; a check, a gather, a copy-out kernel, three copies and
+// a wait more before).
+//
 // Residency: nothing is written before all workgroups have met at a gate.  A workgroup
 // that waits there too long (others hold the chip) closes the gate; then every workgroup
 // leaves, the problem stays active and the host runs the multi-kernel loop.  Past the gate
@@ -126,6 +132,7 @@ __global__ void __launch_bounds__(kResThreads) k_replan_resident(ResidentArgs a)
   uint16_t* par = reinterpret_cast<uint16_t*>(pc + N);
   const int t = threadIdx.x, lane = t & (kWave - 1);
   const uint32_t W = gridDim.x;
+  if (a.ps->active == 0) return;  // the heuristic was refused
   if (!gate(a.sync, W)) return;
   const int32_t n = a.n, R = a.rows;
   const int32_t first = (int32_t)blockIdx.x * R;
@@ -369,6 +376,12 @@ __global__ void __launch_bounds__(kResThreads) k_replan_resident(ResidentArgs a)
       a.pcost[v] = pc[v];
     }
   }
+  // the caller's copy: every workgroup has every vertex, so it takes caller ids in a row
+  for (int i = t; i < own; i += kResThreads) {
+    const int32_t e = first + i, v = a.slot_of[e];
+    if (a.g_out) a.g_out[e] = fabsf(g[v]);
+    if (a.parent_out) a.parent_out[e] = par[v] != 4 * v ? a.ext_of[par[v] / 4] : -1;
+  }
   unsigned long long sp = (unsigned)sum_p, sd = (unsigned)sum_d;
 #pragma unroll
   for (int o = kWave / 2; o > 0; o >>= 1) {
@@ -383,13 +396,24 @@ __global__ void __launch_bounds__(kResThreads) k_replan_resident(ResidentArgs a)
     atomicAdd(&a.ps->edges, sum_e);
     atomicAdd(&a.ps->mark_edges, sum_pe);
   }
-  if (blockIdx.x == 0 && t == 0) {
-    a.ps->iterations = iters;
-    a.ps->status = status;
-    a.ps->active = 0;
-    a.ps->needs_eval = 0;
-    a.ps->changed_total = (unsigned long long)chg_sum;
-  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's sums are in
+  __syncthreads();
+  if (t != 0) return;
+  // the workgroup that is done last has all sums and reports them (all agree on the rest)
+  if (__hip_atomic_fetch_add(&a.sync->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != W - 1) return;
+  ProblemState q = {};
+  q.root = root;
+  q.goal = goal;
+  q.iterations = iters;
+  q.status = status;
+  q.cap = cap;
+  q.edges = load_agent(&a.ps->edges);
+  q.sum_P = load_agent(&a.ps->sum_P);
+  q.sum_D = load_agent(&a.ps->sum_D);
+  q.mark_edges = load_agent(&a.ps->mark_edges);
+  q.changed_total = (unsigned long long)chg_sum;
+  *a.ps = q;
+  *a.report = q;
 }
 
 template <int K>
