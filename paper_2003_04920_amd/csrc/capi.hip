@@ -39,8 +39,9 @@ struct HostBlock {
   float state[4 * kHostState];  // the host Replan's state of up to kHostState vertices
 };
 
-// The one-launch Replan's heuristic: in caller order, device memory to be checked or pinned
-// memory that is checked already.
+// A heuristic whose check is still on its way when a Replan is enqueued.  h: the one-launch
+// Replan's, in caller order (device memory to be checked, pinned memory that is checked
+// already); NULL: the loop's, brought over by a kernel that sets the flag.
 struct RawH {
   const float* h;
   bool check;
@@ -1302,8 +1303,8 @@ int finish_single(pirrt_graph* G, const ProblemState& q, std::chrono::steady_clo
 // Runs Replan for P problems with the given root ids and root / goal slots.  h is
 // a device array in slot order (or NULL).  Fills per-problem stats (P entries,
 // nullable).  out (nullable): the policy copy-out is enqueued before the final wait,
-// so a call waits for the device once at its end.  raw (one-launch Replan only, with h ==
-// hbuf): the heuristic is brought to h by the set-up kernel.
+// so a call waits for the device once at its end.  raw (nullable): h is hbuf and its check not
+// through yet (see RawH).
 int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t* root_slots,
                const int32_t* goal_slots, const float* h, bool prune, bool timing, pirrt_stats* stats,
                const PolicyOut* out = nullptr, const RawH* raw = nullptr) {
@@ -1324,7 +1325,6 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
   }
   if (P == 1 && !G->batched) {
     // one launch from scalar arguments: no host-to-device copies on the latency path
-    G->host->flag = 0;
     launch_replan_init_single(G->ps, root_slots[0], goal_slots[0], G->hps[0].cap, root_ids[0], G->nroots, G->droots,
                               G->slot_of, G->parent, G->pcost, G->ctr, G->ctl, G->g, prune ? 1 : 0, G->rsync,
                               G->fault_gate ? 2u : 0u, n, raw ? raw->h : nullptr, G->hbuf,
@@ -1341,7 +1341,15 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
     G->nroots = P;
     G->hroots.assign(root_ids, root_ids + P);
   };
-  if (!raw) roots_moved();  // (with raw: once the heuristic is known to be good)
+  if (!raw) roots_moved();
+  // with raw: at the first wait, when the check is through
+  auto settle_h = [&]() -> int {
+    if (!raw) return PIRRT_OK;
+    raw = nullptr;
+    if (G->host->flag) return fail(G, PIRRT_EINVAL, "h has a NaN or negative entry");
+    roots_moved();
+    return PIRRT_OK;
+  };
   HIP_OR_FAIL(G, hipGetLastError());
   if (G->fault_launch) {  // injected failure: behave as a failed launch would
     G->fault_launch = false;
@@ -1446,10 +1454,7 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
     ra.report = G->hps;  // (active until then)
     HIP_OR_FAIL(G, launch_replan_resident(ra, s));
     HIP_OR_FAIL(G, hipStreamSynchronize(s));
-    if (raw) {
-      if (G->host->flag) return fail(G, PIRRT_EINVAL, "h has a NaN or negative entry");
-      roots_moved();
-    }
+    if ((rc = settle_h())) return rc;
     const ProblemState& q = G->hps[0];
     if (to_host && !q.active && q.status != 2) {
       if (out->g) memcpy(out->g, ra.g_out, sizeof(float) * (size_t)n);
@@ -1461,7 +1466,7 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
   }
 
   // the multi-kernel loop's marks: no stamp older than this Replan
-  HIP_OR_FAIL(G, hipMemsetAsync(G->stamp, 0, (size_t)n, s));
+  if (!L.sa.pull) HIP_OR_FAIL(G, hipMemsetAsync(G->stamp, 0, (size_t)n, s));
   pirrt_stats agg;
   memset(&agg, 0, sizeof(agg));
   // Without room for the records, link by link.
@@ -1492,6 +1497,26 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
   if (G->truncated) G->tree = false;  // stale g could close a cycle
   const bool direct = timing || G->trace || !G->use_graph;
   int64_t done_iters = 0;
+  bool delivered = false;  // the policy and the state came with the loop's last wait
+  // The loop's wait: `last` (the planned iterations are through) fetches the results too, which
+  // saves a round trip when it really was the last.
+  auto wait_loop = [&](bool last) -> int {
+    int r;
+    if (last) {
+      if (out && (out->g || out->parent)) {
+        if ((r = policy_out(G, out->g, out->parent, nullptr, out->mem_kind, P == 1 ? G->hps : nullptr))) return r;
+      }
+      if (P > 1 || !(out && (out->g || out->parent)))
+        HIP_OR_FAIL(G, hipMemcpyAsync(G->hps, G->ps, sizeof(ProblemState) * (size_t)P, hipMemcpyDeviceToHost, s));
+    }
+    if (P > 1 || !last)
+      HIP_OR_FAIL(G, hipMemcpyAsync(&G->host->ctl, G->ctl, sizeof(LoopCtl), hipMemcpyDeviceToHost, s));
+    HIP_OR_FAIL(G, hipStreamSynchronize(s));
+    if ((r = settle_h())) return r;
+    if (P == 1 && last) G->host->ctl.any_active = G->hps[0].active;
+    delivered = last && !G->host->ctl.any_active;
+    return PIRRT_OK;
+  };
   if (direct) {
     for (int it = 0;; ++it) {
       take_jumps(it);
@@ -1504,6 +1529,7 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
         HIP_OR_FAIL(G, hipMemcpyAsync(G->hps, G->ps, sizeof(ProblemState) * (size_t)P, hipMemcpyDeviceToHost, s));
       }
       HIP_OR_FAIL(G, hipStreamSynchronize(s));
+      if ((rc = settle_h())) return rc;
       ++done_iters;
       if (timing) {
         agg.ms_mark += elapsed_ms(G->ev[2], G->ev[3]);
@@ -1541,6 +1567,7 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
     G->prev_key = key1;
     G->have_prev_key = true;
     int64_t plan = G->last_iterations > 0 ? G->last_iterations : 8;
+    bool planned = G->last_iterations > 0;
     for (;;) {
       const int k = plan >= 8 ? 3 : plan >= 4 ? 2 : plan >= 2 ? 1 : 0;
       take_jumps(done_iters);
@@ -1555,20 +1582,14 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
       done_iters += 1 << k;
       plan -= 1 << k;
       if (plan > 0) continue;
-      HIP_OR_FAIL(G, hipMemcpyAsync(&G->host->ctl, G->ctl, sizeof(LoopCtl), hipMemcpyDeviceToHost, s));
-      HIP_OR_FAIL(G, hipStreamSynchronize(s));
+      if ((rc = wait_loop(planned))) return rc;
+      planned = false;
       if (!G->host->ctl.any_active) break;
       if (done_iters > cap_iters + 8) return fail_device(G, hipErrorUnknown, "Replan loop did not stop");
       plan = 1;
     }
   }
-  const bool reported = P == 1 && out && (out->g || out->parent);
-  if (out && (out->g || out->parent) &&
-      (rc = policy_out(G, out->g, out->parent, nullptr, out->mem_kind, reported ? G->hps : nullptr)))
-    return rc;
-  if (!reported)
-    HIP_OR_FAIL(G, hipMemcpyAsync(G->hps, G->ps, sizeof(ProblemState) * (size_t)P, hipMemcpyDeviceToHost, s));
-  HIP_OR_FAIL(G, hipStreamSynchronize(s));
+  if (!delivered && (rc = wait_loop(true))) return rc;
   int32_t most = 0;
   bool capped = false;
   const double ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t_start).count();
@@ -1712,8 +1733,10 @@ int run_host_replan(pirrt_graph* G, int32_t root, int32_t goal, const float* h, 
 }
 
 // Copies and validates a caller h (caller order) into slot order in hbuf.
-int stage_h(pirrt_graph* G, const float* h, int mem_kind, const float** out) {
+// deferred: a device h's check is left to the caller, in the host block's flag.
+int stage_h(pirrt_graph* G, const float* h, int mem_kind, const float** out, bool deferred = false) {
   *out = nullptr;
+  G->host->flag = 0;
   if (!h) return PIRRT_OK;
   const int32_t n = (int32_t)G->n;
   hipStream_t s = G->stream;
@@ -1725,9 +1748,10 @@ int stage_h(pirrt_graph* G, const float* h, int mem_kind, const float** out) {
     HIP_OR_FAIL(G, hipMemcpyAsync(G->g2, h, sizeof(float) * (size_t)n, hipMemcpyHostToDevice, s));
     hsrc = G->g2;
   } else {
-    G->host->flag = 0;
     launch_gather_by_slot(n, G->ext_of, hsrc, G->hbuf, &G->host->flag, s);
     HIP_OR_FAIL(G, hipGetLastError());
+    *out = G->hbuf;
+    if (deferred) return PIRRT_OK;
     HIP_OR_FAIL(G, hipStreamSynchronize(s));
     if (G->host->flag) return fail(G, PIRRT_EINVAL, "h has a NaN or negative entry");
     *out = G->hbuf;
@@ -2049,6 +2073,7 @@ int pirrt_replan(pirrt_graph* G, int32_t root, int32_t goal, const float* h, uin
   if (G->renumber_due && (flags & (PIRRT_TIMING | PIRRT_TRUNCATED)) && (rc = renumber(G))) return rc;  // the loop
   const float* hdev = nullptr;
   RawH raw{nullptr, false};
+  G->host->flag = 0;
   const bool one_launch = resident_size(G) && !(flags & (PIRRT_TIMING | PIRRT_TRUNCATED));
   if (one_launch && mem_kind == PIRRT_MEM_HOST && (rc = ensure_resident_pin(G))) return rc;
   if (h && one_launch) {
@@ -2061,8 +2086,9 @@ int pirrt_replan(pirrt_graph* G, int32_t root, int32_t goal, const float* h, uin
       }
       raw.h = G->rpin;
     }
-  } else if ((rc = stage_h(G, h, mem_kind, &hdev))) {
-    return rc;
+  } else {
+    raw.check = h && mem_kind == PIRRT_MEM_DEVICE;
+    if ((rc = stage_h(G, h, mem_kind, &hdev, raw.check))) return rc;
   }
   const int32_t rslot = G->hslot[(size_t)root], gslot = G->hslot[(size_t)goal];
   pirrt_stats st;
@@ -2070,7 +2096,7 @@ int pirrt_replan(pirrt_graph* G, int32_t root, int32_t goal, const float* h, uin
   G->truncated = (flags & PIRRT_TRUNCATED) != 0;
   const PolicyOut po{g_out, parent_out, mem_kind};
   rc = run_replan(G, 1, &root, &rslot, &gslot, hdev, (flags & PIRRT_NO_PRUNE) == 0, (flags & PIRRT_TIMING) != 0,
-                  &st, &po, raw.h ? &raw : nullptr);
+                  &st, &po, raw.h || raw.check ? &raw : nullptr);
   if (rc != PIRRT_OK && rc != PIRRT_ENOTCONVERGED) return rc;
   if (stats) *stats = st;
   return rc;

@@ -25,6 +25,8 @@ struct IterCounters {
 };
 
 // Replan state of one problem (a graph, or one graph of a batch) on the device.
+constexpr int32_t kRefused = 3;  // a status: the heuristic had a negative or NaN value
+
 struct ProblemState {
   int32_t root;        // slot of x_init
   int32_t goal;        // slot of x_goal
@@ -32,7 +34,7 @@ struct ProblemState {
   int32_t active;      // still iterating
   int32_t needs_eval;  // Evaluate after the current Improve
   int32_t iterations;  // Improve passes so far
-  int32_t status;      // 0 running / converged, 1 iteration cap reached
+  int32_t status;      // 0 running / converged, 1 iteration cap reached, kRefused
   int32_t cap;         // iteration cap
   unsigned long long edges, sum_P, sum_D, changed_total;
   unsigned long long mark_edges;  // sum over iterations of the promising rows' degrees

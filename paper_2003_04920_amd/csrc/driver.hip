@@ -51,8 +51,9 @@ __global__ void k_replan_init(int32_t P, ProblemState* __restrict__ ps, int32_t*
 // recorded in droots[0], and the problem state starts from the kernel arguments.
 // Otherwise as k_replan_init.
 // h_in (nullable; one-launch Replan): the heuristic in caller order, brought into slot order
-// here.  bad (nullable, pinned): h_in is checked, and if a value is negative or NaN, *bad is
-// set, the problem is inactive and nothing else changed.
+// here.  bad (nullable, pinned): set here if a value of h_in is negative or NaN, or by the
+// kernel that brought the heuristic over; the problem is then refused: inactive (so that what
+// is enqueued behind does nothing), its policy and roots as they were.
 constexpr int kInitThreads = 1024;
 
 __global__ void __launch_bounds__(kInitThreads) k_replan_init_single(
@@ -62,20 +63,17 @@ __global__ void __launch_bounds__(kInitThreads) k_replan_init_single(
     int prune, ResidentSync* __restrict__ sync, uint32_t gate, int32_t n, const float* __restrict__ h_in,
     float* __restrict__ h, int32_t* __restrict__ bad) {
   const int t = threadIdx.x;
+  int wrong = 0;
   if (h_in) {
-    int wrong = 0;
     for (int32_t e = t; e < n; e += kInitThreads) {
       const float x = h_in[e];
       h[slot_of[e]] = x;
       wrong |= !(x >= 0.0f);
     }
-    if (bad && __syncthreads_or(wrong)) {
-      if (t == 0) {
-        *bad = 1;
-        ps[0].active = 0;
-      }
-      return;
-    }
+    wrong = bad && __syncthreads_or(wrong);
+    if (wrong && t == 0) *bad = 1;
+  } else if (bad) {
+    wrong = *bad;
   }
   if (t < 4) sync->word[t][0] = 0ull;
   if (t == 0) {
@@ -92,25 +90,26 @@ __global__ void __launch_bounds__(kInitThreads) k_replan_init_single(
     c.edges = 0ull;
   }
   if (t == 0) {
-    for (int32_t i = 0; i < nold; ++i) {  // in order, before the new mark (a root may repeat)
-      const int32_t s = slot_of[droots[i]];
-      if (parent[s] == kRootMark) parent[s] = -1;
+    if (!wrong) {
+      for (int32_t i = 0; i < nold; ++i) {  // in order, before the new mark (a root may repeat)
+        const int32_t s = slot_of[droots[i]];
+        if (parent[s] == kRootMark) parent[s] = -1;
+      }
+      droots[0] = root_id;
+      parent[root] = kRootMark;
+      pcost[root] = 0.0f;
     }
-    droots[0] = root_id;
-    parent[root] = kRootMark;
-    pcost[root] = 0.0f;
     ProblemState q = {};
     q.root = root;
     q.goal = goal;
     q.thr = prune ? g[goal] : pos_inf();
-    q.active = 1;
-    q.needs_eval = 1;
+    q.active = q.needs_eval = wrong ? 0 : 1;
+    q.status = wrong ? kRefused : 0;
     q.cap = cap;
     ps[0] = q;
     ctl->epoch = next_mark_epoch(ctl->epoch);
     ctl->eval_epoch = next_epoch(ctl->eval_epoch);
-    ctl->any_active = 1;
-    ctl->any_eval = 1;
+    ctl->any_active = ctl->any_eval = wrong ? 0 : 1;
     ctl->ntiles = -1;
     ctl->ndomain = 0;
     ctl->npromising = 0;

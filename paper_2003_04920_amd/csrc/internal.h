@@ -167,7 +167,7 @@ void launch_permute(const PermuteArgs& a, hipStream_t s);
 // bad (nullable, pinned host memory): set to 1 if a value is negative or NaN.
 void launch_gather_by_slot(int32_t n, const int32_t* ext_of, const float* src_ext, float* dst_slot, int32_t* bad,
                            hipStream_t s);
-// report (nullable, pinned host memory): *ps goes there.
+// report (nullable, pinned host memory): *ps goes there; a refused Replan copies nothing.
 // prob/base (nullable): parents are reported relative to the first id of the
 // vertex's problem.
 void launch_policy_to_ext(int32_t n, const int32_t* slot_of, const int32_t* ext_of, const int32_t* prob,

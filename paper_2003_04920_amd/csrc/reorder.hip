@@ -403,6 +403,7 @@ __global__ void __launch_bounds__(kThreads) k_policy_to_ext(int32_t n, const int
                                                            ProblemState* __restrict__ report) {
   int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (report && e == 0) *report = *ps;
+  if (report && ps->status == kRefused) return;
   if (e >= n) return;
   const int32_t s = slot_of[e];
   if (g_ext) g_ext[e] = g[s];

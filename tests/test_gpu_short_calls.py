@@ -67,3 +67,32 @@ def test_refused_heuristic_leaves_the_policy(P, n, bad):
     h[n - 1] = 0.0
     g, _, _ = G.replan(0, n - 1, h)
     assert float(g[n - 1]) == n - 1
+
+
+@pytest.mark.parametrize("kw", [dict(timing=True), dict(truncated=True), dict(lookahead=True), dict()])
+@pytest.mark.parametrize("n", [600, 20_000])
+def test_refused_in_every_mode(P, monkeypatch, n, kw):
+    """A device heuristic is checked while the Replan is enqueued: a refused one changes neither
+    the policy, nor the roots, nor the caller's arrays, and the next call is as if it had not been."""
+    import torch
+    rng = np.random.default_rng(n)
+    e = [(int(rng.integers(max(0, v - 50), v)), v, float(np.float32(rng.random()))) for v in range(1, n) for _ in range(3)]
+    b = W.from_edges(n, e)
+    G, H = P.Graph(), P.Graph()
+    for X in (G, H):
+        X.insert_rows(b)
+    good = torch.from_numpy((rng.random(n) * 0.1).astype(np.float32)).cuda()
+    bad = good.clone()
+    bad[n // 2] = -1.0
+    g_out = torch.full((n,), 7.0, device="cuda")
+    p_out = torch.full((n,), 7, dtype=torch.int32, device="cuda")
+    for root in (0, n // 3, 0):
+        before = [x.copy() for x in G.get_policy()]
+        with pytest.raises(P.PirrtError):
+            G.replan(n - 1, root, bad, True, g_out=g_out.fill_(7.0), parent_out=p_out.fill_(7), **kw)
+        assert bool((g_out == 7.0).all()) and bool((p_out == 7).all())
+        assert all(np.array_equal(x, y) for x, y in zip(before, G.get_policy()))
+        a = G.replan(root, n - 1, good, True, **kw)
+        c = H.replan(root, n - 1, good, True, **kw)
+        assert all(np.array_equal(x.cpu().numpy() if x.is_cuda else x, y.cpu().numpy()) for x, y in zip(a[:2], c[:2]))
+        assert a[2]["iterations"] == c[2]["iterations"] and a[2]["sum_P"] == c[2]["sum_P"]
