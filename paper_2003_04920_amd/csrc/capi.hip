@@ -1150,7 +1150,9 @@ void enqueue_iteration(pirrt_graph* G, LoopArgs& L, hipStream_t s, bool timing) 
   launch_improve(L.sa, L.variant, s);
   if (timing) (void)hipEventRecord(G->ev[4], s);
   const bool single = L.sa.prob == nullptr;
-  if (!walk_finishes(G, L)) launch_finish(L.P, G->ps, G->ctr, G->ctl, single, s);
+  // (a batch's jumps take the finish step along)
+  L.wa.finish_p = !single && L.wa.seg ? L.P : 0;
+  if (!walk_finishes(G, L) && !L.wa.finish_p) launch_finish(L.P, G->ps, G->ctr, G->ctl, single, s);
   if (timing) (void)hipEventRecord(G->ev[0], s);
   enqueue_evaluate(G, L, s, true);
   if (timing) (void)hipEventRecord(G->ev[1], s);
@@ -1410,6 +1412,7 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
   wa.finish = false;
   wa.jump = nullptr;
   wa.seg = nullptr;
+  wa.finish_p = 0;
   EvalArgs& ea = L.ea;
   ea.n = n;
   ea.ps = G->ps;

@@ -116,61 +116,11 @@ __global__ void __launch_bounds__(kInitThreads) k_replan_init_single(
   }
 }
 
-// One workgroup of kCounterSlots threads per problem: sums and clears the counter
-// copies, then applies the convergence test and the iteration cap.  single: a single
-// graph, whose loop has no after-eval step -- its promising list takes that step's
-// place -- so the problem's state goes to the loop flags here.
+// One workgroup of kCounterSlots threads per problem (see finish_problem).
 __global__ void __launch_bounds__(kCounterSlots) k_finish(int32_t P, ProblemState* __restrict__ ps,
                                                           IterCounters* __restrict__ ctr, LoopCtl* __restrict__ ctl,
                                                           int single) {
-  const int32_t i = blockIdx.x;
-  const int t = threadIdx.x;
-  IterCounters& c = ctr[(int64_t)i * kCounterSlots + t];
-  unsigned long long ch = (unsigned)c.changed, np = (unsigned)c.nP, nd = (unsigned)c.nD, ed = c.edges,
-                     pe = (unsigned)c.pedges;
-  c.changed = 0;
-  c.nP = 0;
-  c.nD = 0;
-  c.pedges = 0;
-  c.edges = 0ull;
-#pragma unroll
-  for (int off = kCounterSlots / 2; off > 0; off >>= 1) {
-    ch += __shfl_xor(ch, off, kCounterSlots);
-    np += __shfl_xor(np, off, kCounterSlots);
-    nd += __shfl_xor(nd, off, kCounterSlots);
-    ed += __shfl_xor(ed, off, kCounterSlots);
-    pe += __shfl_xor(pe, off, kCounterSlots);
-  }
-  if (t == 0) {
-    ProblemState& s = ps[i];
-    if (s.active) {
-      s.iterations += 1;
-      s.edges += ed;
-      s.sum_P += np;
-      s.sum_D += nd;
-      s.changed_total += ch;
-      s.mark_edges += pe;
-      if (ch == 0) {  // no parent switched: fixed point (dJ = 0)
-        s.active = 0;
-        s.needs_eval = 0;
-      } else {
-        s.needs_eval = 1;
-        if (s.iterations >= s.cap) {
-          s.active = 0;
-          s.status = 1;
-        }
-        atomicOr(&ctl->any_eval, 1);
-      }
-      if (!s.active) atomicOr(&ctl->tiles_stale, 1);
-    } else {
-      s.needs_eval = 0;
-    }
-    if (single) {
-      ctl->any_active = s.active;
-      ctl->npromising = 0;
-    }
-  }
-  if (i == 0 && t == 0) ctl->epoch = next_mark_epoch(ctl->epoch);
+  finish_problem(blockIdx.x, threadIdx.x, ps, ctr, ctl, single);
 }
 
 // Runs after the Evaluate of an iteration (and after the first Evaluate of a

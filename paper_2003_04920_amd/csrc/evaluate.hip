@@ -234,20 +234,27 @@ constexpr int kJumpHops = 8;
 
 // jump[v]: the ancestor kJumpHops up (or the root, if it is nearer), kRootMark for a root, -1
 // on a detached chain; seg[2 v], seg[2 v + 1]: the costs from v upwards.
+//
+// finish_p > 0 (batches, after an Improve): workgroups [0, finish_p) take the finish step, a
+// launch less.  It may stop a problem while others take its jumps, which are not read then.
 template <bool kBatched>
 __global__ void __launch_bounds__(kWalkThreads) k_walk_jumps(int32_t n, const int32_t* __restrict__ prob,
-                                                            const ProblemState* __restrict__ ps,
-                                                            const LoopCtl* __restrict__ ctl,
+                                                            ProblemState* ps, LoopCtl* ctl,
+                                                            IterCounters* __restrict__ ctr, int32_t finish_p,
                                                             const int32_t* __restrict__ parent,
                                                             const float* __restrict__ pcost,
                                                             const int32_t* __restrict__ tiles,
                                                             int32_t* __restrict__ jump, float4* __restrict__ seg) {
-  if (kBatched ? ctl->any_eval == 0 : ps->active == 0) return;
+  if (kBatched && blockIdx.x < (unsigned)finish_p) {
+    if (threadIdx.x < kCounterSlots) finish_problem(blockIdx.x, threadIdx.x, ps, ctr, ctl, 0);
+    return;
+  }
+  if (kBatched ? finish_p == 0 && ctl->any_eval == 0 : ps->active == 0) return;
   const int64_t units = kBatched ? tile_units(ctl, n, kWalkThreads) : 1;
-  for (int64_t wu = kBatched ? blockIdx.x : 0; wu < units; wu += kBatched ? gridDim.x : 1) {
+  for (int64_t wu = kBatched ? blockIdx.x - finish_p : 0; wu < units; wu += kBatched ? gridDim.x - finish_p : 1) {
     const int64_t v = (kBatched ? tile_unit_slot(ctl, tiles, kWalkThreads, wu) : (int64_t)blockIdx.x * kWalkThreads) +
                       threadIdx.x;
-    if (v >= n || (kBatched && !ps[prob[v]].needs_eval)) continue;
+    if (v >= n || (kBatched && !(finish_p ? ps[prob[v]].active : ps[prob[v]].needs_eval))) continue;
     float c[kJumpHops];
     int32_t u = (int32_t)v, p = 0;
 #pragma unroll
@@ -480,11 +487,11 @@ void launch_eval_walk(const WalkArgs& a, hipStream_t s) {
     const bool b = a.prob != nullptr;
     if (a.seg) {  // by jumps (one part, no hop count, not truncated: see run_replan)
       if (b)
-        hipLaunchKernelGGL(k_walk_jumps<true>, grid, dim3(kWalkThreads), 0, s, a.n, a.prob, a.ps, a.ctl, a.parent,
-                           a.pcost, a.tiles, a.jump, a.seg);
+        hipLaunchKernelGGL(k_walk_jumps<true>, dim3(grid.x + (unsigned)a.finish_p), dim3(kWalkThreads), 0, s, a.n,
+                           a.prob, a.ps, a.ctl, a.ctr, a.finish_p, a.parent, a.pcost, a.tiles, a.jump, a.seg);
       else
-        hipLaunchKernelGGL(k_walk_jumps<false>, grid, dim3(kWalkThreads), 0, s, a.n, a.prob, a.ps, a.ctl, a.parent,
-                           a.pcost, a.tiles, a.jump, a.seg);
+        hipLaunchKernelGGL(k_walk_jumps<false>, grid, dim3(kWalkThreads), 0, s, a.n, a.prob, a.ps, a.ctl, a.ctr, 0,
+                           a.parent, a.pcost, a.tiles, a.jump, a.seg);
 #define PIRRT_WALK_JUMP(C, B, F)                                                                                  \
   hipLaunchKernelGGL((k_eval_walk<false, C, B, false, F, true>), grid, dim3(kWalkThreads), 0, s, lo, hi, a.n,     \
                      a.prob, a.ps, a.ctl, a.parent, a.pcost, a.g, a.word, a.hops, a.tiles, a.h, a.ctr, 1, a.jump, \

@@ -226,6 +226,7 @@ struct WalkArgs {
   // climb link by link.
   int32_t* jump;
   float4* seg;
+  int32_t finish_p;        // batches, by jumps, after an Improve: problems to finish first (else 0)
 };
 void launch_eval_walk(const WalkArgs& a, hipStream_t s);
 // Workgroups of the batched walk resident on one compute unit (256 threads and 16 KB
