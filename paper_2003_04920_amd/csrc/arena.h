@@ -1,8 +1,8 @@
 // Device memory of one handle.  A handle keeps some forty arrays, most of them small, and
-// every hipFree costs 100 to 300 us whatever its size: destroying the two handles of a
-// 200,000-vertex layout took 5.0 ms of its 18 (now 2.9, with slabs of 64 MiB 3.7), and a
-// growing planner paid for every array it replaced.  Here pieces come from a few slabs that go
-// back to the device with the handle.
+// every hipFree costs 100 to 450 us whatever its size: destroying the two handles of a
+// 200,000-vertex layout took 5.0 ms of its 18, now 1.7 of 11, and a growing planner paid for
+// every array it replaced.  Here pieces come from a few slabs that go back to the device with
+// the handle.
 //
 // A freed piece is used again by the same handle only, and all of a handle's work is on its
 // one stream, so a new user is ordered after the old one without a wait.  Requests past
@@ -22,7 +22,7 @@ class Arena {
  public:
   static constexpr size_t kAlign = 256;
   static constexpr size_t kFirst = (size_t)1 << 20;
-  static constexpr size_t kDirect = (size_t)32 << 20;
+  static constexpr size_t kDirect = (size_t)128 << 20;
   static constexpr size_t kSlabMax = (size_t)256 << 20;
 
   Arena() = default;

@@ -360,7 +360,6 @@ struct pirrt_rrg {
   uint4* rec = nullptr;
   int64_t rec_cap = 0, packed = 0;  // records of room; points packed so far
   int32_t* scand = nullptr;
-  float* sccost = nullptr;
   int64_t scand_cap = 0;
   int32_t* scnt = nullptr;
   int64_t scnt_cap = 0;
@@ -574,9 +573,9 @@ int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direc
     a.row0 = row0;
     a.rows = (int32_t)slab;
     if (slab * stride > R->scand_cap) {
-      rfree(R, R->scand); rfree(R, R->sccost);
+      rfree(R, R->scand);  // (candidates and costs in one piece)
       R->scand_cap = 0;
-      if (!ralloc(R, &R->scand, slab * stride) || !ralloc(R, &R->sccost, slab * stride))
+      if (!ralloc(R, &R->scand, 2 * slab * stride))
         return rfail(R, PIRRT_ENOMEM, "device allocation of candidate lists failed");
       R->scand_cap = slab * stride;
     }
@@ -596,7 +595,7 @@ int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direc
     if ((rc = ensure_scan(R, slab + 1))) return rc;
     if ((rc = ensure_rows(R, base + slab * 64, base))) return rc;
     a.cand = R->scand;
-    a.ccost = R->sccost;
+    a.ccost = reinterpret_cast<float*>(R->scand + slab * stride);
     a.cnt = R->scnt;
     a.deg = R->sdeg;
     const bool own = !direct || slab < rows;  // several slabs are gathered in the handle's arrays
@@ -772,7 +771,7 @@ void release(pirrt_rrg* R) {
   rfree(R, R->okind); rfree(R, R->ocentre); rfree(R, R->osize); rfree(R, R->pts); rfree(R, R->cbuf); rfree(R, R->flag); rfree(R, R->freed);
   rfree(R, R->pos); rfree(R, R->cnt); rfree(R, R->cptr); rfree(R, R->cand_u); rfree(R, R->cand_v); rfree(R, R->keep); rfree(R, R->kpos); rfree(R, R->ccost);
   rfree(R, R->rp); rfree(R, R->col); rfree(R, R->cost); rfree(R, R->hbuf); rfree(R, R->dflag);
-  rfree(R, R->rec); rfree(R, R->scand); rfree(R, R->sccost); rfree(R, R->scnt); rfree(R, R->sdeg); rfree(R, R->soff); rfree(R, R->sstate);
+  rfree(R, R->rec); rfree(R, R->scand); rfree(R, R->scnt); rfree(R, R->sdeg); rfree(R, R->soff); rfree(R, R->sstate);
   rfree(R, R->lpts); rfree(R, R->lfeat); rfree(R, R->llogit); rfree(R, R->lenc); rfree(R, R->lflag); rfree(R, R->lsel);
   R->arena.free(R->scan);
   R->scan = nullptr;
