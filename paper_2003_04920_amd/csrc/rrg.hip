@@ -12,7 +12,7 @@
 //   heuristic: binary32 rounding of the binary64 distance to the goal.
 //
 // The radius search runs on the matrix cores (search.hip) while every point lies in the
-// unit cube and no row has more than kSearchRowMax candidates.  Otherwise it is done in
+// unit cube and no row has more than kSearchRowWide candidates.  Otherwise it is done in
 // binary64 over all earlier vertices (k_radius): a workgroup owns 256 consecutive new
 // vertices (one per thread) and streams the earlier points through LDS in tiles every
 // thread reads by broadcast, twice (count, then write candidates in ascending u); the
@@ -368,6 +368,7 @@ struct pirrt_rrg {
   int64_t sdeg_cap = 0;
   SearchState* sstate = nullptr;
   int32_t room = 128;      // candidates a row is expected to have at most
+  bool wide = false;       // the last search met rows of more than kSearchRowMax candidates
   bool outside = false;    // a point outside the unit cube: no matrix-core search
   float* hbuf = nullptr;
   int64_t hcap = 0;
@@ -527,7 +528,7 @@ int ensure_rows(pirrt_rrg* R, int64_t need, int64_t keep) {
 }
 
 // The rows by the matrix-core search.  *done stays false where that search does not
-// apply (points outside the unit cube, rows of more than kSearchRowMax candidates).
+// apply (points outside the unit cube, rows of more than kSearchRowWide candidates).
 // Lists that turn out too short are made longer and the slab searched again; the room
 // is remembered, so a handle learns the density of its scene once.
 int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direct, int64_t* nnz, bool* done,
@@ -555,6 +556,7 @@ int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direc
   a.obs = obs_view(R);
   a.rec = R->rec;
   a.state = R->sstate;
+  a.wide = R->wide;
   static_assert(sizeof(SearchState) <= sizeof(int64_t) * kHostWords, "R->host holds it");
   SearchState* st = reinterpret_cast<SearchState*>(R->host);
   a.report = st;
@@ -611,16 +613,20 @@ int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direc
       R->outside = true;
       return PIRRT_OK;
     }
-    if (st->listed || st->most > kSearchRowMax) return PIRRT_OK;
+    if (st->listed > kSearchRowWide || st->most > kSearchRowWide) return PIRRT_OK;
+    if (st->listed || st->most > kSearchRowMax) a.wide = true;
+    if (st->listed) continue;  // the same slab again, a workgroup a row
     if (st->most) {  // longer lists, the same slab again
       a.cap = (st->most + st->most / 4 + 3) / 4 * 4;
-      R->room = std::max(R->room, a.nch == 1 ? a.cap : std::min(a.cap * a.nch / 2, kSearchRowMax));
+      R->room = std::max(R->room, a.nch == 1 ? a.cap : std::min(a.cap * a.nch / 2, kSearchRowWide));
       continue;
     }
     if (own && st->nnz > R->col_cap) {
       if ((rc = ensure_rows(R, st->nnz, base))) return rc;
       continue;
     }
+    if (a.wide && !st->wide && row0 + slab >= rows) R->wide = false;
+    if (st->wide) R->wide = true;
     base = st->nnz;
     row0 += slab;
     *wrote = !own;

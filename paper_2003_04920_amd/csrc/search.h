@@ -10,12 +10,13 @@ namespace pirrt {
 struct SearchState {
   int32_t outside;  // some point lies outside the unit cube
   int32_t most;     // largest candidate count of a list that was too short (0: none was)
-  int32_t listed;   // largest candidate count of a row past kSearchRowMax (0: none)
-  int32_t pad;
+  int32_t listed;   // largest candidate count of a row past the finish's room (0: none)
+  int32_t wide;     // largest candidate count of a row past kSearchRowMax, wide finish (0: none)
   int64_t nnz;      // entries of all rows
 };
 
-constexpr int kSearchRowMax = 512;     // candidates one row may have here
+constexpr int kSearchRowMax = 512;     // candidates a row may have in the finish by 32 lanes
+constexpr int kSearchRowWide = 4096;   // and in the finish by a workgroup
 constexpr int kSearchRecord = 32;      // bytes of a point's packed record
 constexpr int kSearchPad = 256;        // records of room past the last point
 constexpr int kSearchMaxChunks = 64;
@@ -38,6 +39,7 @@ struct SearchArgs {
   int32_t* cnt;           // [rows][nch] candidates per list
   float* ccost;           // [rows][nch * cap] costs of the finished rows
   int32_t* deg;           // [rows] entries of the finished rows
+  bool wide;              // rows finished by a workgroup each
   SearchState* state;
   SearchState* report;    // pinned host memory: *state at the end
 };

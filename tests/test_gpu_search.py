@@ -170,3 +170,23 @@ def test_many_obstacles(P, d, count):
     pts = G.points()
     assert c == wc and np.array_equal(pts[2:], want)
     check(P, pts, 100, W.radius(n, d), obs, G)
+
+
+@pytest.mark.parametrize("d", [1, 3, 8])
+@pytest.mark.parametrize("members", [513, 514, 769, 1600, 4097, 4098])
+def test_rows_of_hundreds(P, d, members):
+    """A cluster whose last row has members - 1 candidates: up to 512 by 32 lanes, up to
+    4,096 by a workgroup, the all-pairs search above; then rows of few candidates and the
+    cluster's again with the same handle."""
+    rng = np.random.default_rng(members + d)
+    pts = rng.random((members + 600, d))
+    pts[:, 0] = 0.5 + 0.5 * pts[:, 0]
+    pts[300:300 + members] = 0.3 + 0.02 * rng.random((members, d))
+    obs = W.make_obstacles(d, 5, "mixed", 3)
+    # the centre is not crossed by chance alone: an obstacle inside the cluster
+    obs.centre[0], obs.size[0] = 0.31, 0.002
+    G = P.Rrg(d, obs, stream=stream())
+    G.add_points(pts)
+    n = len(pts)
+    for n_old in (300 + members - 40, n - 200, 300 + members - 520):
+        check(P, pts, n_old, 0.08, obs, G)
