@@ -1238,8 +1238,12 @@ struct PolicyOut {
 // 2,993; 3D 400,000: 3.65 / 2.79 ms; 2D 400,000: 21.1 / 18.8 ms; without pruning 6D 1M: 5.06 /
 // 3.23 ms.  Past these sizes, with pruning, the iterations whose promising set is dense pull all
 // the same (k_improve_auto: 6D 1M 2,277 -> 2,050 us).  A batch (64 problems, 1.7M vertices) took 17.4 / 17.5 ms and keeps the marks.
+// Not with rows of hundreds of entries (samples crowded along a corridor): few of those
+// vertices are promising at a time, and the kernel that can do both forms took 4% longer over
+// the listed rows (340 entries a row: 2.58 -> 2.68 ms; 54 a row: 2,277 -> 2,050 us as above).
 constexpr int32_t kPullMax = 1 << 19;
 constexpr int64_t kPullEdges = (int64_t)24 << 20;
+constexpr int32_t kDenseRow = 128;
 
 bool pulls(const pirrt_graph* G, bool prune) {
   if (G->batched || G->truncated || G->pull == 0 || G->pull == 2) return false;
@@ -1389,7 +1393,8 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
   sa.blocks = G->batch_blocks;
   sa.gs = reinterpret_cast<float*>(G->fr1);  // (in the place of the promising list)
   sa.pull = pulls(G, prune);
-  sa.dense = !sa.pull && prune && !G->batched && !G->truncated && G->pull != 0;
+  sa.dense = !sa.pull && prune && !G->batched && !G->truncated &&
+             (G->pull == 2 || (G->pull < 0 && G->nnz <= (int64_t)kDenseRow * G->n));
   if (sa.dense) sa.gs = reinterpret_cast<float*>(G->deg);  // (the list has fr1)
   L.variant = row_variant(G, sa.pull);
   WalkArgs& wa = L.wa;

@@ -51,9 +51,8 @@ void launch_append(int32_t n_new, int64_t n_old, int64_t nnz_old, const int64_t*
 void launch_pending(int32_t n_new, int64_t n_old, const int64_t* brp, const int32_t* bcol, int32_t* pending,
                     int32_t* frontier, int32_t* fcount, hipStream_t s);
 // bcol: neighbour ids as given (tie-break keys); bslot: the same in storage slots.
-// insert_root: the new vertex that gets g = 0 (x_init), or -1.  The level's frontier
-// size is read on the device from *fsize (the grid covers max_size threads), and
-// *done accumulates the sizes, so several levels go out without a host round trip.
+// insert_root: the new vertex that gets g = 0 (x_init), or -1.  *done accumulates the
+// levels' sizes.
 // Every dependency level of a small batch in one single-workgroup launch (the first
 // frontier in f0, its size at fsize0; f1 the other frontier buffer).
 constexpr int32_t kInsertBlockMax = 2048;
