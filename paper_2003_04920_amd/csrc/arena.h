@@ -23,7 +23,8 @@ class Arena {
   static constexpr size_t kAlign = 256;
   static constexpr size_t kFirst = (size_t)1 << 20;
   static constexpr size_t kDirect = (size_t)128 << 20;
-  static constexpr size_t kSlabMax = (size_t)256 << 20;
+  static constexpr size_t kSlabMax = (size_t)256 << 20;  // of a slab that was foreseen (expect)
+  static constexpr size_t kGrow = (size_t)64 << 20;      // of the others
 
   Arena() = default;
   Arena(const Arena&) = delete;
@@ -39,8 +40,9 @@ class Arena {
       for (auto it = free_.begin(); it != free_.end(); ++it)
         if (it->second >= bytes && (best == free_.end() || it->second < best->second)) best = it;
       if (best == free_.end()) {
-        // slabs grow with the handle, so that their number stays small
-        size_t size = std::max(bytes, std::min(std::max({2 * total_, kFirst, expected_}), kSlabMax));
+        // slabs grow with the handle, so that their number stays small, but not far past what
+        // is asked for: the driver wipes all of them when they go back
+        size_t size = std::max({bytes, std::min(std::max(2 * total_, kFirst), kGrow), std::min(expected_, kSlabMax)});
         expected_ = 0;
         slabs_.reserve(slabs_.size() + 1);
         char* p = static_cast<char*>(device(size));

@@ -544,8 +544,10 @@ int ensure_staging(pirrt_graph* G, int64_t rows, int64_t nnz) {
     G->brows_cap = cap;
   }
   if (nnz > G->bnnz_cap) {
-    // a large first batch: staging and both copies of an adjacency of its size come soon
-    if (G->nnz == 0 && (size_t)nnz * 2 * sizeof(int32_t) <= Arena::kDirect) G->arena.expect((size_t)nnz * 44 + Arena::kFirst);
+    // a large first batch: staging, both copies of an adjacency of its size and the walk's
+    // records come soon
+    if (G->nnz == 0 && (size_t)nnz * 2 * sizeof(int32_t) <= Arena::kDirect)
+      G->arena.expect((size_t)nnz * 44 + (size_t)G->vcap * 40 + Arena::kFirst);
     int32_t* c = nullptr;
     int32_t* t = nullptr;
     float* w = nullptr;

@@ -513,7 +513,12 @@ struct RowsOut {
   int64_t capacity;
 };
 
-constexpr int64_t kSlabEntries = (int64_t)1 << 27;  // candidate room of one slab of rows
+// Candidate room of one slab of rows: 128 MiB of ids and costs (65,536 rows at the first room
+// of their lists).  The driver wipes what a handle gives back at some 40 GB/s, and a program that
+// makes handle after handle waits for that: layouts of 200,000 points with 422 MB of lists took
+// 11.3 ms each until the card's memory had been used once, and 35 ms from then on.
+constexpr int64_t kSlabEntries = (int64_t)1 << 24;
+constexpr int64_t kRowEntries = 40;  // entries of a row that room is made for at first
 
 // Room for `need` entries of rows, the first `keep` kept.
 int ensure_rows(pirrt_rrg* R, int64_t need, int64_t keep) {
@@ -562,7 +567,7 @@ int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direc
   a.report = st;
   // enough workgroups to fill the chip: a row's earlier points are cut into chunks, each
   // with its own candidate list
-  const int64_t groups = (rows + (rows >= kSearchWideRows ? 511 : 127)) / (rows >= kSearchWideRows ? 512 : 128);
+  const int64_t groups = rows >= kSearchWideRows ? kSearchWideRows / 512 : (rows + 127) / 128;
   int64_t nch = (kSearchGroups + groups - 1) / groups;
   nch = std::max<int64_t>(1, std::min<int64_t>({nch, kSearchMaxChunks, (R->n + kSearchPad - 1) / kSearchPad}));
   a.chunk = ((R->n + nch - 1) / nch + kSearchPad - 1) / kSearchPad * kSearchPad;
@@ -595,7 +600,7 @@ int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direc
       R->sdeg_cap = slab + 1;
     }
     if ((rc = ensure_scan(R, slab + 1))) return rc;
-    if ((rc = ensure_rows(R, base + slab * 64, base))) return rc;
+    if ((rc = ensure_rows(R, base + (rows - row0) * kRowEntries, base))) return rc;
     a.cand = R->scand;
     a.ccost = reinterpret_cast<float*>(R->scand + slab * stride);
     a.cnt = R->scnt;
