@@ -33,7 +33,6 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 BF16_PEAK_TFLOPS = 2500.0  # dense bf16 matrix-core peak of the MI355X
-FP64_PEAK_TFLOPS = 78.6  # binary64 vector peak of the MI355X (fused multiply-adds counted as two)
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
 IMPROVE_SRC = os.path.join(ROOT, "paper_2003_04920_amd", "csrc", "improve.hip")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_improve_6d_1m_traffic.txt")
@@ -91,7 +90,8 @@ def replan_bytes(st: dict, n: int) -> dict:
     - promising list: 8 B per vertex and iteration (g, h) + 5 B per promising vertex
       (its list entry and stamp);
     - mark: 20 B per promising vertex (list entry, two row offsets) + 5 B per entry of
-      a promising row (neighbour read 4, stamp written 1);
+      a promising row (neighbour read 4, stamp written 1), in every iteration (those whose
+      promising set is dense skip it on large graphs, pull form on others);
     - domain list: 1 B per vertex and iteration (stamps) + 4 B per domain vertex;
     - Improve: 8 B per examined edge + 24 B per domain vertex.
     The g gathers of Improve (L2 / MALL resident) are not counted."""
@@ -197,7 +197,8 @@ def profile_summary(paths):
     print("\n".join(out))
 
 
-LOOP_KERNELS = ("k_promising_list", "k_mark", "k_domain_list", "k_improve", "k_finish", "k_eval_walk",
+LOOP_KERNELS = ("k_promising_list", "k_promising_signs", "k_mark", "k_domain_list",
+                "k_improve", "k_improve_auto", "k_finish", "k_walk_jumps", "k_eval_walk",
                 "k_after_eval")
 
 
@@ -456,8 +457,8 @@ def bench_learned(args):
     root_goal = PL.root_goal(d)
 
     # ---- exploration support on its own: one 200k-vertex 6D graph, the radius search
-    # (two passes over every pair u < v, binary64 squared distance: 3d - 1 = 17 flops
-    # a pair, no fused multiply-add) and the segment tests
+    # (every pair u < v on the matrix cores in f16, 16 products a pair; the candidates
+    # again in binary64), the segment tests and the insert (first calls of the process)
     obs0 = W.make_obstacles(d, 40, "sphere", 19_990)
     R0 = P.Rrg(d, obs0, stream=stream, point_capacity=n_train)
     R0.add_points(root_goal)
@@ -468,11 +469,11 @@ def bench_learned(args):
     R0.connect(0, W.radius(n_train, d), G0)
     torch.cuda.synchronize()
     connect_s = time.perf_counter() - t0
-    pair_tests = 2 * n_train * (n_train - 1) // 2
-    tf = pair_tests * (3 * d - 1) / connect_s / 1e12
+    pair_tests = n_train * (n_train - 1) // 2
+    tf = pair_tests * 32 / connect_s / 1e12
     explore = {"points": n_train, "d": d, "connect_ms": round(1e3 * connect_s, 2), "directed_edges": G0.nnz,
-               "pair_tests": pair_tests, "fp64_tflops": round(tf, 2), "fp64_peak_tflops": FP64_PEAK_TFLOPS,
-               "frac": round(tf / FP64_PEAK_TFLOPS, 4)}
+               "pair_tests": pair_tests, "f16_tflops": round(tf, 2), "f16_peak_tflops": BF16_PEAK_TFLOPS,
+               "frac": round(tf / BF16_PEAK_TFLOPS, 4)}
     log("exploration: %s" % json.dumps(explore))
     del R0, G0
 
