@@ -190,3 +190,33 @@ def test_rows_of_hundreds(P, d, members):
     n = len(pts)
     for n_old in (300 + members - 40, n - 200, 300 + members - 520):
         check(P, pts, n_old, 0.08, obs, G)
+
+
+def test_device_rows_in_slabs(P):
+    """More rows than one slab holds, into device buffers: the same as on the host."""
+    import torch
+    pts = np.random.default_rng(4).random((66_003, 2))
+    r = W.radius(len(pts), 2)
+    G = P.Rrg(2, W.make_obstacles(2, 8, "box", 1), stream=stream())
+    G.add_points(pts)
+    want = G.rows(0, r)
+    got = G.rows(0, r, device=torch.device("cuda", 0))
+    torch.cuda.synchronize()
+    for a, b in zip(want, got):
+        b = b.cpu().numpy()
+        assert np.array_equal(a.view(np.uint8), b.view(np.uint8))
+
+
+def test_slabs_of_long_rows(P):
+    """Rows of up to some 900 candidates, several slabs of them, a workgroup a row."""
+    pts = np.random.default_rng(6).random((20_000, 2))
+    obs = W.make_obstacles(2, 4, "mixed", 5)
+    G = P.Rrg(2, obs, stream=stream())
+    G.add_points(pts)
+    r = 0.12
+    rp, col, cost = G.rows(0, r)
+    for lo, hi in ((0, 4000), (19_000, 20_000)):
+        orp, ocol, ocost = R.build_rows(pts[:hi], lo, r, obs)
+        assert np.array_equal(rp[lo:hi + 1] - rp[lo], orp)
+        assert np.array_equal(col[rp[lo]:rp[hi]], ocol)
+        assert np.array_equal(cost[rp[lo]:rp[hi]].view(np.uint32), ocost.view(np.uint32))
