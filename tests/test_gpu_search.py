@@ -73,7 +73,7 @@ def test_lattice_at_the_threshold(P, d, step):
 @pytest.mark.parametrize("members", [60, 300, 700])
 def test_clusters_outgrow_the_lists(P, members):
     """Clusters denser than the lists' first room: longer lists up to 512 candidates a
-    row (60, 300), the all-pairs search above (700)."""
+    row (60, 300), rows finished by a workgroup each above (700)."""
     rng = np.random.default_rng(members)
     pts = rng.random((2500, 3))
     pts[800:800 + members] = 0.4 + 1e-3 * rng.random((members, 3))  # ids close together: one chunk's list
