@@ -236,7 +236,10 @@ constexpr int kJumpHops = 8;
 // on a detached chain; seg[2 v], seg[2 v + 1]: the costs from v upwards.
 //
 // finish_p > 0 (batches, after an Improve): workgroups [0, finish_p) take the finish step, a
-// launch less.  It may stop a problem while others take its jumps, which are not read then.
+// launch less.  It rewrites active and needs_eval while the others run, and a problem that it
+// stops at the iteration cap is still evaluated.  So the others go by the threshold, which the
+// after-eval step of the iteration before set (-inf: the problem had stopped by then) and
+// nothing in this launch writes: every problem of this iteration gets its jumps.
 template <bool kBatched>
 __global__ void __launch_bounds__(kWalkThreads) k_walk_jumps(int32_t n, const int32_t* __restrict__ prob,
                                                             ProblemState* ps, LoopCtl* ctl,
@@ -254,7 +257,11 @@ __global__ void __launch_bounds__(kWalkThreads) k_walk_jumps(int32_t n, const in
   for (int64_t wu = kBatched ? blockIdx.x - finish_p : 0; wu < units; wu += kBatched ? gridDim.x - finish_p : 1) {
     const int64_t v = (kBatched ? tile_unit_slot(ctl, tiles, kWalkThreads, wu) : (int64_t)blockIdx.x * kWalkThreads) +
                       threadIdx.x;
-    if (v >= n || (kBatched && !(finish_p ? ps[prob[v]].active : ps[prob[v]].needs_eval))) continue;
+    if (v >= n) continue;
+    if (kBatched) {
+      const ProblemState& q = ps[prob[v]];
+      if (finish_p ? q.thr == -pos_inf() : !q.needs_eval) continue;
+    }
     float c[kJumpHops];
     int32_t u = (int32_t)v, p = 0;
 #pragma unroll
