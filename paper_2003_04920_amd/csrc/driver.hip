@@ -65,6 +65,7 @@ __global__ void __launch_bounds__(kInitThreads) k_replan_init_single(
   const int t = threadIdx.x;
   int wrong = 0;
   if (h_in) {
+#pragma unroll 8
     for (int32_t e = t; e < n; e += kInitThreads) {
       const float x = h_in[e];
       h[slot_of[e]] = x;

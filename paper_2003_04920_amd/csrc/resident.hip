@@ -138,15 +138,28 @@ __global__ void __launch_bounds__(kResThreads) k_replan_resident(ResidentArgs a)
   const int32_t first = (int32_t)blockIdx.x * R;
   const int32_t own = first >= n ? 0 : (first + R < n ? R : n - first);
   const int32_t root = a.ps->root, goal = a.ps->goal, cap = a.ps->cap;
+  // (a few vertices' loads in flight together, none behind the value of another)
   float hv[K];
 #pragma unroll
-  for (int k = 0; k < K; ++k) {
-    const int32_t v = t + k * kResThreads;
-    const int32_t p = v < n && v != root ? a.parent[v] : -1;
-    hv[k] = a.h && v < n ? a.h[v] : 0.0f;
-    par[v] = (uint16_t)(4 * (p >= 0 ? p : v));
-    pc[v] = p >= 0 ? a.pcost[v] : 0.0f;
-    g[v] = v == root ? 0.0f : (p >= 0 && a.tree ? a.g[v] : pos_inf());
+  for (int k0 = 0; k0 < K; k0 += kTogether) {
+    int32_t p[kTogether];
+    float c[kTogether], old[kTogether];
+#pragma unroll
+    for (int j = 0; j < kTogether && k0 + j < K; ++j) {
+      const int32_t v = t + (k0 + j) * kResThreads, i = v < n ? v : n - 1;
+      p[j] = a.parent[i];
+      c[j] = a.pcost[i];
+      old[j] = a.g[i];
+      hv[k0 + j] = a.h ? a.h[i] : 0.0f;
+    }
+#pragma unroll
+    for (int j = 0; j < kTogether && k0 + j < K; ++j) {
+      const int32_t v = t + (k0 + j) * kResThreads;
+      const bool has = v < n && v != root && p[j] >= 0;
+      par[v] = (uint16_t)(4 * (has ? p[j] : v));
+      pc[v] = has ? c[j] : 0.0f;
+      g[v] = v == root ? 0.0f : (has && a.tree ? old[j] : pos_inf());
+    }
   }
   if (t < 64) g[N + t] = pos_inf();
   __shared__ int moved[3];  // whether an Evaluate round changed something; the rounds take turns
@@ -382,6 +395,12 @@ __global__ void __launch_bounds__(kResThreads) k_replan_resident(ResidentArgs a)
     if (a.g_out) a.g_out[e] = fabsf(g[v]);
     if (a.parent_out) a.parent_out[e] = par[v] != 4 * v ? a.ext_of[par[v] / 4] : -1;
   }
+  // The counters, one addition each a workgroup: with one a wave, some 6,000 to one line, a
+  // Replan of one iteration took 105 us at 12,000 vertices and 132 at 15,000 (the loop of
+  // launches 98 and 100), now 51 and 61.
+  __shared__ unsigned long long sums[4];
+  if (t < 4) sums[t] = 0ull;
+  __syncthreads();
   unsigned long long sp = (unsigned)sum_p, sd = (unsigned)sum_d;
 #pragma unroll
   for (int o = kWave / 2; o > 0; o >>= 1) {
@@ -391,14 +410,18 @@ __global__ void __launch_bounds__(kResThreads) k_replan_resident(ResidentArgs a)
     sum_pe += __shfl_xor(sum_pe, o, kWave);
   }
   if (lane == 0) {
-    atomicAdd(&a.ps->sum_P, sp);
-    atomicAdd(&a.ps->sum_D, sd);
-    atomicAdd(&a.ps->edges, sum_e);
-    atomicAdd(&a.ps->mark_edges, sum_pe);
+    atomicAdd(&sums[0], sp);
+    atomicAdd(&sums[1], sd);
+    atomicAdd(&sums[2], sum_e);
+    atomicAdd(&sums[3], sum_pe);
   }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's sums are in
   __syncthreads();
   if (t != 0) return;
+  atomicAdd(&a.ps->sum_P, sums[0]);
+  atomicAdd(&a.ps->sum_D, sums[1]);
+  atomicAdd(&a.ps->edges, sums[2]);
+  atomicAdd(&a.ps->mark_edges, sums[3]);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // they are in
   // the workgroup that is done last has all sums and reports them (all agree on the rest)
   if (__hip_atomic_fetch_add(&a.sync->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != W - 1) return;
   ProblemState q = {};
