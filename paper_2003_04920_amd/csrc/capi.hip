@@ -104,7 +104,7 @@ struct LoopKey {
   const void* ptrs[18];
   int64_t n, nnz;
   int32_t P, prune, variant, walk_parts, walk_coherent, eval_levels, has_h, iters, mid, lookahead, truncated, blocks;
-  int32_t bitmap_tiles, walk_rank, pull, dense;
+  int32_t bitmap_tiles, walk_rank, pull, dense_min;
   bool operator==(const LoopKey& o) const { return memcmp(this, &o, sizeof(LoopKey)) == 0; }
 };
 
@@ -1190,7 +1190,7 @@ LoopKey loop_key(pirrt_graph* G, const LoopArgs& L, int iters) {
   k.bitmap_tiles = G->bitmap_tiles;
   k.walk_rank = G->walk_rank;
   k.pull = L.sa.pull;
-  k.dense = L.sa.dense;
+  k.dense_min = L.sa.dense_min;
   return k;
 }
 
@@ -1231,25 +1231,46 @@ struct PolicyOut {
 };
 
 // Whether a single graph's Improve takes every row and finds the domain by itself (pull:
-// two streams of n and one of the whole adjacency an iteration) or the domain is marked
-// and listed first (three launches more, but only the domain's rows, and the promising
-// ones twice).  Without pruning the domain is every reachable row.  With pruning about
-// half the rows are in it, and up to half a million vertices the launches and the marks'
-// scattered writes cost more than the other half.  Measured, marks against pull: with pruning
-// 6D 200,000 vertices 807 / 676 us, 300,000: 956 / 861, 400,000: 1,102 / 1,046, 1M: 2,277 /
-// 2,993; 3D 400,000: 3.65 / 2.79 ms; 2D 400,000: 21.1 / 18.8 ms; without pruning 6D 1M: 5.06 /
-// 3.23 ms.  Past these sizes, with pruning, the iterations whose promising set is dense pull all
-// the same (k_improve_auto: 6D 1M 2,277 -> 2,050 us).  A batch (64 problems, 1.7M vertices) took 17.4 / 17.5 ms and keeps the marks.
-// Not with rows of hundreds of entries (samples crowded along a corridor): few of those
-// vertices are promising at a time, and the kernel that can do both forms took 4% longer over
-// the listed rows (340 entries a row: 2.58 -> 2.68 ms; 54 a row: 2,277 -> 2,050 us as above).
-constexpr int32_t kPullMax = 1 << 19;
-constexpr int64_t kPullEdges = (int64_t)24 << 20;
+// two streams of n and one of the whole adjacency an iteration), or the domain is marked and
+// listed first (three launches more, but only the domain's rows, and the promising ones
+// twice), or each iteration picks the form by its promising set (k_improve_auto: pull from a
+// third of the vertices on, at the price of two launches that then return at once).
+//
+// Pull alone reads the whole adjacency also where the goal is near, or already well connected,
+// and the domain a few rows.  Up to kPullMax vertices and kPullEdges entries that costs a few
+// percent where the launches it saves are a fifth; past them far goals gain less than near
+// ones lose.  Measured in us, marks / pull / both
+// forms, goal in the far corner and goals nearer than 0.1%, 2% and 20% of the vertices:
+//   6D 150,000  643 / 516 / 588 far     122 / 124 / 121, 230 / 244 / 232, 318 / 330 / 320
+//   3D 200,000  2,046 / 1,469 / 1,678   137 / 178 / 137, 317 / 384 / 321, 499 / 561 / 506
+//   6D 300,000  855 / 799 / 767         164 / 242 / 167, 327 / 388 / 311, 401 / 512 / 405
+//   3D 500,000  5,027 / 3,970 / 4,093   239 / 445 / 243, 365 / 664 / 371, 770 / 1,152 / 778
+//   6D 1M       2,640 / 3,430 / 2,505   361 / 1,027 / 370, 444 / 1,269 / 453, 691 / 1,978 / 702
+// Without pruning the domain is every reachable row, and pull wins unless the root's component
+// is small: 6D 300,000 1,430 / 866 / 981 all reachable, 276 / 326 / 279 two vertices reachable;
+// 600,000 2,761 / 1,727 / 1,877 and 457 / 586 / 449; 1M 5,377 / 3,425 / 3,553 and 662 / 996 /
+// 671; 3D 1M 13.4 / 11.9 / 10.6 ms.  So there both forms take over at kPullAll vertices only.
+//
+// The third: shares of 1/2, 1/3, 1/6, 1/12 and 1/24 took 2,512, 2,505, 2,561, 2,738 and 3,555 us
+// (6D 1M, far), 9.5, 9.6, 10.2, 10.9 and 11.4 ms (3D 1M), 18.3, 18.4, 18.7, 19.1 and 19.5 ms (2D
+// 400,000), 1,156, 1,097, 1,115, 1,313 and 1,310 us (6D 500,000); marks alone 2,640 us, 11.8 ms,
+// 20.7 ms and 1,185 us.
+// A batch (64 problems, 1.7M vertices) took 17.4 ms with marks, 17.5 by pull and keeps the marks.
+// Graphs with rows of hundreds of entries (samples crowded along a corridor) do too: few of
+// their vertices are promising at a time, and the kernel with both forms took 4% longer over the
+// listed rows (340 entries a row: 2.58 -> 2.68 ms).
+constexpr int32_t kPullMax = 5 << 15;  // 163,840
+constexpr int64_t kPullEdges = (int64_t)10 << 20;
+constexpr int32_t kPullAll = 1 << 19;  // without pruning
 constexpr int32_t kDenseRow = 128;
+constexpr int32_t kDenseShare = 3;
+
+bool short_rows(const pirrt_graph* G) { return G->nnz <= (int64_t)kDenseRow * G->n; }
 
 bool pulls(const pirrt_graph* G, bool prune) {
   if (G->batched || G->truncated || G->pull == 0 || G->pull == 2) return false;
-  return G->pull == 1 || !prune || (G->n <= kPullMax && G->nnz <= kPullEdges);
+  if (G->pull == 1) return true;
+  return prune ? G->n <= kPullMax && G->nnz <= kPullEdges : G->n <= kPullAll || !short_rows(G);
 }
 
 // Row splits (lanes a row x quads in flight: see launch_mark and launch_improve).  Rows have
@@ -1395,9 +1416,9 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
   sa.blocks = G->batch_blocks;
   sa.gs = reinterpret_cast<float*>(G->fr1);  // (in the place of the promising list)
   sa.pull = pulls(G, prune);
-  sa.dense = !sa.pull && prune && !G->batched && !G->truncated &&
-             (G->pull == 2 || (G->pull < 0 && G->nnz <= (int64_t)kDenseRow * G->n));
-  if (sa.dense) sa.gs = reinterpret_cast<float*>(G->deg);  // (the list has fr1)
+  const bool both = !sa.pull && !G->batched && !G->truncated && (G->pull == 2 || (G->pull < 0 && short_rows(G)));
+  sa.dense_min = both ? n / kDenseShare + 1 : 0;
+  if (both) sa.gs = reinterpret_cast<float*>(G->deg);  // (the list has fr1)
   L.variant = row_variant(G, sa.pull);
   WalkArgs& wa = L.wa;
   wa.n = n;

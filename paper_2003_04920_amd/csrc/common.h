@@ -81,9 +81,10 @@ __device__ __forceinline__ int64_t tile_unit_slot(const LoopCtl* ctl, const int3
   return t * kTileSlots + (w % upt) * per_unit;
 }
 
-// Whether more than a third of a single graph's vertices are promising (the list is complete).
-__device__ __forceinline__ bool dense_promising(const LoopCtl* ctl, int32_t n) {
-  return 3 * (int64_t)ctl->npromising > n;
+// Whether a single graph's promising set is dense: at least dense_min vertices (0: never), once
+// its list is complete.
+__device__ __forceinline__ bool dense_promising(const LoopCtl* ctl, int32_t dense_min) {
+  return dense_min > 0 && ctl->npromising >= dense_min;
 }
 
 // Workgroups of a batch kernel's grid-stride launch.

@@ -173,7 +173,7 @@ __global__ void __launch_bounds__(kThreads) k_improve(int32_t n, const int32_t* 
                                                             pcost, ctr, h);
 }
 
-// Large single graphs with pruning: pull form in the iterations whose promising set is dense
+// Large single graphs: pull form in the iterations whose promising set is dense
 // (its marks and domain list then did nothing), over the listed domain in the others.  The
 // domain of a third of 1M 6D vertices is three quarters of them: marking it took 63 to 113 us,
 // more than the rows it saves.
@@ -188,8 +188,8 @@ __global__ void __launch_bounds__(kThreads) k_improve_auto(int32_t n, const Prob
                                                           const int32_t* __restrict__ ext_of,
                                                           int32_t* __restrict__ parent, float* __restrict__ pcost,
                                                           IterCounters* __restrict__ ctr,
-                                                          const float* __restrict__ h) {
-  if (dense_promising(ctl, n))
+                                                          const float* __restrict__ h, int32_t dense_min) {
+  if (dense_promising(ctl, dense_min))
     improve<GW, Q, Idx, false, false, true, kLook, false>(n, nullptr, ps, ctl, gs, rp, col, cst, dlist, ext_of, parent,
                                                           pcost, ctr, h);
   else
@@ -244,10 +244,10 @@ template <int GW, int U, bool L>
 void launch_improve_auto(const StepArgs& a, hipStream_t s) {
   if (a.nnz < ((int64_t)1 << 32) - 64 * GW)
     hipLaunchKernelGGL((k_improve_auto<GW, U, uint32_t, L>), grid_for(a.n, GW), dim3(kThreads), 0, s, a.n, a.ps, a.ctl,
-                       a.g, a.gs, a.rp, a.col, a.cst, a.dlist, a.ext_of, a.parent, a.pcost, a.ctr, a.h);
+                       a.g, a.gs, a.rp, a.col, a.cst, a.dlist, a.ext_of, a.parent, a.pcost, a.ctr, a.h, a.dense_min);
   else
     hipLaunchKernelGGL((k_improve_auto<GW, U, int64_t, L>), grid_for(a.n, GW), dim3(kThreads), 0, s, a.n, a.ps, a.ctl,
-                       a.g, a.gs, a.rp, a.col, a.cst, a.dlist, a.ext_of, a.parent, a.pcost, a.ctr, a.h);
+                       a.g, a.gs, a.rp, a.col, a.cst, a.dlist, a.ext_of, a.parent, a.pcost, a.ctr, a.h, a.dense_min);
 }
 
 template <int GW, int U, bool L>
@@ -273,9 +273,9 @@ void launch_improve_b(const StepArgs& a, hipStream_t s) {
     launch_improve_t<GW, U, true, false>(a, s);
   else if (a.truncated)
     launch_improve_t<GW, U, false, true>(a, s);
-  else if (a.dense && a.lookahead)
+  else if (a.dense_min && a.lookahead)
     launch_improve_auto<GW, U, true>(a, s);
-  else if (a.dense)
+  else if (a.dense_min)
     launch_improve_auto<GW, U, false>(a, s);
   else
     launch_improve_t<GW, U, false, false>(a, s);

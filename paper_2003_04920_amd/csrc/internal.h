@@ -313,7 +313,7 @@ struct StepArgs {
   int blocks;                // batches: workgroups of each grid-stride launch
   bool pull;                 // single graphs: Improve over every slot, from the signed g
   float* gs;                 // pull, dense: g with the promising set as signs (n entries of room)
-  bool dense;                // single graphs, marks: pull form where the promising set is dense
+  int32_t dense_min;         // single graphs, marks: pull form from this many promising vertices on (0: never)
 };
 void launch_promising_signs(const StepArgs& a, hipStream_t s);
 constexpr int kRowVariants = 4;

@@ -114,12 +114,12 @@ __global__ void __launch_bounds__(kThreads) k_domain_list(int32_t n, LoopCtl* __
                                                          uint8_t* __restrict__ stamp, int32_t* __restrict__ dlist,
                                                          const int32_t* __restrict__ prob,
                                                          const ProblemState* __restrict__ ps,
-                                                         const int32_t* __restrict__ tiles, int dense) {
+                                                         const int32_t* __restrict__ tiles, int32_t dense_min) {
   if (ctl->any_active == 0) return;  // every problem has converged
   const uint32_t epoch = ctl->epoch;
   const uint8_t ep = (uint8_t)epoch;
   const bool wrap = (epoch & 0xffu) == 0xffu;
-  if (dense && !wrap && dense_promising(ctl, n)) return;  // Improve takes every row
+  if (!wrap && dense_promising(ctl, dense_min)) return;  // Improve takes every row
   const int64_t units = prob ? tile_units(ctl, n, kThreads * kListPer) : 1;
   for (int64_t wu = prob ? blockIdx.x : 0; wu < units; wu += prob ? gridDim.x : 1) {
   const int64_t bbase =
@@ -353,13 +353,13 @@ __global__ void __launch_bounds__(kThreads) k_mark_rows(const ProblemState* __re
                                                        const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
                                                        const float* __restrict__ cst, const float* __restrict__ g,
                                                        const float* __restrict__ h, uint8_t* __restrict__ stamp,
-                                                       int32_t dense_n) {
+                                                       int32_t dense_min) {
   constexpr int kSlots = tab_slots<GW>();
   constexpr int kPer = kSlots / kThreads;
   __shared__ int32_t keys[kSlots];
   __shared__ uint32_t offer[kLook ? kSlots : 1];  // best offer (binary32 bits, >= 0) per position
   if (ctl->any_active == 0) return;
-  if (dense_n && dense_promising(ctl, dense_n)) return;  // Improve takes every row
+  if (dense_promising(ctl, dense_min)) return;  // Improve takes every row
   const int64_t cnt = ctl->npromising;
   const uint8_t ep = (uint8_t)ctl->epoch;
   const int64_t step = (int64_t)gridDim.x * (kThreads / GW);  // one pass when the grid covers the list
@@ -453,16 +453,16 @@ void launch_mark_t(const StepArgs& a, hipStream_t s) {
     const dim3 pgrid((unsigned)((a.n + per_block - 1) / per_block));
     if (a.truncated)
       hipLaunchKernelGGL(k_promising_list<true>, pgrid, dim3(kThreads), 0, s, a.n, a.ps, a.ctl, a.g, a.h, a.stamp,
-                         a.plist, a.ctr, a.word, a.prune, a.rp, a.dense ? a.gs : nullptr);
+                         a.plist, a.ctr, a.word, a.prune, a.rp, a.dense_min ? a.gs : nullptr);
     else
       hipLaunchKernelGGL(k_promising_list<false>, pgrid, dim3(kThreads), 0, s, a.n, a.ps, a.ctl, a.g, a.h, a.stamp,
-                         a.plist, a.ctr, a.word, a.prune, a.rp, a.dense ? a.gs : nullptr);
+                         a.plist, a.ctr, a.word, a.prune, a.rp, a.dense_min ? a.gs : nullptr);
     const bool narrow = a.nnz < ((int64_t)1 << 32) - 64 * GW;
     const int div = a.n >= kMarkRowsHalfGridMin ? kMarkRowsGridDiv : 1;
     const dim3 rgrid = grid_for((a.n + div - 1) / div, GW);
 #define PIRRT_MARK_ROWS(I, L)                                                                                   \
   hipLaunchKernelGGL((k_mark_rows<GW, U, I, L>), rgrid, dim3(kThreads), 0, s, a.ps, a.ctl, a.plist, a.rp, a.col, \
-                     a.cst, a.g, a.h, a.stamp, a.dense ? a.n : 0)
+                     a.cst, a.g, a.h, a.stamp, a.dense_min)
     if (narrow) {
       if (a.lookahead) PIRRT_MARK_ROWS(uint32_t, true); else PIRRT_MARK_ROWS(uint32_t, false);
     } else {
@@ -544,7 +544,7 @@ void launch_domain_list(const StepArgs& a, hipStream_t s) {
   static_assert(kThreads * kListPer == kTileSlots, "one domain-list workgroup per tile");
   const dim3 grid = a.prob ? batch_grid(a.n, (int)per_block, a.blocks) : dim3((unsigned)((a.n + per_block - 1) / per_block));
   hipLaunchKernelGGL(k_domain_list, grid, dim3(kThreads), 0, s, a.n, a.ctl, a.stamp, a.dlist, a.prob, a.ps,
-                     a.tiles, a.dense ? 1 : 0);
+                     a.tiles, a.dense_min);
 }
 
 // Variants: lanes per row x quads per lane in flight (GW x Q x 4 entries per pass).

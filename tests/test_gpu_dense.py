@@ -61,3 +61,19 @@ def test_many_iterations(P, share):
     h[int(share * n):n - 1] = np.inf  # never promising
     st = same("chain", G, R, 0, n - 1, h)
     assert st["iterations"] > min(255, int(share * n) - 5)
+
+
+def test_without_pruning(P):
+    """Promising sets that grow from a few vertices to all of them (a root far below the one
+    the policy was built for), and one that stays at a component of two."""
+    n = 6000
+    rng = np.random.default_rng(3)
+    b = W.build_rows(rng.random((n, 2)), 0, n, W.radius(n, 2), free(2))
+    rows = (np.concatenate([b.row_ptr, b.row_ptr[-1] + np.array([0, 1])]), np.append(b.col, np.int32(n)),
+            np.append(b.cost, np.float32(0.5)))
+    G, R = pair(P, W.Batch(0, n + 2, *rows, 0.0))
+    seen = []
+    for root, goal in ((n - 1, 0), (n, n + 1), (0, n - 1), (n // 2, 5)):
+        st = same(root, G, R, root, goal, None, False)
+        seen.append(st["sum_P"] / st["iterations"])
+    assert min(seen) < 3 and max(seen) > n / 3
