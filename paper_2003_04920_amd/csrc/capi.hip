@@ -1532,7 +1532,12 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
   int64_t done_iters = 0;
   bool delivered = false;  // the policy and the state came with the loop's last wait
   // The loop's wait: `last` (the planned iterations are through) fetches the results too, which
-  // saves a round trip when it really was the last.
+  // saves a round trip when it really was the last.  When it was not, they are written again: a
+  // few us for device buffers, but a copy of pageable memory for host ones, which wait for the
+  // end past kEarlyHostMax vertices.  Two goals in turn, 51 and 9 iterations or 14 and 8, a pair
+  // of calls with host arrays, early against not: 20,000 6D vertices 583 / 674 us, 100,000
+  // 935 / 895, 400,000 2,561 / 2,245, 1M 5,543 / 5,105.
+  constexpr int32_t kEarlyHostMax = 1 << 16;
   auto wait_loop = [&](bool last) -> int {
     int r;
     if (last) {
@@ -1600,7 +1605,8 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
     G->prev_key = key1;
     G->have_prev_key = true;
     int64_t plan = G->last_iterations > 0 ? G->last_iterations : 8;
-    bool planned = G->last_iterations > 0;
+    const bool costly = out && (out->g || out->parent) && out->mem_kind == PIRRT_MEM_HOST && n > kEarlyHostMax;
+    bool planned = G->last_iterations > 0 && !costly;
     for (;;) {
       const int k = plan >= 8 ? 3 : plan >= 4 ? 2 : plan >= 2 ? 1 : 0;
       take_jumps(done_iters);
