@@ -17,6 +17,7 @@
 // vertices (one per thread) and streams the earlier points through LDS in tiles every
 // thread reads by broadcast, twice (count, then write candidates in ascending u); the
 // segment tests then run once per candidate and a scan compacts the survivors into rows.
+#include <stdlib.h>
 #include <string.h>
 
 #include <algorithm>
@@ -370,6 +371,9 @@ struct pirrt_rrg {
   int32_t room = 128;      // candidates a row is expected to have at most
   bool wide = false;       // the last search met rows of more than kSearchRowMax candidates
   bool outside = false;    // a point outside the unit cube: no matrix-core search
+  // PIRRT_FAULT_INJECT=search at create: the next search finds no room for its candidate lists,
+  // as if the device allocation had failed
+  bool fault_search = false;
   float* hbuf = nullptr;
   int64_t hcap = 0;
   // learned sampler scratch (at most kSelMax candidates)
@@ -533,7 +537,8 @@ int ensure_rows(pirrt_rrg* R, int64_t need, int64_t keep) {
 }
 
 // The rows by the matrix-core search.  *done stays false where that search does not
-// apply (points outside the unit cube, rows of more than kSearchRowWide candidates).
+// apply (points outside the unit cube, rows of more than kSearchRowWide candidates, no memory
+// for its lists).
 // Lists that turn out too short are made longer and the slab searched again; the room
 // is remembered, so a handle learns the density of its scene once.
 int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direct, int64_t* nnz, bool* done,
@@ -579,24 +584,26 @@ int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direc
     const int64_t slab = std::min(rows - row0, std::max<int64_t>(kSearchPad, kSlabEntries / stride));
     a.row0 = row0;
     a.rows = (int32_t)slab;
+    // (without room for the lists the all-pairs search, whose memory goes by the rows' entries)
     if (slab * stride > R->scand_cap) {
       rfree(R, R->scand);  // (candidates and costs in one piece)
       R->scand_cap = 0;
-      if (!ralloc(R, &R->scand, 2 * slab * stride))
-        return rfail(R, PIRRT_ENOMEM, "device allocation of candidate lists failed");
+      if (R->fault_search || !ralloc(R, &R->scand, 2 * slab * stride)) {
+        R->fault_search = false;
+        return PIRRT_OK;
+      }
       R->scand_cap = slab * stride;
     }
     if (slab * a.nch > R->scnt_cap) {
       rfree(R, R->scnt);
       R->scnt_cap = 0;
-      if (!ralloc(R, &R->scnt, slab * a.nch)) return rfail(R, PIRRT_ENOMEM, "device allocation of list lengths failed");
+      if (!ralloc(R, &R->scnt, slab * a.nch)) return PIRRT_OK;
       R->scnt_cap = slab * a.nch;
     }
     if (slab + 1 > R->sdeg_cap) {
       rfree(R, R->sdeg); rfree(R, R->soff);
       R->sdeg_cap = 0;
-      if (!ralloc(R, &R->sdeg, slab + 1) || !ralloc(R, &R->soff, slab + 1))
-        return rfail(R, PIRRT_ENOMEM, "device allocation of row lengths failed");
+      if (!ralloc(R, &R->sdeg, slab + 1) || !ralloc(R, &R->soff, slab + 1)) return PIRRT_OK;
       R->sdeg_cap = slab + 1;
     }
     if ((rc = ensure_scan(R, slab + 1))) return rc;
@@ -839,6 +846,8 @@ int pirrt_rrg_create(pirrt_rrg** out, const pirrt_rrg_config* cfg) {
   R->stream = (hipStream_t)cfg->hip_stream;
   R->d = d;
   R->nobs = m;
+  const char* fault = getenv("PIRRT_FAULT_INJECT");
+  R->fault_search = fault && strcmp(fault, "search") == 0;
   // points, their records and the sampler's candidates
   if ((size_t)cfg->point_capacity <= Arena::kDirect / (sizeof(double) * d))
     R->arena.expect((size_t)cfg->point_capacity * (20 * (size_t)d + 80));
