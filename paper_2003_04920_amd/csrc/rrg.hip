@@ -12,11 +12,11 @@
 //   heuristic: binary32 rounding of the binary64 distance to the goal.
 //
 // The radius search runs on the matrix cores (search.hip) while every point lies in the
-// unit cube and no row has more than kSearchRowWide candidates.  Otherwise it is done in
-// binary64 over all earlier vertices (k_radius): a workgroup owns 256 consecutive new
-// vertices (one per thread) and streams the earlier points through LDS in tiles every
-// thread reads by broadcast, twice (count, then write candidates in ascending u); the
-// segment tests then run once per candidate and a scan compacts the survivors into rows.
+// unit cube and there is memory for its candidate lists.  Otherwise it is done in binary64
+// over all earlier vertices (k_radius): a workgroup owns 256 consecutive new vertices (one per
+// thread) and streams the earlier points through LDS in tiles every thread reads by broadcast,
+// twice (count, then write candidates in ascending u); the segment tests then run once per
+// candidate and a scan compacts the survivors into rows.
 #include <stdlib.h>
 #include <string.h>
 
@@ -325,6 +325,7 @@ inline unsigned blocks(int64_t n) { return (unsigned)((n + kThreads - 1) / kThre
 }  // namespace
 
 constexpr int kHostWords = 4;
+constexpr int32_t kRoomMax = 4096;  // candidates of a row that later searches make room for
 
 struct pirrt_rrg {
   Arena arena;
@@ -537,8 +538,7 @@ int ensure_rows(pirrt_rrg* R, int64_t need, int64_t keep) {
 }
 
 // The rows by the matrix-core search.  *done stays false where that search does not
-// apply (points outside the unit cube, rows of more than kSearchRowWide candidates, no memory
-// for its lists).
+// apply (points outside the unit cube, no memory for its lists).
 // Lists that turn out too short are made longer and the slab searched again; the room
 // is remembered, so a handle learns the density of its scene once.
 int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direct, int64_t* nnz, bool* done,
@@ -575,11 +575,20 @@ int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direc
   const int64_t groups = rows >= kSearchWideRows ? kSearchWideRows / 512 : (rows + 127) / 128;
   int64_t nch = (kSearchGroups + groups - 1) / groups;
   nch = std::max<int64_t>(1, std::min<int64_t>({nch, kSearchMaxChunks, (R->n + kSearchPad - 1) / kSearchPad}));
-  a.chunk = ((R->n + nch - 1) / nch + kSearchPad - 1) / kSearchPad * kSearchPad;
-  a.nch = (int32_t)((R->n + a.chunk - 1) / a.chunk);
+  auto cut = [&] {
+    if (a.wide) nch = std::max(nch, (R->n + kSearchWindow - 1) / kSearchWindow);
+    a.chunk = ((R->n + nch - 1) / nch + kSearchPad - 1) / kSearchPad * kSearchPad;
+    a.nch = (int32_t)((R->n + a.chunk - 1) / a.chunk);
+  };
+  cut();
   a.cap = a.nch == 1 ? R->room : std::max(16, (2 * R->room / a.nch + 3) / 4 * 4);
   int64_t base = 0;
   for (int64_t row0 = 0; row0 < rows;) {
+    if (a.wide) cut();
+    if (a.wide && a.nch > kSearchMaxChunks) {  // more ids than the wide finish orders
+      R->wide = false;
+      return PIRRT_OK;
+    }
     const int64_t stride = (int64_t)a.nch * a.cap;
     const int64_t slab = std::min(rows - row0, std::max<int64_t>(kSearchPad, kSlabEntries / stride));
     a.row0 = row0;
@@ -625,20 +634,18 @@ int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direc
       R->outside = true;
       return PIRRT_OK;
     }
-    if (st->listed > kSearchRowWide || st->most > kSearchRowWide) return PIRRT_OK;
     if (st->listed || st->most > kSearchRowMax) a.wide = true;
     if (st->listed) continue;  // the same slab again, a workgroup a row
     if (st->most) {  // longer lists, the same slab again
-      a.cap = (st->most + st->most / 4 + 3) / 4 * 4;
-      R->room = std::max(R->room, a.nch == 1 ? a.cap : std::min(a.cap * a.nch / 2, kSearchRowWide));
+      a.cap = (int32_t)(std::min<int64_t>(st->most + st->most / 4, a.chunk) + 3) / 4 * 4;
+      R->room = std::max(R->room, (int32_t)std::min<int64_t>(a.nch == 1 ? a.cap : (int64_t)a.cap * a.nch / 2, kRoomMax));
       continue;
     }
     if (own && st->nnz > R->col_cap) {
       if ((rc = ensure_rows(R, st->nnz, base))) return rc;
       continue;
     }
-    if (a.wide && !st->wide && row0 + slab >= rows) R->wide = false;
-    if (st->wide) R->wide = true;
+    if (a.wide) R->wide = st->wide != 0;
     base = st->nnz;
     row0 += slab;
     *wrote = !own;

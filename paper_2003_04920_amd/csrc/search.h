@@ -10,13 +10,13 @@ namespace pirrt {
 struct SearchState {
   int32_t outside;  // some point lies outside the unit cube
   int32_t most;     // largest candidate count of a list that was too short (0: none was)
-  int32_t listed;   // largest candidate count of a row past the finish's room (0: none)
-  int32_t wide;     // largest candidate count of a row past kSearchRowMax, wide finish (0: none)
+  int32_t listed;   // largest candidate count of a row past kSearchRowMax (0: none; not where wide)
+  int32_t wide;     // wide finish: some row has more than kSearchRowMax candidates
   int64_t nnz;      // entries of all rows
 };
 
 constexpr int kSearchRowMax = 512;     // candidates a row may have in the finish by 32 lanes
-constexpr int kSearchRowWide = 4096;   // and in the finish by a workgroup
+constexpr int64_t kSearchWindow = 1 << 18;  // ids the finish by a workgroup orders together
 constexpr int kSearchRecord = 32;      // bytes of a point's packed record
 constexpr int kSearchPad = 256;        // records of room past the last point
 constexpr int kSearchMaxChunks = 64;
@@ -33,7 +33,7 @@ struct SearchArgs {
   ObsView obs;
   const uint4* rec;       // packed records, kSearchRecord bytes each
   int32_t nch;            // candidate lists per row (chunks of earlier points)
-  int64_t chunk;          // earlier points per chunk (a multiple of kSearchPad)
+  int64_t chunk;          // earlier points per chunk (a multiple of kSearchPad; wide: at most kSearchWindow)
   int32_t cap;            // room of one candidate list
   int32_t* cand;          // [rows][nch][cap] candidate ids; the finished rows replace them
   int32_t* cnt;           // [rows][nch] candidates per list

@@ -17,8 +17,7 @@
 // candidates are not neighbours.  The exact binary64 test, the segment test and the
 // ascending order of a row follow per row (k_search_finish), over some sixty candidates
 // instead of all earlier points.  The points must lie in [0, 1]^D (the scene's cube);
-// otherwise, and for rows of more than kSearchRowWide candidates, the caller's
-// all-pairs search in binary64 does the whole job.
+// otherwise the caller's all-pairs search in binary64 does the whole job.
 //
 // Measured (all rows of 200,000 6D points / 1,000 new points against 100,000): the
 // all-pairs search took 26.3 ms / 1.97 ms in its two passes (binary64 VALU bound, and one
@@ -304,35 +303,39 @@ __global__ void __launch_bounds__(kThreads) k_search_finish(int64_t n_old, int64
   if (live && l == 0) deg[row] = kept;
 }
 
-// The same with a workgroup per row, for scenes whose rows hold hundreds or thousands of
-// candidates (samples crowded along a corridor).  A thread ranks kOwn survivors in one pass
-// over the others: the passes read LDS, eight ids at a time, and were most of the time with
-// one.  Measured, batches of 1,000 samples, half of them along a corridor, search and insert:
-// 3.58 -> 1.38 ms at 400,000 6D vertices with 340 entries a row, 4.38 -> 0.89 ms at 100,000 with
-// 515 (before: the all-pairs search in binary64).
-constexpr int kOwn = 4;
+// The same with a workgroup per row, for rows of hundreds of candidates or more (samples
+// crowded along a corridor, connection radii of a good part of the cube).  The survivors of a
+// window of ids are bits in LDS, so their order costs a count over its words, whatever their
+// number: ranking a row's survivors against each other was most of the time from a thousand
+// on, and rows of more than 4,096 candidates went to the all-pairs search after all (all rows of
+// 10,000 2D points with 2,548 entries each 5.9 ms; the all-pairs search alone 3.5).
+//
+// A window is as many chunks of earlier points as fit the bits.  The row's finished ids take the
+// place of its candidates: those of chunks [0, c) are no more than these chunks' candidates,
+// and a window's are read before its ids are written.
+constexpr int kWideThreads = 1024;
 
 template <int D>
-__global__ void __launch_bounds__(kThreads) k_search_finish_wide(int64_t n_old, int64_t row0, double r2,
+__global__ void __launch_bounds__(kWideThreads) k_search_finish_wide(int64_t n, int64_t n_old, int64_t row0, double r2,
                                                                  const double* __restrict__ pts, ObsView ob,
-                                                                 int32_t nch, int32_t cap,
-                                                                 int32_t* __restrict__ cand,
+                                                                 int32_t nch, int64_t chunk, int32_t cap,
+                                                                 int32_t* cand,
                                                                  const int32_t* __restrict__ cnt,
                                                                  float* __restrict__ ccost,
                                                                  int32_t* __restrict__ deg,
                                                                  SearchState* __restrict__ state) {
-  __shared__ int32_t ids[kSearchRowWide + kRankStep];
-  __shared__ float cst[kSearchRowWide];
+  __shared__ uint32_t bits[kSearchWindow / 32 + kSearchWindow / 1024];
   __shared__ NearObstacles<D> spheres;
   __shared__ int32_t at[kSearchMaxChunks + 1];
-  __shared__ int32_t wkept[2][kThreads / kWave];
+  __shared__ int32_t wsum[kWideThreads / kWave];
   static_assert(kSearchMaxChunks <= kWave, "one wave adds up the lists");
   if (state->outside || state->most) return;
   spheres.load(ob);
-  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+  const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
   const int64_t row = blockIdx.x;
   if (wave == 0) {
-    int incl = lane < nch ? cnt[row * nch + lane] : 0;
+    const int k = lane < nch ? cnt[row * nch + lane] : 0;
+    int incl = k;
 #pragma unroll
     for (int off = 1; off < kWave; off <<= 1) {
       const int y = __shfl_up(incl, off, kWave);
@@ -342,90 +345,83 @@ __global__ void __launch_bounds__(kThreads) k_search_finish_wide(int64_t n_old, 
     if (lane < nch) at[lane + 1] = incl;
   }
   __syncthreads();
-  const int total = at[nch];
-  if (threadIdx.x == 0 && total > kSearchRowMax) atomicMax(&state->wide, total);
-  if (total > kSearchRowWide) {
-    if (threadIdx.x == 0) {
-      atomicMax(&state->listed, total);
-      deg[row] = 0;
-    }
-    return;
-  }
+  auto word = [](int w) { return w + (w >> 5); };  // consecutive words of a thread, other banks
   int32_t* out = cand + row * nch * cap;
   float* outc = ccost + row * nch * cap;
-  for (int c = wave; c < nch; c += kThreads / kWave)
-    for (int i = at[c] + lane; i < at[c + 1]; i += kWave) ids[i] = out[c * cap + i - at[c]];
-  __syncthreads();
   const int64_t v = n_old + row0 + row;
+  // (the rows of the last points have all n to find candidates among)
+  if (t == 0 && at[nch] * n > kSearchRowMax * v && state->wide == 0) state->wide = 1;
   double xv[D];
 #pragma unroll
   for (int k = 0; k < D; ++k) xv[k] = pts[v * D + k];
+  const int per = (int)(kSearchWindow / chunk);
   int kept = 0;
-  for (int i0 = 0, turn = 0; i0 < total; i0 += kThreads, turn ^= 1) {
-    const int i = i0 + (int)threadIdx.x;
-    bool ok = i < total;
-    int32_t u = 0;
-    float w = 0.0f;
-    if (ok) {
-      u = ids[i];
+  for (int c0 = 0; c0 < nch && c0 * chunk < v; c0 += per) {
+    const int c1 = c0 + per < nch ? c0 + per : nch;
+    const int64_t u0 = c0 * chunk, u1 = c1 * chunk < v ? c1 * chunk : v;
+    const int words = (int)((u1 - u0 + 31) / 32);
+    for (int w = t; w < words; w += kWideThreads) bits[word(w)] = 0u;
+    __syncthreads();
+    for (int i = at[c0] + t; i < at[c1]; i += kWideThreads) {
+      int c = c0;  // the list that holds candidate i
+      for (int top = c1; top - c > 1;) {
+        const int mid = (c + top) / 2;
+        if (at[mid] <= i)
+          c = mid;
+        else
+          top = mid;
+      }
+      const int32_t u = out[(int64_t)c * cap + (i - at[c])];
       double xu[D];
 #pragma unroll
       for (int k = 0; k < D; ++k) xu[k] = pts[(int64_t)u * D + k];
       const double d2 = dist2<D>(xu, xv);
-      ok = d2 <= r2 && d2 > 0.0;
-      if (ok) {
-        w = __double2float_rn(__dsqrt_rn(d2));
-        ok = !spheres.segment_blocked(xu, xv, d2, ob);
+      if (d2 <= r2 && d2 > 0.0 && !spheres.segment_blocked(xu, xv, d2, ob)) {
+        const int x = (int)(u - u0);
+        atomicOr(&bits[word(x >> 5)], 1u << (x & 31));
       }
     }
-    const unsigned long long bits = __ballot(ok);
-    if (lane == 0) wkept[turn][wave] = __popcll(bits);
-    __syncthreads();  // every id of this step is read: the survivors go below its end
-    int p = kept;
+    __syncthreads();
+    // the window's ids in order: a run of words a thread
+    const int each = (words + kWideThreads - 1) / kWideThreads;
+    const int w0 = t * each, w1 = w0 + each < words ? w0 + each : words;
+    int mine = 0;
+    for (int w = w0; w < w1; ++w) mine += __popc(bits[word(w)]);
+    int incl = mine;
 #pragma unroll
-    for (int j = 0; j < kThreads / kWave; ++j) {
-      if (j < wave) p += wkept[turn][j];
-      kept += wkept[turn][j];
+    for (int off = 1; off < kWave; off <<= 1) {
+      const int y = __shfl_up(incl, off, kWave);
+      if (lane >= off) incl += y;
     }
-    if (ok) {
-      p += __popcll(bits & ((1ull << lane) - 1ull));
-      ids[p] = u;
-      cst[p] = w;
+    if (lane == kWave - 1) wsum[wave] = incl;
+    __syncthreads();
+    int pos = kept + incl - mine, end = kept;
+#pragma unroll
+    for (int j = 0; j < kWideThreads / kWave; ++j) {
+      if (j < wave) pos += wsum[j];
+      end += wsum[j];
     }
+    for (int w = w0; w < w1; ++w)
+      for (uint32_t m = bits[word(w)]; m; m &= m - 1) out[pos++] = (int32_t)(u0 + 32 * w + __ffs(m) - 1);
+    __syncthreads();
+    for (int i = kept + t; i < end; i += kWideThreads) {
+      double xu[D];
+#pragma unroll
+      for (int k = 0; k < D; ++k) xu[k] = pts[(int64_t)out[i] * D + k];
+      outc[i] = __double2float_rn(__dsqrt_rn(dist2<D>(xu, xv)));
+    }
+    kept = end;
   }
-  __syncthreads();  // (the last step's ids may lie past kept)
-  if (threadIdx.x < kRankStep) ids[kept + threadIdx.x] = INT32_MAX;
-  __syncthreads();
-  for (int i0 = threadIdx.x; i0 < kept; i0 += kOwn * kThreads) {
-    int32_t u[kOwn], rank[kOwn];
-#pragma unroll
-    for (int o = 0; o < kOwn; ++o) {
-      u[o] = i0 + o * kThreads < kept ? ids[i0 + o * kThreads] : 0;
-      rank[o] = 0;
-    }
-    for (int j = 0; j < kept; j += kRankStep)
-#pragma unroll
-      for (int e = 0; e < kRankStep; ++e) {
-        const int32_t x = ids[j + e];
-#pragma unroll
-        for (int o = 0; o < kOwn; ++o) rank[o] += x < u[o];
-      }
-#pragma unroll
-    for (int o = 0; o < kOwn; ++o)
-      if (i0 + o * kThreads < kept) {
-        out[rank[o]] = u[o];
-        outc[rank[o]] = cst[i0 + o * kThreads];
-      }
-  }
-  if (threadIdx.x == 0) deg[row] = kept;
+  if (t == 0) deg[row] = kept;
 }
 
-// Finished rows into CSR.  Up to kPrefixRows rows each workgroup sums the lengths of the
-// rows before its own itself (one launch instead of a scan's three); above, `off` holds
-// their exclusive sums.
-constexpr int kCsrRows = 32;
+// Finished rows into CSR, kCsrRows a workgroup (one where they are long: 181 rows of 10,000
+// entries took 920 us at 32).  Up to kPrefixRows rows each workgroup sums the lengths of the
+// rows before its own itself (one launch instead of a scan's three); above, `off` holds their
+// exclusive sums.
 constexpr int32_t kPrefixRows = 16384;
 
+template <int kCsrRows>
 __global__ void __launch_bounds__(kThreads) k_search_rows(int32_t rows, int32_t stride, const int32_t* __restrict__ deg,
                                                           const int64_t* __restrict__ off,
                                                           const int32_t* __restrict__ cand,
@@ -546,8 +542,8 @@ void launch_search(const SearchArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_search_finish<D>, dim3(blocks_for(a.rows, kFinRows)), dim3(kThreads), 0, s, a.n_old, a.row0, \
                      a.rows, a.radius * a.radius, a.pts, a.obs, a.nch, a.cap, a.cand, a.cnt, a.ccost, a.deg, a.state)
 #define WIDE(D)                                                                                                      \
-  hipLaunchKernelGGL(k_search_finish_wide<D>, dim3((unsigned)a.rows), dim3(kThreads), 0, s, a.n_old, a.row0,        \
-                     a.radius * a.radius, a.pts, a.obs, a.nch, a.cap, a.cand, a.cnt, a.ccost, a.deg, a.state)
+  hipLaunchKernelGGL(k_search_finish_wide<D>, dim3((unsigned)a.rows), dim3(kWideThreads), 0, s, a.n, a.n_old, a.row0, \
+                     a.radius * a.radius, a.pts, a.obs, a.nch, a.chunk, a.cap, a.cand, a.cnt, a.ccost, a.deg, a.state)
   if (a.wide) {
     PIRRT_SEARCH_DIM(a.d, WIDE)
   } else {
@@ -564,9 +560,14 @@ void launch_search_rows(const SearchArgs& a, int64_t base, int64_t capacity, int
     scan_i32_to_i64(a.deg, a.rows, off, scan, s);
     offs = off;
   }
-  hipLaunchKernelGGL(k_search_rows, dim3(blocks_for(a.rows, kCsrRows)), dim3(kThreads), 0, s, a.rows, a.nch * a.cap,
-                     a.deg, offs, a.cand, a.ccost, base, capacity, row_ptr + a.row0, col, cost, a.state,
-                     a.report);
+#define ROWS(R)                                                                                                     \
+  hipLaunchKernelGGL(k_search_rows<R>, dim3(blocks_for(a.rows, R)), dim3(kThreads), 0, s, a.rows, a.nch * a.cap, a.deg, \
+                     offs, a.cand, a.ccost, base, capacity, row_ptr + a.row0, col, cost, a.state, a.report)
+  if (a.wide)
+    ROWS(1);
+  else
+    ROWS(32);
+#undef ROWS
 }
 
 }  // namespace pirrt
