@@ -325,7 +325,7 @@ inline unsigned blocks(int64_t n) { return (unsigned)((n + kThreads - 1) / kThre
 }  // namespace
 
 constexpr int kHostWords = 4;
-constexpr int32_t kRoomMax = 4096;  // candidates of a row that later searches make room for
+constexpr int32_t kRoomMin = 128, kRoomMax = 1 << 16;  // candidates a row is expected to have
 
 struct pirrt_rrg {
   Arena arena;
@@ -369,7 +369,7 @@ struct pirrt_rrg {
   int64_t* soff = nullptr;
   int64_t sdeg_cap = 0;
   SearchState* sstate = nullptr;
-  int32_t room = 128;      // candidates a row is expected to have at most
+  int32_t room = kRoomMin;  // candidates a row is expected to have at most
   bool wide = false;       // the last search met rows of more than kSearchRowMax candidates
   bool outside = false;    // a point outside the unit cube: no matrix-core search
   // PIRRT_FAULT_INJECT=search at create: the next search finds no room for its candidate lists,
@@ -538,9 +538,9 @@ int ensure_rows(pirrt_rrg* R, int64_t need, int64_t keep) {
 }
 
 // The rows by the matrix-core search.  *done stays false where that search does not
-// apply (points outside the unit cube, no memory for its lists).
-// Lists that turn out too short are made longer and the slab searched again; the room
-// is remembered, so a handle learns the density of its scene once.
+// apply (points outside the unit cube, no memory for its lists).  Lists that turn out too
+// short are made longer and the slab searched again; the room is remembered, so a handle
+// learns the density of its scene once, and taken back by halves while lists stay short.
 int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direct, int64_t* nnz, bool* done,
                 bool* wrote) {
   const int64_t rows = R->n - n_old;
@@ -567,30 +567,37 @@ int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direc
   a.rec = R->rec;
   a.state = R->sstate;
   a.wide = R->wide;
+  int32_t floor = 0;  // candidates that a list of this call turned out to hold, and a quarter more
   static_assert(sizeof(SearchState) <= sizeof(int64_t) * kHostWords, "R->host holds it");
   SearchState* st = reinterpret_cast<SearchState*>(R->host);
   a.report = st;
-  // enough workgroups to fill the chip: a row's earlier points are cut into chunks, each
-  // with its own candidate list
-  const int64_t groups = rows >= kSearchWideRows ? kSearchWideRows / 512 : (rows + 127) / 128;
-  int64_t nch = (kSearchGroups + groups - 1) / groups;
-  nch = std::max<int64_t>(1, std::min<int64_t>({nch, kSearchMaxChunks, (R->n + kSearchPad - 1) / kSearchPad}));
-  auto cut = [&] {
-    if (a.wide) nch = std::max(nch, (R->n + kSearchWindow - 1) / kSearchWindow);
-    a.chunk = ((R->n + nch - 1) / nch + kSearchPad - 1) / kSearchPad * kSearchPad;
-    a.nch = (int32_t)((R->n + a.chunk - 1) / a.chunk);
+  // Rows, chunks of earlier points (a candidate list each) and room of a list of the next slab:
+  // enough workgroups to fill the chip, lists as long as rows are expected to need.
+  auto plan = [&](int64_t left) {
+    int64_t slab = std::min(rows, kSlabEntries / (2 * kRoomMin));  // (of the whole call: lists keep their length)
+    for (;;) {
+      const int64_t groups = slab >= kSearchWideRows ? slab / 512 : (slab + 127) / 128;
+      int64_t nch = (kSearchGroups + groups - 1) / groups;
+      nch = std::max<int64_t>(1, std::min<int64_t>({nch, kSearchMaxChunks, (R->n + kSearchPad - 1) / kSearchPad}));
+      if (a.wide) nch = std::max(nch, (R->n + kSearchWindow - 1) / kSearchWindow);
+      a.chunk = ((R->n + nch - 1) / nch + kSearchPad - 1) / kSearchPad * kSearchPad;
+      a.nch = (int32_t)((R->n + a.chunk - 1) / a.chunk);
+      const int32_t room = std::max(a.nch == 1 ? R->room : std::max(16, 2 * R->room / a.nch), floor);
+      a.cap = (int32_t)(std::min<int64_t>(room, a.chunk) + 3) / 4 * 4;
+      const int64_t fits = std::max<int64_t>(kSearchPad, kSlabEntries / ((int64_t)a.nch * a.cap));
+      if (4 * fits > slab) return std::min(left, fits);
+      slab = fits;  // fewer rows than the chunks were cut for: again
+    }
   };
-  cut();
-  a.cap = a.nch == 1 ? R->room : std::max(16, (2 * R->room / a.nch + 3) / 4 * 4);
   int64_t base = 0;
   for (int64_t row0 = 0; row0 < rows;) {
-    if (a.wide) cut();
+    const int64_t slab = plan(rows - row0);
     if (a.wide && a.nch > kSearchMaxChunks) {  // more ids than the wide finish orders
       R->wide = false;
       return PIRRT_OK;
     }
     const int64_t stride = (int64_t)a.nch * a.cap;
-    const int64_t slab = std::min(rows - row0, std::max<int64_t>(kSearchPad, kSlabEntries / stride));
+    a.crowd = R->room > kRoomMin || floor > 0 ? a.cap / 4 : INT32_MAX;
     a.row0 = row0;
     a.rows = (int32_t)slab;
     // (without room for the lists the all-pairs search, whose memory goes by the rows' entries)
@@ -634,18 +641,27 @@ int search_rows(pirrt_rrg* R, int64_t n_old, double radius, const RowsOut* direc
       R->outside = true;
       return PIRRT_OK;
     }
-    if (st->listed || st->most > kSearchRowMax) a.wide = true;
-    if (st->listed) continue;  // the same slab again, a workgroup a row
-    if (st->most) {  // longer lists, the same slab again
-      a.cap = (int32_t)(std::min<int64_t>(st->most + st->most / 4, a.chunk) + 3) / 4 * 4;
-      R->room = std::max(R->room, (int32_t)std::min<int64_t>(a.nch == 1 ? a.cap : (int64_t)a.cap * a.nch / 2, kRoomMax));
-      continue;
+    if (st->listed || st->most > kSearchRowMax) R->wide = a.wide = true;
+    if (st->most) {  // longer lists
+      floor = st->most + st->most / 4;
+      R->room = std::max(R->room, (int32_t)std::min<int64_t>(a.nch == 1 ? floor : (int64_t)floor * a.nch / 2, kRoomMax));
     }
+    if (st->listed || st->most) continue;  // the same slab again
     if (own && st->nnz > R->col_cap) {
-      if ((rc = ensure_rows(R, st->nnz, base))) return rc;
+      // as many as all rows will have if the others are as dense (a row has v earlier points)
+      auto pairs = [&](int64_t r) { return (double)r * ((double)n_old + 0.5 * (double)r); };
+      const double all = (double)st->nnz * pairs(rows) / pairs(row0 + slab);
+      if (all > 1e12 || ensure_rows(R, std::max(st->nnz, (int64_t)all), base))
+        if ((rc = ensure_rows(R, st->nnz, base))) return rc;
       continue;
     }
-    if (a.wide) R->wide = st->wide != 0;
+    // what one crowded place asked for goes as the lists stay short: a handle with room for
+    // 4,096 candidates a row searched 200,000 6D rows in slabs of 2,048, 17.4 ms where 2.6 do
+    if (a.wide && !st->wide) R->wide = a.wide = false;
+    if (!st->crowded) {
+      floor /= 2;
+      R->room = std::max(kRoomMin, R->room / 2);
+    }
     base = st->nnz;
     row0 += slab;
     *wrote = !own;

@@ -12,6 +12,7 @@ struct SearchState {
   int32_t most;     // largest candidate count of a list that was too short (0: none was)
   int32_t listed;   // largest candidate count of a row past kSearchRowMax (0: none; not where wide)
   int32_t wide;     // wide finish: some row has more than kSearchRowMax candidates
+  int32_t crowded;  // some list holds more than SearchArgs::crowd candidates
   int64_t nnz;      // entries of all rows
 };
 
@@ -35,6 +36,7 @@ struct SearchArgs {
   int32_t nch;            // candidate lists per row (chunks of earlier points)
   int64_t chunk;          // earlier points per chunk (a multiple of kSearchPad; wide: at most kSearchWindow)
   int32_t cap;            // room of one candidate list
+  int32_t crowd;          // candidates from which a list speaks against less room
   int32_t* cand;          // [rows][nch][cap] candidate ids; the finished rows replace them
   int32_t* cnt;           // [rows][nch] candidates per list
   float* ccost;           // [rows][nch * cap] costs of the finished rows

@@ -60,6 +60,7 @@ __global__ void __launch_bounds__(kThreads) k_search_pack(int64_t first, int64_t
     state->most = 0;
     state->listed = 0;
     state->wide = 0;
+    state->crowded = 0;
     state->nnz = 0;
   }
   if (i >= n) return;
@@ -214,7 +215,7 @@ constexpr int kRankStep = 8;  // ids compared per step of the ranking
 template <int D>
 __global__ void __launch_bounds__(kThreads) k_search_finish(int64_t n_old, int64_t row0, int32_t rows, double r2,
                                                             const double* __restrict__ pts, ObsView ob, int32_t nch,
-                                                            int32_t cap, int32_t* __restrict__ cand,
+                                                            int32_t cap, int32_t crowd, int32_t* __restrict__ cand,
                                                             const int32_t* __restrict__ cnt,
                                                             float* __restrict__ ccost, int32_t* __restrict__ deg,
                                                             SearchState* __restrict__ state) {
@@ -231,6 +232,7 @@ __global__ void __launch_bounds__(kThreads) k_search_finish(int64_t n_old, int64
   for (int c0 = 0; c0 < nch; c0 += kFinLanes) {
     const int c = c0 + l;
     const int k = live && c < nch ? cnt[row * nch + c] : 0;
+    if (k > crowd && !state->crowded) state->crowded = 1;
     int incl = k;
 #pragma unroll
     for (int off = 1; off < kFinLanes; off <<= 1) {
@@ -319,7 +321,7 @@ template <int D>
 __global__ void __launch_bounds__(kWideThreads) k_search_finish_wide(int64_t n, int64_t n_old, int64_t row0, double r2,
                                                                  const double* __restrict__ pts, ObsView ob,
                                                                  int32_t nch, int64_t chunk, int32_t cap,
-                                                                 int32_t* cand,
+                                                                 int32_t crowd, int32_t* cand,
                                                                  const int32_t* __restrict__ cnt,
                                                                  float* __restrict__ ccost,
                                                                  int32_t* __restrict__ deg,
@@ -343,6 +345,7 @@ __global__ void __launch_bounds__(kWideThreads) k_search_finish_wide(int64_t n, 
     }
     if (lane == 0) at[0] = 0;
     if (lane < nch) at[lane + 1] = incl;
+    if (__ballot(k > crowd) != 0ull && lane == 0 && !state->crowded) state->crowded = 1;
   }
   __syncthreads();
   auto word = [](int w) { return w + (w >> 5); };  // consecutive words of a thread, other banks
@@ -437,6 +440,7 @@ __global__ void __launch_bounds__(kThreads) k_search_rows(int32_t rows, int32_t 
     report->most = state->most;
     report->listed = state->listed;
     report->wide = state->wide;
+    report->crowded = state->crowded;
   }
   if (state->outside || state->most || state->listed) return;
   const int32_t first = blockIdx.x * kCsrRows;
@@ -540,10 +544,11 @@ void launch_search(const SearchArgs& a, hipStream_t s) {
                        a.row0, a.rows, a.rec, ht, a.nch, a.chunk, a.cap, a.cand, a.cnt, a.state);
 #define FINISH(D)                                                                                                   \
   hipLaunchKernelGGL(k_search_finish<D>, dim3(blocks_for(a.rows, kFinRows)), dim3(kThreads), 0, s, a.n_old, a.row0, \
-                     a.rows, a.radius * a.radius, a.pts, a.obs, a.nch, a.cap, a.cand, a.cnt, a.ccost, a.deg, a.state)
+                     a.rows, a.radius * a.radius, a.pts, a.obs, a.nch, a.cap, a.crowd, a.cand, a.cnt, a.ccost, a.deg,          \
+                     a.state)
 #define WIDE(D)                                                                                                      \
   hipLaunchKernelGGL(k_search_finish_wide<D>, dim3((unsigned)a.rows), dim3(kWideThreads), 0, s, a.n, a.n_old, a.row0, \
-                     a.radius * a.radius, a.pts, a.obs, a.nch, a.chunk, a.cap, a.cand, a.cnt, a.ccost, a.deg, a.state)
+                     a.radius * a.radius, a.pts, a.obs, a.nch, a.chunk, a.cap, a.crowd, a.cand, a.cnt, a.ccost, a.deg, a.state)
   if (a.wide) {
     PIRRT_SEARCH_DIM(a.d, WIDE)
   } else {
