@@ -1256,21 +1256,29 @@ struct PolicyOut {
 // 400,000), 1,156, 1,097, 1,115, 1,313 and 1,310 us (6D 500,000); marks alone 2,640 us, 11.8 ms,
 // 20.7 ms and 1,185 us.
 // A batch (64 problems, 1.7M vertices) took 17.4 ms with marks, 17.5 by pull and keeps the marks.
-// Graphs with rows of hundreds of entries (samples crowded along a corridor) do too: few of
-// their vertices are promising at a time, and the kernel with both forms took 4% longer over the
-// listed rows (340 entries a row: 2.58 -> 2.68 ms).
+//
+// Long rows: with hundreds of entries a row the domain of a near goal is a smaller part of the
+// adjacency, and a few thousand such rows leave pull's four lanes a row too few waves.  Marks /
+// pull as above: 3D 4,000 vertices of 684 entries 585 / 464 far, 120 / 178, 196 / 256, 300 / 315;
+// 6D 20,000 of 446 660 / 490, 61 / 117, 78 / 117, 234 / 270; 2D 20,000 of 389 745 / 549, 62 / 88,
+// 89 / 90, 357 / 320; 3D 50,000 of 163 537 / 500, 67 / 82, 218 / 255, 347 / 370.  So kPullRow.
+// The kernel with both forms was 2 to 20% faster than marks on uniform graphs of 135 to 446
+// entries a row, and 4% slower where samples crowd along a corridor (1M vertices of 340 entries,
+// few of them promising at a time: 2.58 -> 2.68 ms).  So it stays with rows up to kDenseRow.
 constexpr int32_t kPullMax = 5 << 15;  // 163,840
 constexpr int64_t kPullEdges = (int64_t)10 << 20;
+constexpr int32_t kPullRow = 400;
 constexpr int32_t kPullAll = 1 << 19;  // without pruning
-constexpr int32_t kDenseRow = 128;
+constexpr int32_t kDenseRow = 256;
 constexpr int32_t kDenseShare = 3;
 
-bool short_rows(const pirrt_graph* G) { return G->nnz <= (int64_t)kDenseRow * G->n; }
+bool rows_to(const pirrt_graph* G, int32_t entries) { return G->nnz <= (int64_t)entries * G->n; }
 
 bool pulls(const pirrt_graph* G, bool prune) {
   if (G->batched || G->truncated || G->pull == 0 || G->pull == 2) return false;
   if (G->pull == 1) return true;
-  return prune ? G->n <= kPullMax && G->nnz <= kPullEdges : G->n <= kPullAll || !short_rows(G);
+  return prune ? G->n <= kPullMax && G->nnz <= kPullEdges && rows_to(G, kPullRow)
+               : G->n <= kPullAll || !rows_to(G, kDenseRow);
 }
 
 // Row splits (lanes a row x quads in flight: see launch_mark and launch_improve).  Rows have
@@ -1416,7 +1424,7 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
   sa.blocks = G->batch_blocks;
   sa.gs = reinterpret_cast<float*>(G->fr1);  // (in the place of the promising list)
   sa.pull = pulls(G, prune);
-  const bool both = !sa.pull && !G->batched && !G->truncated && (G->pull == 2 || (G->pull < 0 && short_rows(G)));
+  const bool both = !sa.pull && !G->batched && !G->truncated && (G->pull == 2 || (G->pull < 0 && rows_to(G, kDenseRow)));
   sa.dense_min = both ? n / kDenseShare + 1 : 0;
   if (both) sa.gs = reinterpret_cast<float*>(G->deg);  // (the list has fr1)
   L.variant = row_variant(G, sa.pull);
