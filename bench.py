@@ -1281,8 +1281,9 @@ def main():
     replan_hbm = {"bytes_per_replan": rb["total"], "by_phase": {k: v for k, v in rb.items() if k != "total"},
                   "achieved": round(rb["total"] / (ms_per_step * 1e-3) / 1e9, 1), "peak": HBM_PEAK_GBS,
                   "unit": "GB/s", "frac": round(rb["total"] / (ms_per_step * 1e-3) / 1e9 / HBM_PEAK_GBS, 4),
-                  "note": "the whole Replan's algorithmic bytes (every phase, counters of the timed call) over "
-                          "the timed ms per Replan"}
+                  "note": "the whole Replan's algorithmic bytes (every phase, counters of the timed call; the marks' "
+                          "and the domain list's in every iteration, though those with a dense promising set skip "
+                          "them: an upper bound) over the timed ms per Replan"}
     log("replan HBM: %s" % json.dumps(replan_hbm))
     out = {
         "metric": "Replan GTEPS + ms/replan (6D 1M-vertex RRG), HBM % peak; plain vs learned",

@@ -47,9 +47,8 @@ struct RawH {
   bool check;
 };
 
-// Validation kernels for device-resident inputs of replan / set_policy.
-
-// parent ids are local to the problem [base, base + len) of each vertex.
+// Validation of a device-resident policy; parent ids are local to the problem
+// [base, base + len) of each vertex.
 __global__ void k_check_policy(int32_t n, const int32_t* __restrict__ parent, const float* __restrict__ pcost,
                                const int32_t* __restrict__ prob, const int64_t* __restrict__ base,
                                int* __restrict__ bad) {
@@ -924,24 +923,24 @@ int insert_rows(pirrt_graph* G, int32_t n_new, const int64_t* row_ptr, const int
     std::swap(G->cst, G->cst2);
     std::swap(G->ecap, G->ecap2);
   } else {
-  // new vertices take the slots after the existing ones; neighbours to slots
-  launch_identity_ids(n_old, n1, G->ext_of, G->slot_of, s, G->prob, new_problem ? (int32_t)G->pbase.size() - 1 : 0);
-  launch_translate(nnz_b, bcol, G->slot_of, G->bslot, s);
-  if (new_problem) {
-    // a new problem shares no edge with the older ones: its rows are appended
-    launch_append(n_new, n_old, G->nnz, G->brp, G->bslot, G->bcost, G->rp, G->col, G->cst, G->add, G->deg, G->rp2,
-                  G->scan_scratch, s);
-    HIP_OR_FAIL(G, hipGetLastError());
-  } else {
-    // adjacency rebuild into the spare arrays, then swap
-    launch_rebuild(n_new, n_old, brp, G->bslot, bcost, G->rp, G->col, G->cst, G->rp2, G->col2, G->cst2, G->add,
-                   G->add0, G->deg, G->scan_scratch, s);
-    HIP_OR_FAIL(G, hipGetLastError());
-    std::swap(G->rp, G->rp2);
-    std::swap(G->col, G->col2);
-    std::swap(G->cst, G->cst2);
-    std::swap(G->ecap, G->ecap2);
-  }
+    // new vertices take the slots after the existing ones; neighbours to slots
+    launch_identity_ids(n_old, n1, G->ext_of, G->slot_of, s, G->prob, new_problem ? (int32_t)G->pbase.size() - 1 : 0);
+    launch_translate(nnz_b, bcol, G->slot_of, G->bslot, s);
+    if (new_problem) {
+      // a new problem shares no edge with the older ones: its rows are appended
+      launch_append(n_new, n_old, G->nnz, G->brp, G->bslot, G->bcost, G->rp, G->col, G->cst, G->add, G->deg, G->rp2,
+                    G->scan_scratch, s);
+      HIP_OR_FAIL(G, hipGetLastError());
+    } else {
+      // adjacency rebuild into the spare arrays, then swap
+      launch_rebuild(n_new, n_old, brp, G->bslot, bcost, G->rp, G->col, G->cst, G->rp2, G->col2, G->cst2, G->add,
+                     G->add0, G->deg, G->scan_scratch, s);
+      HIP_OR_FAIL(G, hipGetLastError());
+      std::swap(G->rp, G->rp2);
+      std::swap(G->col, G->col2);
+      std::swap(G->cst, G->cst2);
+      std::swap(G->ecap, G->ecap2);
+    }
   }
   G->n = n1;
   G->nnz += 2 * nnz_b;
@@ -1288,7 +1287,7 @@ bool pulls(const pirrt_graph* G, bool prune) {
 // vertices 733 / 697 / 692 us, 6D 100,002: 463 / 446 / 465, 8D 200,000: 657 / 552 / 587, 6D
 // 300,000: 980 / 880 / 861, 1M without pruning 3.25 / 3.48 / 3.23 ms.  With marks 8 x 2 is
 // the fastest on single graphs (1M: 2.28 ms, 4 x 4 2.35); a batch's flat passes over all rows
-// of its tiles take 4 x 4 (64 problems 12.8 -> 11.2 ms).
+// of its tiles take 4 x 4 (64 problems, by jumps: 12.8 -> 11.2 ms).
 constexpr int32_t kNarrowPull = 1 << 18;
 
 int row_variant(const pirrt_graph* G, bool pull) {
@@ -1300,7 +1299,8 @@ int row_variant(const pirrt_graph* G, bool pull) {
 // a 36-byte record per vertex more and shorten the climb eightfold.  Measured, link by link
 // against jumps from the start: 2D 20,000 vertices 1,925 / 1,338 us, 200,000: 15.3 / 9.4 ms;
 // 3D 60,001: 883 / 741 us; 6D 100,002: 480 / 480, 400,000: 1,157 / 1,115, 700,000: 1,673 /
-// 1,708, 1M: 2,268 / 2,374; 64 problems of 5,000 to 100,000 vertices 17.3 / 12.9 ms.  Past
+// 1,708, 1M: 2,268 / 2,374; 64 problems of 5,000 to 100,000 vertices, rows by 8 x 2 lanes,
+// 17.3 / 12.9 ms.  Past
 // kJumpMax vertices a problem the records cost more than shallow trees' climbs, so there
 // Replan waits kJumpIterations: a vertex k edges from the root settles in iteration k at the
 // earliest, so one that goes on that long has deep trees (2D 400,000: 31.3 ms link by link,
@@ -1675,8 +1675,9 @@ int run_replan(pirrt_graph* G, int32_t P, const int32_t* root_ids, const int32_t
 //
 // Bound by the two round trips.  The policy moves through pinned memory that one kernel
 // writes and one reads: as copies of pageable vectors (two over, four back, up to three more
-// for device buffers) a call of 302 vertices took 119 us, of which the Replan itself about 40;
-// now 88.
+// for device buffers) a call of 302 vertices on an unchanged graph took 115 us, of which the
+// Replan itself about 40; now 82.  The first call after an insert also copies the adjacency into
+// pageable vectors: 235 and 215 us.
 int run_host_replan(pirrt_graph* G, int32_t root, int32_t goal, const float* h, int mem_kind, bool prune,
                     bool lookahead, float* g_out, int32_t* parent_out, pirrt_stats* stats) {
   auto t_start = std::chrono::steady_clock::now();

@@ -1,17 +1,18 @@
 // Device side of the Replan loop (Alg. 2) for one or many problems: per-problem
 // thresholds, the per-iteration bookkeeping of the convergence test, and the root
-// marks.  The loop itself never waits on the host: each iteration is
-//   mark -> domain list -> improve -> finish -> evaluate -> after-eval (thresholds)
-// and a problem whose Improve switched no parent stops (its threshold becomes
-// -inf, so the later kernels skip it), exactly when the serial loop would break.
+// marks.  The loop itself never waits on the host: an iteration of a batch is
+//   mark -> domain list -> improve -> finish -> evaluate -> after-eval (thresholds),
+// the finish step in a launch of its own or with the walk's jumps; of a single graph
+//   promising list -> marked rows -> domain list -> improve -> evaluate, or
+//   promising signs -> improve -> evaluate,
+// its thresholds with the first kernel and its finish step with the walk.  A problem whose
+// Improve switched no parent stops (its threshold becomes -inf, so the later kernels skip
+// it), exactly when the serial loop would break.
 #include "internal.h"
 
 namespace pirrt {
 
 namespace {
-
-// Mark epochs are stored as their low byte: skip the values whose low byte is 0
-// (the cleared stamp).
 
 // Marks the roots, clears the counters and takes fresh epochs.  The threshold is set
 // to g(goal) as stored before any Evaluate of this Replan (the truncated Evaluate's

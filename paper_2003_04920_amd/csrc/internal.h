@@ -324,12 +324,14 @@ constexpr int kRowVariants = 4;
 // workgroups could not all become resident: nothing was changed); parent, pcost and g are
 // read and written in place (the root's parent and cost untouched).
 //
-// kResidentMax: what fits 16-bit slots and the LDS (10 bytes a vertex).  It is faster than
-// the multi-kernel loop at every size below (one synchronous call, 2D unless noted: 600
-// vertices 119 against 389 us, 2,002: 189 / 726, 8,000: 436 / 1,452, 15,000: 921 / 2,159;
-// 6D 15,000: 316 / 401).  kResidentEdges: entries past a row's first 64 come from memory
-// every iteration, by one workgroup per 128 rows; 4,000 vertices of 3D with 251 neighbours
-// take 184 against 376 us, with 532 (2.1M entries) 482 / 486.
+// kResidentMax: what fits 16-bit slots and the LDS (10 bytes a vertex).  One synchronous call
+// with device arrays, goal in the far corner and goals nearer than 0.1% and 20% of the vertices,
+// the multi-kernel loop against one launch, in us: 2D 600 vertices 196 / 78, 62 / 35, 101 / 50;
+// 2,002: 407 / 138, 63 / 35, 147 / 66; 8,000: 755 / 376, 59 / 42, 239 / 153; 15,000: 1,138 /
+// 820, 60 / 64, 263 / 260; 6D 5,000: 179 / 93, 66 / 39, 102 / 60; 15,000: 240 / 236, 62 / 61,
+// 165 / 165.  kResidentEdges: entries past a row's first 64 come from memory every iteration, by
+// one workgroup per 128 rows; 4,000 vertices of 3D with 355 entries a row take 187 us against
+// 338.
 constexpr int32_t kResidentMax = 15360;
 constexpr int64_t kResidentEdges = 1 << 21;
 constexpr int kResidentGroups = 128;  // workgroups at most
