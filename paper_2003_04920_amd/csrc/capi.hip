@@ -2312,12 +2312,12 @@ int pirrt_promising_count(pirrt_graph* G, int32_t goal, const float* h, int64_t 
       hd = h + first;
     }
   }
-  if (count <= kPromisingBlockMax) {
-    launch_count_promising(first, count, G->hslot[(size_t)goal], G->slot_of, G->g, hd, &G->host->hops, s);
+  if (count <= (h && mem_kind == PIRRT_MEM_HOST ? kPromisingBlockHost : kPromisingBlockMax)) {
+    launch_count_promising(true, first, count, G->hslot[(size_t)goal], G->slot_of, G->g, hd, &G->host->hops, s);
     HIP_OR_FAIL(G, hipGetLastError());
   } else {
     HIP_OR_FAIL(G, hipMemsetAsync(G->dhops, 0, sizeof(unsigned long long), s));
-    launch_count_promising(first, count, G->hslot[(size_t)goal], G->slot_of, G->g, hd, G->dhops, s);
+    launch_count_promising(false, first, count, G->hslot[(size_t)goal], G->slot_of, G->g, hd, G->dhops, s);
     HIP_OR_FAIL(G, hipGetLastError());
     HIP_OR_FAIL(G, hipMemcpyAsync(&G->host->hops, G->dhops, sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
   }

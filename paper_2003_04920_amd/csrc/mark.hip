@@ -529,12 +529,12 @@ __global__ void __launch_bounds__(kCountThreads) k_count_promising_block(int64_t
 
 }  // namespace
 
-void launch_count_promising(int64_t first, int64_t count, int32_t goal_slot, const int32_t* slot_of, const float* g,
-                            const float* h, unsigned long long* out, hipStream_t s) {
-  if (count > 0 && count <= kPromisingBlockMax)
+void launch_count_promising(bool block, int64_t first, int64_t count, int32_t goal_slot, const int32_t* slot_of,
+                            const float* g, const float* h, unsigned long long* out, hipStream_t s) {
+  if (block)
     hipLaunchKernelGGL(k_count_promising_block, dim3(1), dim3(kCountThreads), 0, s, first, (int32_t)count, goal_slot,
                        slot_of, g, h, out);
-  else if (count > 0)
+  else
     hipLaunchKernelGGL(k_count_promising, dim3((unsigned)((count + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
                        first, count, goal_slot, slot_of, g, h, out);
 }

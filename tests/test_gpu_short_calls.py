@@ -96,3 +96,17 @@ def test_refused_in_every_mode(P, monkeypatch, n, kw):
         c = H.replan(root, n - 1, good, True, **kw)
         assert all(np.array_equal(x.cpu().numpy() if x.is_cuda else x, y.cpu().numpy()) for x, y in zip(a[:2], c[:2]))
         assert a[2]["iterations"] == c[2]["iterations"] and a[2]["sum_P"] == c[2]["sum_P"]
+
+
+@pytest.mark.parametrize("count", [4095, 4096, 4097])
+def test_promising_counts_host_heuristic(P, count):
+    """Where a heuristic copied from host memory leaves the one workgroup for the counter."""
+    n, first = 9000, 77
+    rng = np.random.default_rng(count)
+    G = P.Graph()
+    G.insert_rows(W.path_graph(n, rng.random(n - 1).astype(np.float32)))
+    g = G.get_policy()[0]
+    h = rng.random(n).astype(np.float32) * 3
+    want = int(np.sum((g + h).astype(np.float32)[first:first + count] < g[n // 2]))
+    for _ in range(2):
+        assert G.promising_count(n // 2, h, first, count) == want
